@@ -180,6 +180,88 @@ def run(state):
     return state["outputs"]
 
 
+def exact(case, seed):
+    """Every member's outputs with its layers written out in plain torch, all values in 64 bits (nothing is rounded in storage)."""
+    fams = families(case)
+    models = [model_of(case, fam) for fam in fams]
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    stored = torch.float32 if case["dtype"] == "f32" else torch.bfloat16
+    tiny = fams[0] == "tiny"
+
+    def image_batch(b):
+        shape = (b, case["side"], case["side"], 3)
+        x = torch.rand(shape, generator=g, device="cuda") if tiny else torch.randn(shape, generator=g, device="cuda")
+        return x.to(stored)
+
+    serve = case["mode"] == "serve"
+    inputs = [image_batch(b) for b in (batches(case) if serve else [case["batch"]])]
+    outs = []
+    for i, (fam, model) in enumerate(zip(fams, models)):
+        blob = weights(model, seed * 64 + i + 1, tiny).cuda()
+        x = inputs[i if serve else 0].double().permute(0, 3, 1, 2)
+        outs.append(torch.cat([forward64(model, blob, part) for part in x.split(8)]).float())
+    return outs
+
+
+def activation64(y, act):
+    if act == zoo.RELU:
+        return y.clamp(min=0)
+    if act == zoo.RELU6:
+        return y.clamp(0, 6)
+    gates = {zoo.HARDSWISH: lambda v: v * (v + 3).clamp(0, 6) / 6, zoo.HARDSIGMOID: lambda v: (v + 3).clamp(0, 6) / 6,
+             zoo.SILU: lambda v: v * torch.sigmoid(v), zoo.SIGMOID: torch.sigmoid, zoo.NONE: lambda v: v}
+    return gates[act](y)
+
+
+def forward64(model, blob, x):
+    """One model in 64 bits on an NCHW batch; a layer's value is dropped after its last reader."""
+    stored, size = (torch.float32, 4) if model.dtype == "f32" else (torch.bfloat16, 2)
+    last = {}
+    for i, layer in enumerate(model.layers):
+        last[layer.input] = last[layer.residual] = i
+    values = {zoo.MODEL_INPUT: x}
+    for i, layer in enumerate(model.layers):
+        v, n = values[layer.input], x.shape[0]
+        other = values.get(layer.residual)
+        kh, kw = layer.k, layer.kw or layer.k
+        if layer.op in (zoo.CONV, zoo.DWCONV, zoo.FC):
+            groups = {zoo.CONV: layer.groups, zoo.DWCONV: layer.cout, zoo.FC: 1}[layer.op]
+            if layer.op == zoo.FC:
+                v, kh, kw, stride, pad = v.reshape(n, layer.cin, 1, 1), 1, 1, 1, 0
+            else:
+                stride = layer.stride
+                pad = layer.pad if kh == kw else (layer.pad if kh > 1 else 0, layer.pad if kw > 1 else 0)
+            count = layer.cout * (v.shape[1] // groups) * kh * kw
+            w = blob[layer.w_off:layer.w_off + count * size].view(stored).double().view(groups, layer.cout // groups, -1)
+            b = blob[layer.b_off:layer.b_off + 4 * layer.cout].view(torch.float32).double()
+            y = torch.empty((n, layer.cout, layer.out_h, layer.out_w), dtype=torch.float64, device=x.device)
+            for image in range(n):
+                taps = torch.nn.functional.unfold(v[image:image + 1].contiguous(), (kh, kw), padding=pad, stride=stride)
+                y[image] = torch.matmul(w, taps.view(groups, w.shape[2], -1)).view(y.shape[1:])
+            y += b.view(1, -1, 1, 1)
+            y = activation64(y if other is None else y + other, layer.act)
+        elif layer.op == zoo.MAXPOOL:
+            y = torch.nn.functional.max_pool2d(v, kh, layer.stride, layer.pad, ceil_mode=layer.ceil)
+        elif layer.op == zoo.AVGPOOL:
+            y = torch.nn.functional.avg_pool2d(v, kh, layer.stride, layer.pad)
+        elif layer.op == zoo.GAP:
+            y = v.mean((2, 3), keepdim=True)
+        elif layer.op == zoo.SOFTMAX:
+            y = torch.softmax(v, 1)
+        elif layer.op == zoo.CONCAT:
+            y = torch.cat([v, other], 1)
+        elif layer.op == zoo.MUL:
+            y = v * other
+        elif layer.op == zoo.SLICE:
+            y = v[:, layer.first:layer.first + layer.cout]
+        else:   # shuffle: the channels as a groups x rest matrix, transposed
+            y = v.view(n, layer.groups, -1, *v.shape[2:]).transpose(1, 2).reshape(v.shape)
+        values[i] = y
+        for done in [k for k in values if last.get(k, i) <= i and k != i]:
+            del values[done]
+    return values[model.output].reshape(x.shape[0], -1)
+
+
 def work(case):
     """Images and weights in once, logits out once; two operations per multiply-add."""
     size = 4 if case["dtype"] == "f32" else 2
