@@ -150,4 +150,32 @@ __device__ __forceinline__ void runs_to_fragments(const uint32_t (&pk)[4][2], ui
     }
 }
 
+
+// Finishes four consecutive features [o, o + 4) of output row n from their complete fp32 sums: bias
+// (and residual), activation, zero in the padded features, store.  p: the problem's slot in the launch.
+template <typename TA>
+__device__ __forceinline__ void finish_row4(const KArgs& a, const Desc& d, int p, int n, int o, float4 sum) {
+  const float4 b = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(a.wbase + d.b_off) + o);
+  float v[4] = {sum.x + b.x, sum.y + b.y, sum.z + b.z, sum.w + b.w};
+  if (d.r_off != kNone) {
+    const TA* r = reinterpret_cast<const TA*>(a.abase + d.r_off) + (int64_t)n * d.Cop + o;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] += ld(r + t);
+  }
+  activate_n<4>(v, d.act);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) v[t] = (o + t < d.Co) ? v[t] : 0.0f;
+  if (d.ext) {
+    float* y = static_cast<float*>(a.ext_out[p]) + (int64_t)n * d.Co + o;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (o + t < d.Co) y[t] = v[t];
+  } else if (sizeof(TA) == 4 || d.out_f32) {
+    *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.abase + d.y_off) + (int64_t)n * d.ys + o) = make_float4(v[0], v[1], v[2], v[3]);
+  } else {
+    *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(a.abase + d.y_off) + (int64_t)n * d.ys + o) =
+        make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+  }
+}
+
 }  // namespace fi

@@ -23,7 +23,7 @@ inline uint64_t align_up(uint64_t v, uint64_t a = kAlign) { return (v + a - 1) /
 // Kernel families.  A launch runs one family over 1..FI_MAX_GROUP problems.
 enum Kind : int32_t {
   K_STAGE = 0,        // caller's NHWC input -> channel-padded copy in the activation arena
-  K_CONV_DIRECT = 1,  // one thread per output element (fp32 models, fp32-activation members)
+  K_CONV_DIRECT = 1,  // one thread per output element (fp32 models beyond what K_CONV_KWAVE addresses)
   K_CONV_MFMA = 2,    // implicit GEMM on the matrix cores (bf16 weights, bf16 activations)
   K_DWCONV = 3,
   K_MAXPOOL = 4,
@@ -39,6 +39,7 @@ enum Kind : int32_t {
   K_STEM = 14,        // a 7x7 stride-2, 3x3 stride-1 or 3x3 stride-2 convolution over the 4-channel model input, from an input patch
                       // in LDS (tile bit 0 clear), or a stride-2 one and the 3x3 stride-2 max-pool that alone reads it (tile bit 0
                       // set: the pool node carries the launch); tile bits 1.. = which convolution
+  K_CONV_KWAVE = 15,  // implicit GEMM whose waves share the reduction of one tile (fp32 models)
   K_NKINDS
 };
 
@@ -53,6 +54,16 @@ enum Tile : int32_t { T_128x128 = 0, T_128x64 = 1, T_64x64 = 2, T_256x128 = 3, T
 #endif
 FI_HD inline int tile_bm(int t) { return (t == T_256x128 || t == T_256x64) ? 256 : t == T_64x64 ? 64 : 128; }
 FI_HD inline int tile_bn(int t) { return (t == T_128x128 || t == T_256x128 || t == T_128x128_DEEP) ? 128 : 64; }
+
+// Tiles of the K_CONV_KWAVE kernels: side of the square tile x waves that share its reduction.  KW_SCALAR is added for
+// fp32 tensors whose channel stride four does not divide.
+enum KwaveTile : int32_t { KW_64x4 = 0, KW_32x8 = 1, KW_NTILES, KW_SCALAR = 8 };
+FI_HD inline int kwave_side(int t) { return t == KW_32x8 ? 32 : 64; }
+// What these kernels can address: input and weights through 32-bit byte offsets (a tile of rows past the last weight
+// row included), row and reduction indices below 2^24.
+inline bool kwave_fits(int64_t batch, int64_t H, int64_t W, int64_t Cp, int64_t Ho, int64_t Wo, int64_t Co, int64_t taps, int64_t Kp, int es) {
+  return batch * Ho * Wo < (1ll << 24) && taps * Cp + 64 < (1ll << 24) && (batch * H * W + 1) * Cp * es < (1ll << 31) && (Co + 64) * Kp * es < (1ll << 31);
+}
 
 // Problem descriptor: one node of the fused DAG, batch independent, handed to the kernels
 // as launch arguments.  Tensor offsets are relative to the activation region, weight offsets
@@ -182,6 +193,9 @@ int static_scratch(void** ptr, uint64_t* bytes);
 
 // Implemented in fi_chain.hip: a K_CHAIN launch (problems are triples of descriptors).  Returns a hipError_t as int.
 int launch_chain(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);
+
+// Implemented in fi_kwave.hip: a K_CONV_KWAVE launch.  Returns a hipError_t as int.
+int launch_kwave(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);
 
 // Implemented in fi_stem.hip: a K_STEM launch, and the workgroups one of its problems takes.  Returns a hipError_t as int.
 int launch_stem(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);

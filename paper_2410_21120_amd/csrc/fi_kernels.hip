@@ -72,10 +72,9 @@ __global__ void __launch_bounds__(256) stage_kernel(KArgs a) {
 }
 
 // ---------------------------------------------------------------------------------
-// direct convolution / FC: one thread per output element.  Used by fp32 models and by
-// bf16 members that keep fp32 activations.
+// direct convolution / FC: one thread per output element.  fp32 models, where a tensor
+// is larger than the 32-bit offsets of the matrix kernel reach.
 // ---------------------------------------------------------------------------------
-template <typename TW, typename TA>
 __global__ void __launch_bounds__(256) conv_direct_kernel(KArgs a) {
   int p, bid;
   if (!find_problem(a, K_CONV_DIRECT, 0, p, bid)) return;
@@ -91,8 +90,8 @@ __global__ void __launch_bounds__(256) conv_direct_kernel(KArgs a) {
     const int q = (int)(m % d.Wo);
     const int pp = (int)((m / d.Wo) % d.Ho);
     const int n = (int)(m / ((int64_t)d.Wo * d.Ho));
-    const TA* x = reinterpret_cast<const TA*>(a.abase + d.x_off);
-    const TW* w = reinterpret_cast<const TW*>(a.wbase + d.w_off) + (int64_t)o * d.Kp;
+    const float* x = reinterpret_cast<const float*>(a.abase + d.x_off);
+    const float* w = reinterpret_cast<const float*>(a.wbase + d.w_off) + (int64_t)o * d.Kp;
     float acc = 0.0f;
     for (int r = 0; r < d.k; ++r) {
       const int ih = pp * d.stride - d.pad + r;
@@ -100,21 +99,19 @@ __global__ void __launch_bounds__(256) conv_direct_kernel(KArgs a) {
       for (int s = 0; s < d.kw; ++s) {
         const int iw = q * d.stride - d.pad_w + s;
         if (iw < 0 || iw >= d.W) continue;
-        const TA* xr = x + (((int64_t)n * d.H + ih) * d.W + iw) * d.Cp;
-        const TW* wr = w + (r * d.kw + s) * d.Cp;
-        for (int c = 0; c < d.C; ++c) acc += ld(xr + c) * ld(wr + c);
+        const float* xr = x + (((int64_t)n * d.H + ih) * d.W + iw) * d.Cp;
+        const float* wr = w + (r * d.kw + s) * d.Cp;
+        for (int c = 0; c < d.C; ++c) acc += xr[c] * wr[c];
       }
     }
     v = acc + reinterpret_cast<const float*>(a.wbase + d.b_off)[o];
-    if (d.r_off != kNone) v += ld(reinterpret_cast<const TA*>(a.abase + d.r_off) + m * d.Cop + o);
+    if (d.r_off != kNone) v += reinterpret_cast<const float*>(a.abase + d.r_off)[m * d.Cop + o];
     v = activate(v, d.act);
   }
   if (d.ext) {
     if (o < d.Co) static_cast<float*>(a.ext_out[p])[m * d.Co + o] = v;
-  } else if (d.out_f32) {
-    reinterpret_cast<float*>(a.abase + d.y_off)[m * d.Cop + o] = v;
   } else {
-    st(reinterpret_cast<TA*>(a.abase + d.y_off) + m * d.Cop + o, v);
+    reinterpret_cast<float*>(a.abase + d.y_off)[m * d.Cop + o] = v;
   }
 }
 
@@ -133,33 +130,6 @@ __global__ void __launch_bounds__(256) conv_direct_kernel(KArgs a) {
 // Workgroups are renumbered so that each XCD (blockIdx % 8) owns one contiguous run of
 // tiles: neighbouring tiles, which share input rows and a member's weights, meet in one L2.
 // ---------------------------------------------------------------------------------
-// Finishes four consecutive features [o, o + 4) of output row n from their complete fp32 sums: bias
-// (and residual), activation, zero in the padded features, store.  p: the problem's slot in the launch.
-template <typename TA>
-__device__ __forceinline__ void finish_row4(const KArgs& a, const Desc& d, int p, int n, int o, float4 sum) {
-  const float4 b = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(a.wbase + d.b_off) + o);
-  float v[4] = {sum.x + b.x, sum.y + b.y, sum.z + b.z, sum.w + b.w};
-  if (d.r_off != kNone) {
-    const TA* r = reinterpret_cast<const TA*>(a.abase + d.r_off) + (int64_t)n * d.Cop + o;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) v[t] += ld(r + t);
-  }
-  activate_n<4>(v, d.act);
-#pragma unroll
-  for (int t = 0; t < 4; ++t) v[t] = (o + t < d.Co) ? v[t] : 0.0f;
-  if (d.ext) {
-    float* y = static_cast<float*>(a.ext_out[p]) + (int64_t)n * d.Co + o;
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-      if (o + t < d.Co) y[t] = v[t];
-  } else if (sizeof(TA) == 4 || d.out_f32) {
-    *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.abase + d.y_off) + (int64_t)n * d.ys + o) = make_float4(v[0], v[1], v[2], v[3]);
-  } else {
-    *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(a.abase + d.y_off) + (int64_t)n * d.ys + o) =
-        make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-  }
-}
-
 // WIDE: the member keeps fp32 activations.  Each fp32 input is split on the fly into
 // hi = bf16(x) and lo = bf16(x - hi) (two bf16 terms carry 16 mantissa bits), both halves are
 // multiplied by the bf16 weights into the same fp32 accumulator, and outputs / residuals stay
@@ -1703,6 +1673,7 @@ int static_scratch(void** ptr, uint64_t* bytes) {
 int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::vector<Desc>& hd) {
   if (L.kind == K_CHAIN) return launch_chain(L, args, stream, hd);
   if (L.kind == K_STEM) return launch_stem(L, args, stream, hd);
+  if (L.kind == K_CONV_KWAVE) return launch_kwave(L, args, stream, hd);
   hipStream_t s = static_cast<hipStream_t>(stream);
   KArgs a = args;
   for (int i = 0; i < L.n; ++i) a.d[i] = hd[(size_t)(L.first_desc + i)];
@@ -1731,9 +1702,7 @@ int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::v
       if (wb) return go(stage_kernel<bf16_t, float>, nb, 256, a, s);
       return go(stage_kernel<float, float>, nb, 256, a, s);
     case K_CONV_DIRECT:
-      if (wb && ab) return go(conv_direct_kernel<bf16_t, bf16_t>, nb, 256, a, s);
-      if (wb) return go(conv_direct_kernel<bf16_t, float>, nb, 256, a, s);
-      return go(conv_direct_kernel<float, float>, nb, 256, a, s);
+      return wb ? (int)hipErrorInvalidValue : go(conv_direct_kernel, nb, 256, a, s);
     case K_CONV_MFMA:
       if (!wb) return (int)hipErrorInvalidValue;
       if (hd[(size_t)L.first_desc].Cp == 4) {  // 4-channel model input

@@ -1,0 +1,235 @@
+// Implicit-GEMM convolution / FC whose waves share the reduction instead of the tile.
+//
+// The tile kernel of fi_kernels.hip gives its four waves a quarter of the tile each and walks the reduction with two
+// workgroup barriers per 64 elements, one tile of loads in flight.  A problem of few tiles and a long reduction (one
+// workgroup per compute unit) then runs at one memory latency per step, whatever the arithmetic.  Here every wave owns
+// the WHOLE tile and every NW-th step of the reduction: it has LDS buffers of its own, so the loop has no barrier, the
+// waves' loads are in flight side by side (NW steps at a time), and the NW partial sums meet in LDS at the end, in wave
+// order, where bias, residual, activation and rounding follow.  No partial sum leaves the workgroup and no second
+// launch adds them up.
+//
+// A step is 128 bytes of a row (64 bf16 or 32 fp32 elements).  Rows come into LDS by direct global -> LDS loads (no
+// staging registers, no LDS-write instructions): eight lanes fetch one row's 128 contiguous bytes, and lane l's 16
+// bytes land at l * 16, so the 16-byte pieces of a row are permuted at the source (piece ^ row % 8), which makes the
+// operand reads (32 rows, one piece each) free of bank conflicts.  Out-of-range offsets write zeros: that is the
+// padding, the rows past M, the channels past Co and the reduction's tail.
+//
+// fp32 models multiply with v_mfma_f32_32x32x2_f32 (fp32 products, fp32 sums): a 16-byte piece is four reduction
+// elements of both operands, multiplied in four instructions.  Bound: the fp32 matrix rate (157 TFLOP/s, a sixteenth of
+// bf16), which asks so little of LDS and L1 that a wave may own a whole 64 x 64 tile.  Measured, ResNet-18 in fp32 at
+// batch 4: the 56 x 56 x 64 3x3 layers 20 us each (46 TFLOP/s), the pass 18.2 ms -> 0.40 ms against one thread per
+// output element, whose serial sums also gave way to four or eight shorter ones (closer to the exact value).
+#include <hip/hip_runtime.h>
+
+#include "fi_device.h"
+#include "fi_internal.h"
+
+namespace fi {
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// One direct load: lane l's N bytes at `off` go to at + N * l (zeros where `off` is out of range).
+template <int N>
+__device__ __forceinline__ void load_lds(const __amdgpu_buffer_rsrc_t res, uint8_t* at, uint32_t off) {
+  if constexpr (N == 16) __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void*)at, 16, off, 0, 0, 0);
+  else __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void*)at, 4, off, 0, 0, 0);
+}
+
+// F32: fp32 weights and activations.  SCALAR: a channel stride that four does not divide (an RGB input): rows are not
+// 16-byte aligned and a piece may span two filter taps, so every element is fetched by itself (4-byte loads, no swizzle).
+template <bool F32, bool SCALAR, int MI, int NI, int NW>
+__global__ void __launch_bounds__(NW * 64) conv_kwave_kernel(KArgs a) {
+  static_assert(F32 || !SCALAR, "bf16 tensors have channel strides that eight divides");
+  using TA = typename std::conditional<F32, float, bf16_t>::type;
+  constexpr int ES = (int)sizeof(TA);
+  constexpr int TK = 128 / ES;                 // reduction elements per step
+  constexpr int BM = 32 * MI, BN = 32 * NI;
+  constexpr int WAVE_LDS = (BM + BN) * 128;
+  constexpr int EPS = BN + 4;                  // fp32 row stride of a partial tile
+  constexpr int SMEM = NW * WAVE_LDS;
+  static_assert(NW * 32 * EPS * 4 <= SMEM, "the partial sums of 32 rows fit in the operand buffers");
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[SMEM];
+
+  int p, bid;
+  if (!find_problem_at(a, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), p, bid)) return;
+  const Desc d = a.d[p];
+  const int batch = a.batch[p];
+  const int M = batch * d.Ho * d.Wo;
+  const int m0 = (bid / d.tiles_n) * BM, n0 = (bid % d.tiles_n) * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+      a.abase + d.x_off, 0, (int)((int64_t)batch * d.H * d.W * d.Cp * ES), 0x00020000);
+  const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(a.wbase + d.w_off), 0, (int)((int64_t)d.Co * d.Kp * ES), 0x00020000);
+
+  // what this lane fetches of a step: rows lrow + RPI * i, element kv (the same in every row)
+  constexpr int RPI = SCALAR ? 2 : 8;          // rows per load instruction
+  constexpr int AI = BM / RPI, BI = BN / RPI;
+  const int lrow = SCALAR ? lane >> 5 : lane >> 3;
+  const int kv = SCALAR ? lane & 31 : ((lane & 7) ^ (lane >> 3)) * (16 / ES);
+  const float inv_wo = 1.0f / (float)d.Wo, inv_ho = 1.0f / (float)d.Ho, inv_cp = 1.0f / (float)d.Cp, inv_kw = 1.0f / (float)d.kw;
+  int a_row[AI], a_rc[AI];                     // byte offset of the row's window origin; filter rows / columns inside the image
+#pragma unroll
+  for (int i = 0; i < AI; ++i) {
+    const int m = m0 + lrow + RPI * i;
+    const bool ok = m < M;
+    const int mm = ok ? m : 0;   // (rows past M read as zero)
+    const int t = fast_div(mm, d.Wo, inv_wo);
+    const int q = mm - t * d.Wo;
+    const int n = fast_div(t, d.Ho, inv_ho);
+    const int pp = t - n * d.Ho;
+    const int ih0 = pp * d.stride - d.pad, iw0 = q * d.stride - d.pad_w;
+    a_row[i] = ((n * d.H + ih0) * d.W + iw0) * d.Cp * ES;
+    int rc = (int)(taps_inside(ih0, d.k, d.H) | (taps_inside(iw0, d.kw, d.W) << 16));
+    asm volatile("" : "+v"(rc));   // (computed for every row: a select, not a branch per row)
+    a_rc[i] = ok ? rc : 0;
+  }
+  const uint32_t b_row = (uint32_t)(n0 + lrow) * (uint32_t)d.Kp * ES;   // rows past Co lie past the buffer's end
+  const uint32_t b_step = (uint32_t)RPI * (uint32_t)d.Kp * ES;
+  const int K = d.k * d.kw * d.Cp;
+  const int steps = (K + TK - 1) / TK;
+
+  uint8_t* const As = smem + wave * WAVE_LDS;
+  uint8_t* const Bs = As + BM * 128;
+  auto fetch = [&](int step) {
+    const int k = step * TK + kv;
+    const int rs = fast_div(k, d.Cp, inv_cp);
+    const int kr = fast_div(rs, d.kw, inv_kw);
+    const int ks = rs - kr * d.kw;
+    const uint32_t tvar = (uint32_t)(((kr * d.W + ks) * d.Cp + (k - rs * d.Cp)) * ES);
+    const uint32_t dead = k < K ? 0u : OOB;    // past the reduction (a weight row's next elements belong to the next row)
+    const uint32_t tap_r = k < K ? (uint32_t)kr : 0u, tap_c = k < K ? 16u + (uint32_t)ks : 16u;
+#pragma unroll
+    for (int i = 0; i < AI; ++i) {
+      const bool ok = (((uint32_t)a_rc[i] >> tap_r) & ((uint32_t)a_rc[i] >> tap_c) & 1) != 0;
+      const uint32_t off = (ok ? (uint32_t)a_row[i] + tvar : OOB) | dead;
+      load_lds<SCALAR ? 4 : 16>(xres, As + i * RPI * 128, off);
+    }
+#pragma unroll
+    for (int i = 0; i < BI; ++i)
+      load_lds<SCALAR ? 4 : 16>(wres, Bs + i * RPI * 128, (b_row + b_step * i + (uint32_t)(k * ES)) | dead);
+  };
+
+  f32x16 acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+  const int r31 = lane & 31, half = lane >> 5;
+  if (wave < steps) fetch(wave);
+  for (int step = wave; step < steps; step += NW) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's step is in its LDS buffers
+    u32x4 af[4][MI], bf[4][NI];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int piece = 2 * j + half;
+      const int at = r31 * 128 + ((SCALAR ? piece : piece ^ (r31 & 7)) << 4);
+#pragma unroll
+      for (int i = 0; i < MI; ++i) af[j][i] = *reinterpret_cast<const u32x4*>(As + i * 32 * 128 + at);
+#pragma unroll
+      for (int i = 0; i < NI; ++i) bf[j][i] = *reinterpret_cast<const u32x4*>(Bs + i * 32 * 128 + at);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // every operand is in registers: the buffers may be overwritten
+    if (step + NW < steps) fetch(step + NW);            // in flight while this step is multiplied
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+          if constexpr (F32) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(bf[j][n][e]), __uint_as_float(af[j][i][e]), acc[i][n], 0, 0, 0);
+          } else {
+            acc[i][n] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bf[j][n]), __builtin_bit_cast(bf16x8, af[j][i]), acc[i][n], 0, 0, 0);
+          }
+        }
+  }
+
+  // The weights were the first operand: a lane holds, for pixel (lane & 31), four runs of four consecutive channels.
+  float* const part = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    __syncthreads();   // the operand buffers (or the previous rows' partial sums) are no longer read
+#pragma unroll
+    for (int n = 0; n < NI; ++n)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4*>(&part[(wave * 32 + r31) * EPS + n * 32 + 8 * g + 4 * half]) =
+            make_float4(acc[i][n][4 * g], acc[i][n][4 * g + 1], acc[i][n][4 * g + 2], acc[i][n][4 * g + 3]);
+    __syncthreads();
+    for (int u = tid; u < 32 * (BN / 4); u += NW * 64) {
+      const int row = u / (BN / 4), c = (u % (BN / 4)) * 4;
+      const int m = m0 + i * 32 + row, o = n0 + c;
+      if (m >= M || o >= d.Cop) continue;
+      float4 sum = *reinterpret_cast<const float4*>(&part[row * EPS + c]);
+#pragma unroll
+      for (int w = 1; w < NW; ++w) {
+        const float4 v = *reinterpret_cast<const float4*>(&part[(w * 32 + row) * EPS + c]);
+        sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+      }
+      if (!F32 || d.Cop % 4 == 0) {
+        finish_row4<TA>(a, d, p, m, o, sum);
+      } else {   // fp32 rows of any channel count: no vector of four is aligned
+        const float s[4] = {sum.x, sum.y, sum.z, sum.w};
+        for (int t = 0; t < 4 && o + t < d.Co; ++t) {
+          float v = s[t] + reinterpret_cast<const float*>(a.wbase + d.b_off)[o + t];
+          if (d.r_off != kNone) v += reinterpret_cast<const float*>(a.abase + d.r_off)[(int64_t)m * d.Cop + o + t];
+          v = activate(v, d.act);
+          if (d.ext) static_cast<float*>(a.ext_out[p])[(int64_t)m * d.Co + o + t] = v;
+          else reinterpret_cast<float*>(a.abase + d.y_off)[(int64_t)m * d.Cop + o + t] = v;
+        }
+      }
+    }
+  }
+}
+
+template <typename F>
+static int go_kwave(F kernel, int blocks, int waves, const KArgs& a, hipStream_t s) {
+  if (blocks <= 0) return (int)hipSuccess;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3((unsigned)(waves * 64)), 0, s, a);
+  return (int)hipGetLastError();
+}
+
+int launch_kwave(const Launch& L, const KArgs& args, void* stream, const std::vector<Desc>& hd) {
+  const bool f32 = L.wdtype == FI_F32;
+  if (L.n < 1 || L.n > FI_MAX_GROUP || (f32 ? L.adtype != FI_F32 : L.adtype != FI_BF16)) return (int)hipErrorInvalidValue;
+  const bool scalar = (L.tile & KW_SCALAR) != 0;
+  const int tile = L.tile & ~KW_SCALAR;
+  if (tile >= KW_NTILES || (scalar && !f32)) return (int)hipErrorInvalidValue;
+  const int side = kwave_side(tile), es = f32 ? 4 : 2;
+  KArgs a = args;
+  int64_t blocks = 0;
+  for (int i = 0; i < L.n; ++i) {
+    const Desc& t = hd[(size_t)(L.first_desc + i)];
+    a.d[i] = t;
+    const int b = a.batch[i];
+    // 32-bit byte offsets, indices decoded with exact float arithmetic, 16-byte pieces inside one filter tap, no input stage
+    if (b < 0 || t.xs != t.Cp || t.pre_kind != 0 || t.gin > 0 || t.splits != 1 || t.k < 1 || t.k > 15 || t.kw < 1 || t.kw > 15 ||
+        (!scalar && t.Cp % (16 / es)) || (!f32 && t.Cop % 8) || (f32 && t.ys != t.Cop) || t.tiles_n != (t.Co + side - 1) / side ||
+        !kwave_fits(b, t.H, t.W, t.Cp, t.Ho, t.Wo, t.Co, t.k * t.kw, t.Kp, es))
+      return (int)hipErrorInvalidValue;
+    a.first_block[i] = (int32_t)blocks;
+    blocks += ((int64_t)b * t.Ho * t.Wo + side - 1) / side * t.tiles_n;
+    if (blocks > 0x7FFFFFFF) return (int)hipErrorInvalidConfiguration;
+  }
+  for (int i = L.n; i <= FI_MAX_GROUP; ++i) a.first_block[i] = (int32_t)blocks;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const int nb = (int)blocks;
+#define FI_KWAVE_CASE(F32, SCALAR, T, MI, NW) \
+  if (f32 == (F32) && scalar == (SCALAR) && tile == (T)) return go_kwave(conv_kwave_kernel<F32, SCALAR, MI, MI, NW>, nb, NW, a, s);
+  FI_KWAVE_CASE(true, false, KW_64x4, 2, 4)
+  FI_KWAVE_CASE(true, false, KW_32x8, 1, 8)
+  FI_KWAVE_CASE(true, true, KW_64x4, 2, 4)
+  FI_KWAVE_CASE(true, true, KW_32x8, 1, 8)
+#undef FI_KWAVE_CASE
+  return (int)hipErrorInvalidValue;
+}
+
+}  // namespace fi

@@ -59,6 +59,39 @@ def test_conv_relu(case, mode):
     _run_case(m, 100 + cin + cout, b, act_dtype="f32" if mode == "bf16_wide" else None)
 
 
+KWAVE_CASES = [  # cin, cout, k, stride, pad, H, W, batch
+    (64, 64, 3, 1, 1, 56, 56, 4),      # 64x64 tiles (196 of them), the last one whole
+    (12, 70, 3, 1, 1, 61, 53, 3),      # 64x64 tiles, ragged rows and columns, Cop % 4 != 0, a step that spans three taps
+    (4, 128, 1, 1, 0, 80, 81, 2),      # 64x64 tiles, a reduction of one piece
+    (3, 64, 5, 2, 2, 161, 157, 4),     # element-wise fetch (3 channels), 64x64 tiles
+    (5, 33, 3, 1, 1, 8, 4, 1),         # element-wise fetch, 32x32 tiles: exactly one tile of rows, one column past one tile
+    (36, 31, 3, 2, 1, 9, 11, 1),       # 32x32 tiles, ragged, a tail of 4 elements in the last step, Cop % 4 != 0
+    (32, 32, 1, 1, 0, 33, 1, 1),       # one step for eight waves, one row past a tile
+    (512, 36, 3, 1, 1, 7, 7, 3),       # 144 steps over eight waves
+]
+
+
+@pytest.mark.parametrize("case", KWAVE_CASES)
+def test_conv_f32_shared_reduction(case):
+    """fp32 convolutions with the reduction shared by the waves of a workgroup, at the edges of the tiles and of the
+    reduction steps, with a residual; held to 2 sqrt(K) fp32 roundings of the oracle's (the serial sum's typical error
+    and this kernel's, which is smaller)."""
+    cin, cout, k, s, p, h, w, b = case
+    m = zoo.Model("c", "f32", cin, h, w)
+    a = m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.NONE)
+    m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.RELU, residual=a)
+    _run_case(m, 900 + cin + cout, b, tol=2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23)
+
+
+@pytest.mark.parametrize("features, batch", [(1000, 4), (1001, 33), (7, 1)])
+def test_fc_f32_shared_reduction(features, batch):
+    """fp32 fully connected layers over a flattened map (a reduction of 3 x 2 x 50 elements: not a whole step)."""
+    m = zoo.Model("c", "f32", 50, 3, 2)
+    a = m.add(zoo.CONV, -1, cin=50, cout=50, k=1, stride=1, pad=0, act=zoo.RELU)
+    m.add(zoo.FC, a, cin=50 * 6, cout=features)
+    _run_case(m, 950 + features, batch, tol=2.0 * 350 ** 0.5 * 2.0 ** -23)
+
+
 def test_long_reductions_in_small_launches_keep_their_bits():
     """ResNet-50's last stage in isolation: a 3x3 over 512 channels and a 1x1 over 2048 at 7x7, batch 32, bring 52
     workgroups each and take the 128x128 tile with three reduction tiles in flight.  At batch 96 the same layers bring
