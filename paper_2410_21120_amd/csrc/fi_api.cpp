@@ -318,7 +318,7 @@ static void store_concat_sources_in_place(fi_dag* g) {
       }
       if (first_uses != (second ? 0 : 1)) return false;
       switch (S.kind) {
-        case K_CONV_MFMA: return true;
+        case K_CONV_MFMA: case K_CONV_KWAVE: return true;
         case K_DWCONV: case K_MAXPOOL: case K_AVGPOOL: case K_GATHER: return S.Cp % 8 == 0;   // their 8-channel forms
         case K_CONCAT: return can_elide[(size_t)s] != 0;
         default: return false;
@@ -667,6 +667,25 @@ static void assign_run_positions(fi_dag* g) {
 
 }
 
+// A bf16 convolution of few tiles and a long reduction: the kernel whose waves share the reduction.  It covers a
+// compute unit's latency with eight waves' loads and adds the partial sums in LDS, where the tile kernel would leave
+// most of the chip idle or split the reduction over workgroups and add the partial sums in a second launch.  The rule
+// looks at the node's own shape only (it fixes the summation order).  Lines, measured on 2x ResNet-18 at batch 1, a
+// three-model DAG at batch 8, a four-model serving round, 3x GoogLeNet at batch 13 and 4x DenseNet-121 at batch 32:
+// 220 / 1185 / 1022 / 633 / 3694 us without this kernel, 173 / 1128 / 827 / 617 / 3437 us with it up to 128 64x64 tiles
+// from 16 reduction tiles of 64 elements on; from 8 tiles on 165 / 1128 / 829 / 660 / 3438 us.  (64x64 tiles instead of
+// 32x32 for the larger half of the range: 1129 / 862 / 616 / 3540 us.)
+static bool takes_kwave(const fi_dag* g, const Node& nd, int B) {
+  if (g->members[(size_t)nd.model].spec.act_dtype != FI_BF16 || nd.Cp == 4 || walks_groups(nd, FI_BF16)) return false;
+  const int64_t M = (int64_t)B * nd.Ho * nd.Wo;
+  if (((M + 63) / 64) * ((nd.Co + 63) / 64) > 128 || (nd.Kp + 63) / 64 < 16) return false;
+  if (nd.input >= 0 && nd.k == 1) {   // (an affine or scaling node in front is applied by the tile kernel on the way in)
+    const Node& in = g->nodes[(size_t)nd.input];
+    if (in.op == FI_MUL || (in.op == FI_DWCONV2D && in.k == 1)) return false;
+  }
+  return kwave_fits(B, nd.H, nd.W, nd.Cp, nd.Ho, nd.Wo, nd.Co, (int64_t)nd.k * nd.kw, nd.Kp, 2);
+}
+
 // Planner pass: kernel family, tile and reduction split of every node.
 static fi_status choose_kernels(fi_dag* g) {
   const fi_build_opts* opts = &g->opts;
@@ -722,6 +741,7 @@ static fi_status choose_kernels(fi_dag* g) {
             nd.tile = pick_group_tile(nd, B, std::min(grp * g->members[(size_t)nd.model].sibling_lanes, (int)FI_MAX_GROUP));
             nd.splits = 1;
           }
+          if (takes_kwave(g, nd, B)) { nd.kind = K_CONV_KWAVE; nd.tile = KW_32x8; nd.splits = 1; }
         } else {
           // fp32 models: the reduction-sharing kernel.  The tile depends on the node's own shape only (it fixes the
           // summation order): 64 x 64 where that gives most compute units a workgroup, 32 x 32 below.  (ResNet-18,

@@ -39,7 +39,7 @@ enum Kind : int32_t {
   K_STEM = 14,        // a 7x7 stride-2, 3x3 stride-1 or 3x3 stride-2 convolution over the 4-channel model input, from an input patch
                       // in LDS (tile bit 0 clear), or a stride-2 one and the 3x3 stride-2 max-pool that alone reads it (tile bit 0
                       // set: the pool node carries the launch); tile bits 1.. = which convolution
-  K_CONV_KWAVE = 15,  // implicit GEMM whose waves share the reduction of one tile (fp32 models)
+  K_CONV_KWAVE = 15,  // implicit GEMM whose waves share the reduction of one tile (fp32 models; bf16 problems of few tiles and a long reduction)
   K_NKINDS
 };
 

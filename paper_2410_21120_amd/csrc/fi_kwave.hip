@@ -228,6 +228,7 @@ int launch_kwave(const Launch& L, const KArgs& args, void* stream, const std::ve
   FI_KWAVE_CASE(true, false, KW_32x8, 1, 8)
   FI_KWAVE_CASE(true, true, KW_64x4, 2, 4)
   FI_KWAVE_CASE(true, true, KW_32x8, 1, 8)
+  FI_KWAVE_CASE(false, false, KW_32x8, 1, 8)
 #undef FI_KWAVE_CASE
   return (int)hipErrorInvalidValue;
 }

@@ -83,6 +83,31 @@ def test_conv_f32_shared_reduction(case):
     _run_case(m, 900 + cin + cout, b, tol=2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23)
 
 
+@pytest.mark.parametrize("case", [(128, 40, 3, 1, 1, 8, 4, 1),    # exactly one tile of rows, 18 steps over eight waves, a ragged column tile
+                                  (120, 31, 3, 2, 1, 13, 11, 1),  # rows padded to 32 elements: the last step is half a step; padding channels
+                                  (1024, 32, 1, 1, 0, 11, 3, 1),  # 16 steps, one row past a tile
+                                  (512, 512, 3, 1, 1, 7, 7, 3),   # many column tiles, 72 steps
+                                  (64, 128, 5, 1, 0, 36, 36, 4)]) # 64 tiles of rows: the end of the range
+def test_conv_bf16_shared_reduction(case):
+    """bf16 convolutions of few tiles and a long reduction: with a residual, and stored inside a concatenation."""
+    import paper_2410_21120_amd as fi
+    from tests import harness
+    cin, cout, k, s, p, h, w, b = case
+    m = zoo.Model("c", "bf16", cin, h, w)
+    e = m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.NONE)
+    r = m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.RELU, residual=e)
+    c = m.add(zoo.CONV, -1, cin=cin, cout=24, k=k, stride=s, pad=p, act=zoo.HARDSWISH)
+    q = m.add(zoo.CONCAT, c, residual=r)
+    m.add(zoo.CONV, q, cin=24 + cout, cout=32, k=1, stride=1, pad=0, act=zoo.NONE)
+    m.shapes()
+    g = harness.GpuDag([(m, gen.make_blob(m, 1), None)], b)
+    try:
+        assert sum(L.n_problems for L in g.dag.launches() if L.name == b"conv_kwave") == 3
+    finally:
+        g.close()
+    _run_case(m, 970 + cin + cout, b)
+
+
 @pytest.mark.parametrize("features, batch", [(1000, 4), (1001, 33), (7, 1)])
 def test_fc_f32_shared_reduction(features, batch):
     """fp32 fully connected layers over a flattened map (a reduction of 3 x 2 x 50 elements: not a whole step)."""
