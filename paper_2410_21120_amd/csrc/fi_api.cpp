@@ -672,13 +672,14 @@ static void assign_run_positions(fi_dag* g) {
 // most of the chip idle or split the reduction over workgroups and add the partial sums in a second launch.  The rule
 // looks at the node's own shape only (it fixes the summation order).  Lines, measured on 2x ResNet-18 at batch 1, a
 // three-model DAG at batch 8, a four-model serving round, 3x GoogLeNet at batch 13 and 4x DenseNet-121 at batch 32:
-// 220 / 1185 / 1022 / 633 / 3694 us without this kernel, 173 / 1128 / 827 / 617 / 3437 us with it below 128 64x64 tiles
+// 220 / 1185 / 1022 / 633 / 3694 us without this kernel, 173 / 1128 / 827 / 617 / 3437 us with it up to 128 64x64 tiles
 // from 16 reduction tiles of 64 elements on; from 8 tiles on 165 / 1128 / 829 / 660 / 3438 us.  (64x64 tiles instead of
-// 32x32 for the larger half of the range: 1129 / 862 / 616 / 3540 us.)
+// 32x32 for the larger half of the range: 1129 / 862 / 616 / 3540 us.)  Sixteen rows or less fill half a tile at most and
+// leave a workgroup per 32 output channels: the split over workgroups keeps them.
 static bool takes_kwave(const fi_dag* g, const Node& nd, int B) {
   if (g->members[(size_t)nd.model].spec.act_dtype != FI_BF16 || nd.Cp == 4 || walks_groups(nd, FI_BF16)) return false;
   const int64_t M = (int64_t)B * nd.Ho * nd.Wo;
-  if (((M + 63) / 64) * ((nd.Co + 63) / 64) >= 128 || (nd.Kp + 63) / 64 < 16) return false;
+  if (((M + 63) / 64) * ((nd.Co + 63) / 64) > 128 || M <= 16 || (nd.Kp + 63) / 64 < 16) return false;
   if (nd.input >= 0 && nd.k == 1) {   // (an affine or scaling node in front is applied by the tile kernel on the way in)
     const Node& in = g->nodes[(size_t)nd.input];
     if (in.op == FI_MUL || (in.op == FI_DWCONV2D && in.k == 1)) return false;

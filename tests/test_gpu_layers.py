@@ -87,7 +87,7 @@ def test_conv_f32_shared_reduction(case):
                                   (120, 31, 3, 2, 1, 13, 11, 1),  # rows padded to 32 elements: the last step is half a step; padding channels
                                   (1024, 32, 1, 1, 0, 11, 3, 1),  # 16 steps, one row past a tile
                                   (512, 512, 3, 1, 1, 7, 7, 3),   # many column tiles, 72 steps
-                                  (64, 128, 5, 1, 0, 35, 36, 4)]) # 62 x 2 tiles of 64 x 64: near the end of the range
+                                  (64, 128, 5, 1, 0, 36, 36, 4)]) # 64 tiles of rows: the end of the range
 def test_conv_bf16_shared_reduction(case):
     """bf16 convolutions of few tiles and a long reduction: with a residual, and stored inside a concatenation."""
     import paper_2410_21120_amd as fi
