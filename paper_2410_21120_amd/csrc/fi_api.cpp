@@ -156,6 +156,7 @@ const char* kind_name(int kind, int tile) {
     case K_STAGE: return "stage_input";
     case K_CONV_DIRECT: return "conv_direct";
     case K_CONV_KWAVE: return "conv_kwave";
+    case K_CONV_PATCH: return "conv_patch";
     case K_CONV_MFMA: return tile == T_256x128 ? "conv_mfma_256x128" : tile == T_256x64 ? "conv_mfma_256x64" : (tile == T_128x128 || tile == T_128x128_DEEP) ? "conv_mfma_128x128" : tile == T_128x64 ? "conv_mfma_128x64" : "conv_mfma_64x64";
     case K_DWCONV: return "dwconv";
     case K_MAXPOOL: return "maxpool";
@@ -512,6 +513,53 @@ static void take_stem_launches(fi_dag* g) {
     P.kind = K_STEM;
     P.tile = A.tile | 1;
     A.elided = 1;
+  }
+}
+
+// Planner pass, after the passes that fold nodes into convolutions: 3x3 stride-1 bf16 convolutions that read their taps
+// from one input patch in LDS (the same bits as on the tile they had, so the rule may look at the launch).  The lines,
+// measured without and with the kernel (us): narrow layers on the 256x64 tile 4x DenseNet-121 at batch 32 3444 / 3000,
+// 4x ResNet-18 at batch 32 857 / 830 (wider images than the 256-row patch holds gain nothing: VGG's 224 x 224 x 64 at
+// batch 64 350 / 358); groups 4x ResNeXt-101 7155 / 6756; 512x128 where the 256x128 tile is taken and 256 such workgroups
+// remain VGG-16 at batch 64 2875 / 2648, and 256x64 below that (512x128 on 104 workgroups of ResNet-50's 14 x 14 layers 57 / 61
+// per launch, 256x64 2x VGG-11 at batch 20 1015 / 982); the smaller tiles down to 128 workgroups a three-model DAG at
+// batch 8 930 / 891, 2x ResNet-50 at batch 32 1428 / 1393 (from 192 on 1397, from 256 on 1428).
+static void take_patch_launches(fi_dag* g) {
+  if (g->wdtype != FI_BF16) return;
+  const int64_t B = g->opts.max_batch;
+  std::map<std::tuple<int, int, int, int, int>, int> same;   // convolutions of one shape that share a launch
+  auto shape = [](const Node& nd) { return std::make_tuple(nd.run, nd.lane, nd.tile, nd.Ho * nd.Wo, nd.Co); };
+  if (g->opts.group_levels)
+    for (const Node& nd : g->nodes)
+      if (nd.kind == K_CONV_MFMA) ++same[shape(nd)];
+  for (Node& nd : g->nodes) {
+    const Member& mb = g->members[(size_t)nd.model];
+    const int adt = mb.spec.act_dtype;
+    if (nd.kind != K_CONV_MFMA || nd.op != FI_CONV2D || adt != FI_BF16 || nd.out_dtype != FI_BF16 || nd.is_output || nd.elided || nd.pre >= 0 ||
+        nd.chain >= 0 || nd.splits != 1)
+      continue;
+    if (nd.k != 3 || nd.kw != 3 || nd.stride != 1 || nd.pad != 1 || nd.pad_w != 1 || nd.Cp % 64 || nd.Co != nd.Cop || nd.Co % 8 || nd.Kp != 9 * nd.Cp) continue;
+    const int64_t ys = nd.root >= 0 ? g->nodes[(size_t)nd.root].Cop : nd.Cop;
+    if ((B * nd.Ho * nd.Wo + 512) * ys * 2 >= (1ll << 31) || (int64_t)nd.Co * nd.Kp * 2 >= (1ll << 31)) continue;   // 32-bit offsets
+    const auto it = same.find(shape(nd));
+    const int64_t group = it == same.end() ? 1 : std::min<int64_t>((int64_t)it->second * mb.sibling_lanes, FI_MAX_GROUP);
+    auto blocks = [&](int t) { return group * ((B * nd.Ho * nd.Wo + patch_bm(t) - 1) / patch_bm(t)) * ((nd.Co + patch_bn(t) - 1) / patch_bn(t)); };
+    const int narrow = nd.Co <= 32 ? PT_256x32 : PT_256x64;
+    int tile = -1;
+    if (nd.groups > 1) {   // a 64-column tile has to read the 64 channels of the same index
+      const int per = nd.Co / nd.groups;
+      if (!walks_groups(nd, adt) || nd.C != nd.Co || 64 % per || nd.Co % 64 || nd.tile != T_256x64) continue;
+      tile = per > 32 ? PT_256x64 : patch_fits(PT_256x64_DIAG, nd.W) ? PT_256x64_DIAG : PT_512x64_DIAG;
+    } else if (nd.tile == T_256x64) {
+      tile = narrow;
+    } else if (nd.tile == T_256x128) {
+      tile = blocks(PT_512x128) >= 256 ? PT_512x128 : PT_256x64;
+    } else if ((nd.tile == T_128x128 || nd.tile == T_128x64) && blocks(narrow) >= 128) {
+      tile = narrow;
+    }
+    if (tile < 0 || !patch_fits(tile, nd.W)) continue;
+    nd.kind = K_CONV_PATCH;
+    nd.tile = tile;
   }
 }
 
@@ -1106,9 +1154,10 @@ static void fill_descriptors(fi_dag* g) {
       d.out_f32 = (nd.out_dtype == FI_F32 && adt != FI_F32) ? 1 : 0;
       if (nd.out_dtype == FI_F32 && adt != FI_F32 && !nd.is_output) d.Cop = nd.Cop;  // fp32 rows keep the padded stride
       d.tiles_n = L.kind == K_CONV_MFMA ? (nd.Co + tile_bn(L.tile) - 1) / tile_bn(L.tile) : 0;
+      if (L.kind == K_CONV_PATCH) d.tiles_n = (nd.Co + patch_bn(L.tile) - 1) / patch_bn(L.tile);
       if (L.kind == K_CONV_KWAVE) { const int side = kwave_side(L.tile & ~KW_SCALAR); d.tiles_n = (nd.Co + side - 1) / side; }
       d.splits = std::max(1, nd.splits);
-      if (walks_groups(nd, adt)) { d.gin = nd.C / nd.groups; d.gout = nd.Co / nd.groups; }
+      if (walks_groups(nd, adt) || (nd.kind == K_CONV_PATCH && nd.groups > 1)) { d.gin = nd.C / nd.groups; d.gout = nd.Co / nd.groups; }
       {
         const Node* in = nd.input >= 0 ? &g->nodes[(size_t)nd.input] : nullptr;
         d.pw_off = d.pb_off = kNone;
@@ -1211,6 +1260,7 @@ static fi_status plan_dag(fi_dag* g) {
   fold_nodes_into_readers(g);
   form_chains(g);
   take_stem_launches(g);
+  take_patch_launches(g);
   deepen_long_reductions(g);
   build_schedule(g);
   plan_activation_arena(g);

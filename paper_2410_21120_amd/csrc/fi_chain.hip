@@ -172,26 +172,27 @@ __global__ void __launch_bounds__(256, 2) chain_mfma_kernel(KArgs a) {
     constexpr int DEPTH = W1 == 64 ? 3 : 1;
     u32x4 av[DEPTH][4], bw[DEPTH][NI1];
     const int ntiles = d1.Kp / BK;   // Cp is a multiple of 64: every reduction tile lies inside one filter tap
-    int kr = 0, ks = 0, kc = kvec;
-#define FI_FETCH_1(S, KT)                                                                                    \
+    const int taps_r = d1.k;
+    int kr = 0, ks = 0, kc = kvec;   // (conv_mfma_kernel's order: every tap of 64 channels, then the next 64 channels)
+#define FI_FETCH_1(S)                                                                                        \
     {                                                                                                        \
       const int tvar = ((kr * Wd + ks) * Cp + kc) * 2;                                                       \
       _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                        \
         const bool ok = ((a_rc[i] >> kr) & (a_rc[i] >> (16 + ks)) & 1) != 0;                                 \
         av[S][i] = __builtin_amdgcn_raw_buffer_load_b128(xres, ok ? (uint32_t)(a_row[i] + tvar) : OOB, 0, 0); \
       }                                                                                                      \
-      _Pragma("unroll") for (int i = 0; i < NI1; ++i) bw[S][i] = b1_ptr[i][(KT) * (BK / 8)];                 \
-      kc += BK;                                                                                              \
-      const bool wrap = kc >= Cp;                                                                            \
-      kc -= wrap ? Cp : 0;                                                                                   \
-      ks += wrap ? 1 : 0;                                                                                    \
-      const bool wrap2 = ks == kw;                                                                           \
-      ks = wrap2 ? 0 : ks;                                                                                   \
-      kr += wrap2 ? 1 : 0;                                                                                   \
+      _Pragma("unroll") for (int i = 0; i < NI1; ++i) bw[S][i] = b1_ptr[i][((kr * kw + ks) * Cp + kc - kvec) >> 3]; \
+      ++ks;                                                                                                  \
+      const bool wrap = ks == kw;                                                                            \
+      ks = wrap ? 0 : ks;                                                                                    \
+      kr += wrap ? 1 : 0;                                                                                    \
+      const bool wrap2 = kr == taps_r;                                                                       \
+      kr = wrap2 ? 0 : kr;                                                                                   \
+      kc += wrap2 ? BK : 0;                                                                                  \
     }
 #pragma unroll
     for (int u = 0; u < DEPTH; ++u)
-      if (u < ntiles) FI_FETCH_1(u, u)
+      if (u < ntiles) FI_FETCH_1(u)
     for (int kt = 0; kt < ntiles; kt += DEPTH) {
 #pragma unroll
       for (int u = 0; u < DEPTH; ++u) {
@@ -202,7 +203,7 @@ __global__ void __launch_bounds__(256, 2) chain_mfma_kernel(KArgs a) {
 #pragma unroll
           for (int i = 0; i < NI1; ++i) *reinterpret_cast<u32x4*>(&Bs[(srow + 32 * i) * LDS_STRIDE + kvec]) = bw[u][i];
           __syncthreads();
-          if (t + DEPTH < ntiles) FI_FETCH_1(u, t + DEPTH)
+          if (t + DEPTH < ntiles) FI_FETCH_1(u)
 #pragma unroll
           for (int kk = 0; kk < BK; kk += 16) {
             const int kof = kk + lh * 8;

@@ -40,6 +40,7 @@ enum Kind : int32_t {
                       // in LDS (tile bit 0 clear), or a stride-2 one and the 3x3 stride-2 max-pool that alone reads it (tile bit 0
                       // set: the pool node carries the launch); tile bits 1.. = which convolution
   K_CONV_KWAVE = 15,  // implicit GEMM whose waves share the reduction of one tile (fp32 models; bf16 problems of few tiles and a long reduction)
+  K_CONV_PATCH = 16,  // 3x3 stride-1 convolution whose nine taps are read from one input patch in LDS
   K_NKINDS
 };
 
@@ -59,6 +60,14 @@ FI_HD inline int tile_bn(int t) { return (t == T_128x128 || t == T_256x128 || t 
 // fp32 tensors whose channel stride four does not divide.
 enum KwaveTile : int32_t { KW_64x4 = 0, KW_32x8 = 1, KW_NTILES, KW_SCALAR = 8 };
 FI_HD inline int kwave_side(int t) { return t == KW_32x8 ? 32 : 64; }
+// Tiles of the K_CONV_PATCH kernel: rows x columns; DIAG: groups of at most 32 channels, only the 32 x 32 blocks of the
+// weights on the diagonal are multiplied.  A tile's patch holds rows + 2 W + 2 pixels of 64 channels.
+enum PatchTile : int32_t { PT_256x32 = 0, PT_256x64 = 1, PT_256x64_DIAG = 2, PT_512x128 = 3, PT_512x64_DIAG = 4, PT_NTILES };
+FI_HD constexpr int patch_bm(int t) { return t >= PT_512x128 ? 512 : 256; }
+FI_HD constexpr int patch_bn(int t) { return t == PT_256x32 ? 32 : t == PT_512x128 ? 128 : 64; }
+FI_HD constexpr int patch_pixels(int t) { return t == PT_512x128 ? 896 : t == PT_512x64_DIAG ? 1088 : 448; }   // capacity in LDS; the last eight stay free
+inline bool patch_fits(int t, int W) { return patch_bm(t) + 2 * W + 2 <= patch_pixels(t) - 8; }
+
 // What these kernels can address: input and weights through 32-bit byte offsets (a tile of rows past the last weight
 // row included), row and reduction indices below 2^24.
 inline bool kwave_fits(int64_t batch, int64_t H, int64_t W, int64_t Cp, int64_t Ho, int64_t Wo, int64_t Co, int64_t taps, int64_t Kp, int es) {
@@ -196,6 +205,9 @@ int launch_chain(const Launch& L, const KArgs& a, void* stream, const std::vecto
 
 // Implemented in fi_kwave.hip: a K_CONV_KWAVE launch.  Returns a hipError_t as int.
 int launch_kwave(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);
+
+// Implemented in fi_patch.hip: a K_CONV_PATCH launch.  Returns a hipError_t as int.
+int launch_patch(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);
 
 // Implemented in fi_stem.hip: a K_STEM launch, and the workgroups one of its problems takes.  Returns a hipError_t as int.
 int launch_stem(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);

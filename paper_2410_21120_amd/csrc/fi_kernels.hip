@@ -119,7 +119,8 @@ __global__ void __launch_bounds__(256) conv_direct_kernel(KArgs a) {
 // implicit-GEMM convolution / FC on MFMA.
 //   rows  m = (n, p, q) output pixels      M = batch*Ho*Wo
 //   cols  o = output channel               N = Co
-//   red.  kk = (r, s, c), c innermost      K = k*k*Cp, weight rows padded to Kp (x32)
+//   red.  kk = (r, s, c), c innermost      K = k*k*Cp, weight rows padded to Kp (x32); walked in 64-channel runs where
+//         64 divides Cp: (c / 64, r, s, c % 64)
 // Per 64-element reduction tile every thread fetches 16-byte vectors of A (input patches,
 // through a buffer resource whose out-of-range reads return zero: that is the padding, the
 // rows past M and the reduction tail) and of B (weights) into registers one tile ahead of
@@ -245,15 +246,20 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv_mfma_kernel(KArgs a) {
     c_hi = min(d.Cp, ((g1 + 1) * d.gin + BK - 1) / BK * BK);
   }
   const int c_len = c_hi - c_lo;
+  // Order of the reduction.  Whole reduction tiles per filter tap (Cp % 64 == 0): every tap of 64 channels, then the next 64
+  // channels (the order in which the patch kernel of fi_patch.hip has its operands in LDS, so that both give the same
+  // bits); otherwise every channel of a tap, then the next tap.
+  const bool tap_inner = !C4 && (GROUPED || d.Cp % BK == 0);
+  const int c_step = tap_inner ? 0 : BK;
   const int ntiles_all = GROUPED ? d.k * d.kw * (c_len / BK) : (d.Kp + BK - 1) / BK;
   const int per_split = (ntiles_all + d.splits - 1) / d.splits;
   const int kt0 = split * per_split;
   const int ntiles = min(ntiles_all, kt0 + per_split);  // this workgroup multiplies tiles [kt0, ntiles)
   int kr, ks, kc;
-  if constexpr (GROUPED) {
-    const int per_tap = c_len / BK;
-    const int rs = kt0 / per_tap;
-    kc = c_lo + (kt0 - rs * per_tap) * BK + kvec;
+  if (tap_inner) {
+    const int chunk = kt0 / (d.k * d.kw);
+    const int rs = kt0 - chunk * (d.k * d.kw);
+    kc = c_lo + chunk * BK + kvec;
     kr = rs / d.kw;
     ks = rs - kr * d.kw;
   } else {
@@ -330,17 +336,20 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv_mfma_kernel(KArgs a) {
     }                                                                                             \
     const bool bok = !(b_tail && (KT) == ntiles_all - 1 && kvec >= 32);                           \
     /* position of this tile in a weight row, in 8-element vectors past the thread's own kvec */  \
-    const int wt = GROUPED ? ((kr * d.kw + ks) * d.Cp + kc - kvec) >> 3 : (KT) * (BK / 8);        \
+    const int wt = tap_inner ? ((kr * d.kw + ks) * d.Cp + kc - kvec) >> 3 : (KT) * (BK / 8);        \
     _Pragma("unroll") for (int i = 0; i < BR; ++i)                                                \
         bv[S][i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wres, (bok ? (uint32_t)(b_row[i] + wt * 16) : OOB) | dead, 0, 0)); \
-    kc += BK;                                                                                     \
+    kc += c_step;                                                                                 \
     if (GROUPED || one_wrap) { /* at least 64 channels per tap: the walk leaves a tap at most once per tile */ \
-      const bool wrap = kc >= c_hi;                                                               \
-      kc -= wrap ? c_len : 0;                                                                     \
-      ks += wrap ? 1 : 0;                                                                         \
+      const bool over = kc >= c_hi;                                                               \
+      kc -= over ? c_len : 0;                                                                     \
+      ks += (over || tap_inner) ? 1 : 0;                                                          \
       const bool wrap2 = ks == d.kw;                                                              \
       ks = wrap2 ? 0 : ks;                                                                        \
       kr += wrap2 ? 1 : 0;                                                                        \
+      const bool wrap3 = tap_inner && kr == d.k;                                                  \
+      kr = wrap3 ? 0 : kr;                                                                        \
+      kc += wrap3 ? BK : 0;                                                                       \
     } else {                                                                                      \
       _Pragma("unroll") for (int t = 0; t < 8; ++t) {                                             \
         const bool wrap = kc >= c_hi;                                                             \
@@ -1673,6 +1682,7 @@ int static_scratch(void** ptr, uint64_t* bytes) {
 int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::vector<Desc>& hd) {
   if (L.kind == K_CHAIN) return launch_chain(L, args, stream, hd);
   if (L.kind == K_STEM) return launch_stem(L, args, stream, hd);
+  if (L.kind == K_CONV_PATCH) return launch_patch(L, args, stream, hd);
   if (L.kind == K_CONV_KWAVE) return launch_kwave(L, args, stream, hd);
   hipStream_t s = static_cast<hipStream_t>(stream);
   KArgs a = args;

@@ -108,6 +108,33 @@ def test_conv_bf16_shared_reduction(case):
     _run_case(m, 970 + cin + cout, b)
 
 
+@pytest.mark.parametrize("case", [(128, 32, 1, 90, 91, 8, 0),     # the widest image of the 256-row patches, a ragged last tile, two runs of 64 channels
+                                  (64, 64, 1, 56, 56, 21, 1),     # one run of 64 channels
+                                  (64, 520, 1, 57, 45, 11, 4),    # 512 x 128 tiles, a ragged column tile
+                                  (256, 256, 32, 41, 67, 6, 2),   # groups of 8: diagonal blocks
+                                  (256, 256, 32, 27, 220, 3, 5),  # the same, 512 rows
+                                  (256, 256, 4, 1, 91, 181, 1)])  # groups of 64, images of one row
+def test_conv_patch(case):
+    """3x3 stride-1 convolutions from an input patch in LDS: with a residual, and stored inside a concatenation."""
+    from tests import harness
+    cin, cout, groups, h, w, b, tile = case
+    m = zoo.Model("c", "bf16", cin, h, w)
+    conv = dict(cin=cin, cout=cout, k=3, stride=1, pad=1, groups=groups)
+    e = m.add(zoo.CONV, -1, act=zoo.NONE, **conv)
+    s = m.add(zoo.CONV, -1, cin=cin, cout=8, k=1, stride=1, pad=0, act=zoo.NONE)
+    r = m.add(zoo.CONV, -1, act=zoo.RELU6 if tile else zoo.HARDSWISH, residual=e, **conv)
+    q = m.add(zoo.CONCAT, s, residual=r)
+    m.add(zoo.CONV, q, cin=8 + cout, cout=8, k=1, stride=1, pad=0, act=zoo.NONE)
+    m.shapes()
+    g = harness.GpuDag([(m, gen.make_blob(m, 1), None)], b)
+    try:
+        launches = [L for L in g.dag.launches() if L.name == b"conv_patch"]
+        assert sum(L.n_problems for L in launches) == 2, [L.name for L in g.dag.launches()]
+    finally:
+        g.close()
+    _run_case(m, 990 + cin + cout + groups, b)
+
+
 @pytest.mark.parametrize("features, batch", [(1000, 4), (1001, 33), (7, 1)])
 def test_fc_f32_shared_reduction(features, batch):
     """fp32 fully connected layers over a flattened map (a reduction of 3 x 2 x 50 elements: not a whole step)."""
