@@ -249,7 +249,8 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv_mfma_kernel(KArgs a) {
   // Order of the reduction.  Whole reduction tiles per filter tap (Cp % 64 == 0): every tap of 64 channels, then the next 64
   // channels (the order in which the patch kernel of fi_patch.hip has its operands in LDS, so that both give the same
   // bits); otherwise every channel of a tap, then the next tap.
-  const bool tap_inner = !C4 && (GROUPED || d.Cp % BK == 0);
+  // (The patch kernel has no fp32-stored form, and a pointwise convolution has one tap: those keep the plain walk.)
+  const bool tap_inner = !C4 && !WIDE && PRE == 0 && (GROUPED || d.Cp % BK == 0);
   const int c_step = tap_inner ? 0 : BK;
   const int ntiles_all = GROUPED ? d.k * d.kw * (c_len / BK) : (d.Kp + BK - 1) / BK;
   const int per_split = (ntiles_all + d.splits - 1) / d.splits;
