@@ -222,7 +222,7 @@ def main():
         flops = 2.0 * L.macs_per_image * B
         nbytes = float(L.bytes_per_image) * B + L.weight_bytes
         t_m, t_h = flops / (PEAK_MFMA_BF16 * 1e12) * 1e3, nbytes / (PEAK_HBM * 1e9) * 1e3   # ms at either roof
-        row = dict(launch=i, level=L.level, lane=L.lane, kernel=L.name.decode(), problems=L.n_problems,
+        row = dict(launch=i, level=L.level, lane=L.lane, kernel=L.kernel, problems=L.n_problems,
                    gflop=round(flops / 1e9, 2), mbytes=round(nbytes / 1e6, 2), flop_per_byte=round(flops / max(nbytes, 1.0), 1),
                    bound="mfma" if t_m >= t_h else "hbm", roof_ms=round(max(t_m, t_h), 5),
                    alone_ms=round(float(alone[i]), 5), span_ms=round(per_launch_span[i], 5),

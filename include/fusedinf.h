@@ -225,7 +225,7 @@ typedef struct {
 
 typedef struct {
   int32_t level, kind, n_problems, first_node; /* kind: internal kernel family id */
-  int32_t lane, reserved;    /* launch lane (stream) */
+  int32_t lane, tile;        /* launch lane (stream); tile: which of the family's kernels runs, 0 where it has one (internal id, as kind) */
   uint64_t macs_per_image;   /* dense work of the launch */
   uint64_t bytes_per_image;  /* compulsory activation bytes (in + out + residual), per image */
   uint64_t weight_bytes;     /* weight + bias bytes read once per launch */

@@ -96,8 +96,20 @@ class fi_node_info(C.Structure):
 
 class fi_launch_info(C.Structure):
     _fields_ = [("level", C.c_int32), ("kind", C.c_int32), ("n_problems", C.c_int32), ("first_node", C.c_int32),
-                ("lane", C.c_int32), ("reserved", C.c_int32), ("macs_per_image", C.c_uint64), ("bytes_per_image", C.c_uint64), ("weight_bytes", C.c_uint64),
+                ("lane", C.c_int32), ("tile", C.c_int32), ("macs_per_image", C.c_uint64), ("bytes_per_image", C.c_uint64), ("weight_bytes", C.c_uint64),
                 ("name", C.c_char * 32)]
+
+    # Tiles of the families whose name does not say which one runs, by internal id: rows x columns of a workgroup; "diag": only
+    # the 32 x 32 blocks on the diagonal of grouped weights; x waves that share the reduction; "scalar": element-wise fetch.
+    TILES = {b"conv_mfma_128x128": {5: "deep"},   # three reduction tiles in flight
+             b"conv_patch": {0: "256x32", 1: "256x64", 2: "256x64 diag", 3: "512x128", 4: "512x64 diag"},
+             b"conv_kwave": {0: "64x64x4", 1: "32x32x8", 8: "64x64x4 scalar", 9: "32x32x8 scalar"}}
+
+    @property
+    def kernel(self):
+        """The family's name and, where the family has several kernels that the name leaves open, the tile."""
+        tile = self.TILES.get(self.name, {}).get(self.tile)
+        return self.name.decode() + (" " + tile if tile else "")
 
 
 LIB_PATH = _build.OUT

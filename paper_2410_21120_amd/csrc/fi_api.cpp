@@ -1317,7 +1317,7 @@ fi_status fi_launch(const fi_dag* g, int32_t i, fi_launch_info* o) {
   if (!g || !o || i < 0 || i >= (int32_t)g->launches.size()) { set_error("bad launch index"); return FI_EINVAL; }
   const Launch& L = g->launches[(size_t)i];
   std::memset(o, 0, sizeof(*o));
-  o->lane = L.lane;
+  o->lane = L.lane; o->tile = L.tile;
   o->level = L.level; o->kind = L.kind; o->n_problems = L.n;
   o->first_node = (L.nodes.empty() || L.kind == K_STAGE) ? -1 : L.nodes[0];
   o->macs_per_image = L.macs; o->bytes_per_image = L.act_bytes; o->weight_bytes = L.weight_bytes;

@@ -14,13 +14,17 @@ F32_TOL = 1e-4
 
 
 
-def _run_case(model, seed, batch, act_dtype=None, tol=None, bias_std=0.1):
+def _run_case(model, seed, batch, act_dtype=None, tol=None, bias_std=0.1, kernels=()):
+    """kernels: (launch name with tile, problems) pairs the schedule has to hold."""
     from tests import harness
     model.shapes()
     blob = gen.make_blob(model, seed, bias_std=bias_std)
     x = gen.make_input(seed + 1, batch, model.in_c, model.in_h, model.in_w, "normal", model.dtype)
     g = harness.GpuDag([(model, blob, act_dtype)], batch)
     try:
+        have = [(L.kernel, L.n_problems) for L in g.dag.launches()]
+        for name, n in kernels:
+            assert sum(k for h, k in have if h == name) == n, (name, n, have)
         y = g.run(x)[0]
     finally:
         g.close()
@@ -59,15 +63,15 @@ def test_conv_relu(case, mode):
     _run_case(m, 100 + cin + cout, b, act_dtype="f32" if mode == "bf16_wide" else None)
 
 
-KWAVE_CASES = [  # cin, cout, k, stride, pad, H, W, batch
-    (64, 64, 3, 1, 1, 56, 56, 4),      # 64x64 tiles (196 of them), the last one whole
-    (12, 70, 3, 1, 1, 61, 53, 3),      # 64x64 tiles, ragged rows and columns, Cop % 4 != 0, a step that spans three taps
-    (4, 128, 1, 1, 0, 80, 81, 2),      # 64x64 tiles, a reduction of one piece
-    (3, 64, 5, 2, 2, 161, 157, 4),     # element-wise fetch (3 channels), 64x64 tiles
-    (5, 33, 3, 1, 1, 8, 4, 1),         # element-wise fetch, 32x32 tiles: exactly one tile of rows, one column past one tile
-    (36, 31, 3, 2, 1, 9, 11, 1),       # 32x32 tiles, ragged, a tail of 4 elements in the last step, Cop % 4 != 0
-    (32, 32, 1, 1, 0, 33, 1, 1),       # one step for eight waves, one row past a tile
-    (512, 36, 3, 1, 1, 7, 7, 3),       # 144 steps over eight waves
+KWAVE_CASES = [  # cin, cout, k, stride, pad, H, W, batch, tile
+    (64, 64, 3, 1, 1, 56, 56, 4, "64x64x4"),          # 196 tiles of 64x64, the last one whole
+    (12, 70, 3, 1, 1, 61, 53, 3, "64x64x4"),          # ragged rows and columns, Cop % 4 != 0, a step that spans three taps
+    (4, 128, 1, 1, 0, 80, 81, 2, "64x64x4"),          # a reduction of one piece
+    (3, 64, 5, 2, 2, 161, 157, 4, "64x64x4 scalar"),  # element-wise fetch (3 channels)
+    (5, 33, 3, 1, 1, 8, 4, 1, "32x32x8 scalar"),      # element-wise fetch: exactly one tile of rows, one column past one tile
+    (36, 31, 3, 2, 1, 9, 11, 1, "32x32x8"),           # ragged, a tail of 4 elements in the last step, Cop % 4 != 0
+    (32, 32, 1, 1, 0, 33, 1, 1, "32x32x8"),           # one step for eight waves, one row past a tile
+    (512, 36, 3, 1, 1, 7, 7, 3, "32x32x8"),           # 144 steps over eight waves
 ]
 
 
@@ -76,11 +80,18 @@ def test_conv_f32_shared_reduction(case):
     """fp32 convolutions with the reduction shared by the waves of a workgroup, at the edges of the tiles and of the
     reduction steps, with a residual; held to 2 sqrt(K) fp32 roundings of the oracle's (the serial sum's typical error
     and this kernel's, which is smaller)."""
-    cin, cout, k, s, p, h, w, b = case
+    cin, cout, k, s, p, h, w, b, tile = case
     m = zoo.Model("c", "f32", cin, h, w)
     a = m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.NONE)
     m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.RELU, residual=a)
-    _run_case(m, 900 + cin + cout, b, tol=2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23)
+    _run_case(m, 900 + cin + cout, b, tol=2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23, kernels=[("conv_kwave " + tile, 2)])
+
+
+def test_conv_f32_beyond_the_shared_reduction():
+    """2^24 output rows, one more than the shared-reduction kernel decodes: the element-wise kernel, held like the above."""
+    m = zoo.Model("c", "f32", 1, 4096, 4096)
+    m.add(zoo.CONV, -1, cin=1, cout=1, k=3, stride=1, pad=1, act=zoo.RELU)
+    _run_case(m, 911, 1, tol=2.0 * 9 ** 0.5 * 2.0 ** -23, kernels=[("conv_direct", 1)])
 
 
 @pytest.mark.parametrize("case", [(128, 40, 3, 1, 1, 8, 4, 1),    # exactly one tile of rows, 18 steps over eight waves, a ragged column tile
@@ -90,8 +101,6 @@ def test_conv_f32_shared_reduction(case):
                                   (64, 128, 5, 1, 0, 36, 36, 4)]) # 64 tiles of rows: the end of the range
 def test_conv_bf16_shared_reduction(case):
     """bf16 convolutions of few tiles and a long reduction: with a residual, and stored inside a concatenation."""
-    import paper_2410_21120_amd as fi
-    from tests import harness
     cin, cout, k, s, p, h, w, b = case
     m = zoo.Model("c", "bf16", cin, h, w)
     e = m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.NONE)
@@ -99,40 +108,67 @@ def test_conv_bf16_shared_reduction(case):
     c = m.add(zoo.CONV, -1, cin=cin, cout=24, k=k, stride=s, pad=p, act=zoo.HARDSWISH)
     q = m.add(zoo.CONCAT, c, residual=r)
     m.add(zoo.CONV, q, cin=24 + cout, cout=32, k=1, stride=1, pad=0, act=zoo.NONE)
-    m.shapes()
-    g = harness.GpuDag([(m, gen.make_blob(m, 1), None)], b)
-    try:
-        assert sum(L.n_problems for L in g.dag.launches() if L.name == b"conv_kwave") == 3
-    finally:
-        g.close()
-    _run_case(m, 970 + cin + cout, b)
+    _run_case(m, 970 + cin + cout, b, kernels=[("conv_kwave 32x32x8", 3)])
 
 
-@pytest.mark.parametrize("case", [(128, 32, 1, 90, 91, 8, 0),     # the widest image of the 256-row patches, a ragged last tile, two runs of 64 channels
-                                  (64, 64, 1, 56, 56, 21, 1),     # one run of 64 channels
-                                  (64, 520, 1, 57, 45, 11, 4),    # 512 x 128 tiles, a ragged column tile
-                                  (256, 256, 32, 41, 67, 6, 2),   # groups of 8: diagonal blocks
-                                  (256, 256, 32, 27, 220, 3, 5),  # the same, 512 rows
-                                  (256, 256, 4, 1, 91, 181, 1)])  # groups of 64, images of one row
+PATCH_CASES = [  # cin, cout, groups, H, W, batch, tile
+    (128, 32, 1, 90, 91, 8, "256x32"),           # the widest image of the 256-row patches, a ragged last tile, two runs of 64 channels
+    (64, 64, 1, 56, 56, 21, "256x64"),           # one run of 64 channels
+    (192, 72, 1, 41, 37, 22, "256x64"),          # three runs, a ragged column tile
+    (64, 520, 1, 57, 45, 11, "512x128"),         # a ragged column tile
+    (128, 136, 1, 57, 45, 26, "512x128"),        # two runs of 64 channels, ragged rows and columns
+    (64, 264, 1, 19, 140, 17, "512x128"),        # an image wider than the 256-row patches hold
+    (256, 256, 32, 41, 67, 6, "256x64 diag"),    # groups of 8: diagonal blocks
+    (256, 256, 32, 27, 220, 3, "512x64 diag"),   # the same, 512 rows
+    (256, 256, 4, 1, 91, 181, "256x64"),         # groups of 64, images of one row
+]
+
+
+@pytest.mark.parametrize("case", PATCH_CASES)
 def test_conv_patch(case):
     """3x3 stride-1 convolutions from an input patch in LDS: with a residual, and stored inside a concatenation."""
-    from tests import harness
     cin, cout, groups, h, w, b, tile = case
     m = zoo.Model("c", "bf16", cin, h, w)
     conv = dict(cin=cin, cout=cout, k=3, stride=1, pad=1, groups=groups)
     e = m.add(zoo.CONV, -1, act=zoo.NONE, **conv)
     s = m.add(zoo.CONV, -1, cin=cin, cout=8, k=1, stride=1, pad=0, act=zoo.NONE)
-    r = m.add(zoo.CONV, -1, act=zoo.RELU6 if tile else zoo.HARDSWISH, residual=e, **conv)
+    r = m.add(zoo.CONV, -1, act=zoo.HARDSWISH if tile == "256x32" else zoo.RELU6, residual=e, **conv)
     q = m.add(zoo.CONCAT, s, residual=r)
     m.add(zoo.CONV, q, cin=8 + cout, cout=8, k=1, stride=1, pad=0, act=zoo.NONE)
+    _run_case(m, 990 + cin + cout + groups, b, kernels=[("conv_patch " + tile, 2)])
+
+
+def _same_bits(m, few, many, kernel_few, kernel_many, x=None, blob=None):
+    """The first images of a batch, run in a handle for `few` and in one for `many` images, asserting each one's kernel."""
+    from tests import harness
     m.shapes()
-    g = harness.GpuDag([(m, gen.make_blob(m, 1), None)], b)
-    try:
-        launches = [L for L in g.dag.launches() if L.name == b"conv_patch"]
-        assert sum(L.n_problems for L in launches) == 2, [L.name for L in g.dag.launches()]
-    finally:
-        g.close()
-    _run_case(m, 990 + cin + cout + groups, b)
+    blob = gen.make_blob(m, 61) if blob is None else blob
+    x = gen.make_input(62, many, m.in_c, m.in_h, m.in_w, "normal", m.dtype) if x is None else x
+    ys = []
+    for b, kernel in ((few, kernel_few), (many, kernel_many)):
+        g = harness.GpuDag([(m, blob, None)], b)
+        try:
+            assert kernel in [L.kernel for L in g.dag.launches()], (kernel, [L.kernel for L in g.dag.launches()])
+            ys.append(g.run(x[:b])[0][:few])
+        finally:
+            g.close()
+    assert np.array_equal(ys[0], ys[1], equal_nan=True)
+    return x, blob, ys[0]
+
+
+@pytest.mark.parametrize("case", [(64, 32, 1, 23, 29, 5, 70, "conv_mfma_64x64", "256x32"),
+                                  (128, 136, 1, 57, 45, 3, 26, "conv_mfma_64x64", "512x128"),
+                                  (192, 72, 1, 41, 37, 7, 22, "conv_mfma_64x64", "256x64"),
+                                  (256, 256, 32, 21, 35, 2, 24, "conv_mfma_64x64", "256x64 diag"),
+                                  (256, 256, 32, 7, 220, 1, 12, "conv_mfma_64x64", "512x64 diag"),
+                                  (256, 256, 4, 21, 35, 2, 24, "conv_mfma_64x64", "256x64")])
+def test_conv_patch_has_the_bits_of_the_tile_kernel(case):
+    """The planner takes the patch kernel by the size of a launch: an image's bits must not depend on it."""
+    cin, cout, groups, h, w, few, many, small, tile = case
+    m = zoo.Model("c", "bf16", cin, h, w)
+    a = m.add(zoo.CONV, -1, cin=cin, cout=cout, k=3, stride=1, pad=1, groups=groups, act=zoo.NONE)
+    m.add(zoo.MAXPOOL, a, k=1, stride=1, pad=0)
+    assert np.isfinite(_same_bits(m, few, many, small, "conv_patch " + tile)[2]).all()
 
 
 @pytest.mark.parametrize("features, batch", [(1000, 4), (1001, 33), (7, 1)])
@@ -145,10 +181,10 @@ def test_fc_f32_shared_reduction(features, batch):
 
 
 def test_long_reductions_in_small_launches_keep_their_bits():
-    """ResNet-50's last stage in isolation: a 3x3 over 512 channels and a 1x1 over 2048 at 7x7, batch 32, bring 52
-    workgroups each and take the 128x128 tile with three reduction tiles in flight.  At batch 96 the same layers bring
-    148 workgroups and take the plain tile: the first 32 images must come out with the same bits (the reduction order
-    does not depend on the prefetch depth), and meet the oracle."""
+    """ResNet-50's last stage in isolation, a 3x3 over 512 channels and a 1x1 over 2048 at 7x7: one member at batch 32 has
+    64x64 tiles; at batch 96 the 3x3 reads from a patch; eight members at batch 32 take the patch and, for the 1x1, the 128x128 tile
+    with three reduction tiles in flight (52 workgroups each).  A member's images must come out with the same bits (the
+    reduction order depends on none of these), and meet the oracle."""
     from tests import harness
     m = zoo.Model("stage4", "bf16", 512, 7, 7)
     a = m.add(zoo.CONV, -1, cin=512, cout=512, k=3, stride=1, pad=1, act=zoo.RELU)
@@ -159,15 +195,21 @@ def test_long_reductions_in_small_launches_keep_their_bits():
     blob = gen.make_blob(m, 777)
     x = gen.make_input(778, 96, 512, 7, 7, "normal", "bf16")
     outs = {}
-    for batch in (32, 96, 31):   # (31: a ragged last tile under the deep prefetch)
-        g = harness.GpuDag([(m, blob, None)], batch)
+    for members, batch, kernels in ((1, 32, ["conv_mfma_64x64"] * 3), (1, 96, ["conv_patch 256x64"]), (1, 31, ["conv_mfma_64x64"] * 3),
+                                    (8, 32, ["conv_patch 256x64", "conv_mfma_128x128 deep"]),
+                                    (8, 31, ["conv_patch 256x64", "conv_mfma_128x128 deep"])):   # (31: ragged last tiles)
+        g = harness.GpuDag([(m, blob, None)] * members, batch)
         try:
-            outs[batch] = g.run(x[:batch])[0]
+            have = [L.kernel for L in g.dag.launches()]
+            assert all(have.count(k) >= kernels.count(k) for k in kernels), have
+            outs[members, batch] = g.run(x[:batch])
         finally:
             g.close()
-    assert np.isfinite(outs[32]).all()
-    assert np.array_equal(outs[32], outs[96][:32]) and np.array_equal(outs[31], outs[96][:31])
-    harness.check_against_oracle("last-stage layers, deep prefetch", m, blob, None, x[:32], outs[32], rows=[0, 7, 31])
+    first = outs[1, 96][0]
+    assert np.isfinite(first).all()
+    for (members, batch), ys in outs.items():
+        assert all(np.array_equal(y, first[:batch]) for y in ys), (members, batch)
+    harness.check_against_oracle("last-stage layers, deep prefetch", m, blob, None, x[:32], outs[8, 32][0], rows=[0, 7, 31])
 
 
 @pytest.mark.parametrize("case", [(128, 128, 3, 1, 1, 127, 129, 4),   # 256x128 tile: long reduction, ragged last tile
