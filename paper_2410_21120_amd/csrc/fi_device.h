@@ -150,6 +150,27 @@ __device__ __forceinline__ void runs_to_fragments(const uint32_t (&pk)[4][2], ui
     }
 }
 
+// One element of an fp32 convolution, output pixel m and channel o: the taps inside the image, one after the other.
+__device__ __forceinline__ float conv_element(const KArgs& a, const Desc& d, int64_t m, int o) {
+  const int q = (int)(m % d.Wo);
+  const int pp = (int)((m / d.Wo) % d.Ho);
+  const int n = (int)(m / ((int64_t)d.Wo * d.Ho));
+  const float* x = reinterpret_cast<const float*>(a.abase + d.x_off);
+  const float* w = reinterpret_cast<const float*>(a.wbase + d.w_off) + (int64_t)o * d.Kp;
+  float acc = 0.0f;
+  for (int r = 0; r < d.k; ++r) {
+    const int ih = pp * d.stride - d.pad + r;
+    if (ih < 0 || ih >= d.H) continue;
+    for (int s = 0; s < d.kw; ++s) {
+      const int iw = q * d.stride - d.pad_w + s;
+      if (iw < 0 || iw >= d.W) continue;
+      const float* xr = x + (((int64_t)n * d.H + ih) * d.W + iw) * d.Cp;
+      const float* wr = w + (r * d.kw + s) * d.Cp;
+      for (int c = 0; c < d.C; ++c) acc += xr[c] * wr[c];
+    }
+  }
+  return acc;
+}
 
 // Finishes four consecutive features [o, o + 4) of output row n from their complete fp32 sums: bias
 // (and residual), activation, zero in the padded features, store.  p: the problem's slot in the launch.

@@ -87,24 +87,7 @@ __global__ void __launch_bounds__(256) conv_direct_kernel(KArgs a) {
   const int64_t m = idx / d.Cop;
   float v = 0.0f;
   if (o < d.Co) {
-    const int q = (int)(m % d.Wo);
-    const int pp = (int)((m / d.Wo) % d.Ho);
-    const int n = (int)(m / ((int64_t)d.Wo * d.Ho));
-    const float* x = reinterpret_cast<const float*>(a.abase + d.x_off);
-    const float* w = reinterpret_cast<const float*>(a.wbase + d.w_off) + (int64_t)o * d.Kp;
-    float acc = 0.0f;
-    for (int r = 0; r < d.k; ++r) {
-      const int ih = pp * d.stride - d.pad + r;
-      if (ih < 0 || ih >= d.H) continue;
-      for (int s = 0; s < d.kw; ++s) {
-        const int iw = q * d.stride - d.pad_w + s;
-        if (iw < 0 || iw >= d.W) continue;
-        const float* xr = x + (((int64_t)n * d.H + ih) * d.W + iw) * d.Cp;
-        const float* wr = w + (r * d.kw + s) * d.Cp;
-        for (int c = 0; c < d.C; ++c) acc += xr[c] * wr[c];
-      }
-    }
-    v = acc + reinterpret_cast<const float*>(a.wbase + d.b_off)[o];
+    v = conv_element(a, d, m, o) + reinterpret_cast<const float*>(a.wbase + d.b_off)[o];
     if (d.r_off != kNone) v += reinterpret_cast<const float*>(a.abase + d.r_off)[m * d.Cop + o];
     v = activate(v, d.act);
   }

@@ -87,6 +87,37 @@ def test_conv_f32_shared_reduction(case):
     _run_case(m, 900 + cin + cout, b, tol=2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23, kernels=[("conv_kwave " + tile, 2)])
 
 
+@pytest.mark.parametrize("case", [(64, 40, 3, 1, 1, 61, 57, 4, "64x64x4"), (3, 64, 7, 2, 3, 161, 157, 4, "64x64x4 scalar"),
+                                  (5, 33, 3, 1, 1, 9, 11, 1, "32x32x8 scalar"), (36, 31, 5, 2, 2, 9, 11, 1, "32x32x8")])
+def test_conv_f32_weights_that_are_not_finite(case):
+    """Infinite and NaN weights reach the outputs whose window holds their tap, and no output at the border where the tap
+    lies outside the image; every other value meets the bound of the finite case."""
+    from tests import harness
+    cin, cout, k, s, p, h, w, b, tile = case
+    m = zoo.Model("c", "f32", cin, h, w)
+    m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.NONE)
+    m.shapes()
+    blob = gen.make_blob(m, 71)
+    wt = blob[m.layers[0].w_off:m.layers[0].w_off + 4 * cout * cin * k * k].view(np.float32).reshape(cout, cin, k, k)
+    for o, value in ((1, np.inf), (2, -np.inf), (cout - 1, np.nan)):
+        wt[o, cin - 1, 0, 0] = value      # outside the image in the first row and the first column
+    wt[3, 0, k - 1, k - 1] = np.inf       # ... in the last ones
+    x = gen.make_input(72, b, cin, h, w, "normal", "f32")
+    g = harness.GpuDag([(m, blob, None)], b)
+    try:
+        assert "conv_kwave " + tile in [L.kernel for L in g.dag.launches()]
+        y = g.run(x)[0]
+    finally:
+        g.close()
+    ref = harness.oracle_nhwc(m, blob, x, False)
+    assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(np.isinf(y), np.isinf(ref))
+    assert np.array_equal(y[np.isinf(y)], ref[np.isinf(ref)])
+    border = ref.reshape(b, m.layers[0].out_h, m.layers[0].out_w, cout)[:, 0, :, 1]
+    assert np.isfinite(border).all()
+    finite = np.isfinite(ref)
+    assert harness.rel_l2(y[finite], ref[finite]) <= 2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23
+
+
 def test_conv_f32_beyond_the_shared_reduction():
     """2^24 output rows, one more than the shared-reduction kernel decodes: the element-wise kernel, held like the above."""
     m = zoo.Model("c", "f32", 1, 4096, 4096)
