@@ -228,6 +228,10 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv_mfma_kernel(KArgs a) {
     c_lo = (g0 * d.gin) / BK * BK;
     c_hi = min(d.Cp, ((g1 + 1) * d.gin + BK - 1) / BK * BK);
   }
+  // Groups of at most 32 channels, as many outputs as inputs each: of a 64 x 64 block of weights only the two 32 x 32 blocks on the
+  // diagonal are other than zero, and only these are multiplied.  (As in the patch kernel, which a larger launch takes: an
+  // activation that is not finite reaches the same outputs either way.)
+  const bool diagonal = GROUPED && d.gin == d.gout && 32 % max(d.gin, 1) == 0;
   const int c_len = c_hi - c_lo;
   // Order of the reduction.  Whole reduction tiles per filter tap (Cp % 64 == 0): every tap of 64 channels, then the next 64
   // channels (the order in which the patch kernel of fi_patch.hip has its operands in LDS, so that both give the same
@@ -418,8 +422,10 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv_mfma_kernel(KArgs a) {
           bfr[j] = *reinterpret_cast<const bf16x8*>(&Bp[(wn * WTN + j * 32 + (lane & 31)) * LDS_STRIDE + kof]); \
       _Pragma("unroll") for (int h = AT - 1; h >= 0; --h) /* small (lo) terms first */            \
       _Pragma("unroll") for (int i = 0; i < MI; ++i)                                              \
-      _Pragma("unroll") for (int j = 0; j < NI; ++j)                                              \
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[h][i], acc[i][j], 0, 0, 0); \
+      _Pragma("unroll") for (int j = 0; j < NI; ++j) {                                            \
+        if (GROUPED && diagonal && (wn * (WTN / 32) + j) % 2 != kk / 32) continue;                \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[h][i], acc[i][j], 0, 0, 0); \
+      }                                                                                           \
     }                                                                                             \
   }
 

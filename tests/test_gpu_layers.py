@@ -211,6 +211,22 @@ def test_fc_f32_shared_reduction(features, batch):
     _run_case(m, 950 + features, batch, tol=2.0 * 350 ** 0.5 * 2.0 ** -23)
 
 
+@pytest.mark.parametrize("case", [(32, 21, 35, 2, 24, "conv_mfma_64x64", "conv_patch 256x64 diag"), (32, 7, 220, 1, 12, "conv_mfma_64x64", "conv_patch 512x64 diag"),
+                                  (8, 21, 35, 12, 24, "conv_mfma_128x64", "conv_patch 256x64 diag"), (16, 29, 110, 10, 20, "conv_mfma_128x64", "conv_mfma_256x64")])
+def test_grouped_conv_activations_that_are_not_finite(case):
+    """Groups of at most 32 channels: an infinite or NaN activation reaches the 32 output channels of its block and no others,
+    whichever kernel the size of the launch asks for."""
+    groups, h, w, few, many, small, large = case
+    m = zoo.Model("c", "bf16", 256, h, w)
+    a = m.add(zoo.CONV, -1, cin=256, cout=256, k=3, stride=2 if "mfma" in large else 1, pad=1, groups=groups, act=zoo.NONE)
+    m.add(zoo.MAXPOOL, a, k=1, stride=1, pad=0)
+    x = gen.make_input(62, many, 256, h, w, "normal", "bf16")
+    x[0, 5, 2, 3], x[0, 70, 4, 30], x[0, 255, h - 1, w - 1] = np.inf, np.nan, -np.inf
+    y = _same_bits(m, few, many, small, large, x=x)[2].reshape(few, -1, 8, 32)
+    hit = ~np.isfinite(y[0]).all(axis=(0, 2))
+    assert hit.tolist() == [True, False, True, False, False, False, False, True] and np.isfinite(y[1:]).all()
+
+
 def test_long_reductions_in_small_launches_keep_their_bits():
     """ResNet-50's last stage in isolation, a 3x3 over 512 channels and a 1x1 over 2048 at 7x7: one member at batch 32 has
     64x64 tiles; at batch 96 the 3x3 reads from a patch; eight members at batch 32 take the patch and, for the 1x1, the 128x128 tile
