@@ -150,11 +150,10 @@ __device__ __forceinline__ void runs_to_fragments(const uint32_t (&pk)[4][2], ui
     }
 }
 
-// One element of an fp32 convolution, output pixel m and channel o: the taps inside the image, one after the other.
-__device__ __forceinline__ float conv_element(const KArgs& a, const Desc& d, int64_t m, int o) {
-  const int q = (int)(m % d.Wo);
-  const int pp = (int)((m / d.Wo) % d.Ho);
-  const int n = (int)(m / ((int64_t)d.Wo * d.Ho));
+// One element of an fp32 convolution, output pixel (n, pp, q) and channel o: the taps inside the image, one after the other.
+// RARE: for a path that is hardly ever taken (short code: it is fetched with the code around it).
+template <bool RARE>
+__device__ __forceinline__ float conv_element(const KArgs& a, const Desc& d, int n, int pp, int q, int o) {
   const float* x = reinterpret_cast<const float*>(a.abase + d.x_off);
   const float* w = reinterpret_cast<const float*>(a.wbase + d.w_off) + (int64_t)o * d.Kp;
   float acc = 0.0f;
@@ -166,7 +165,12 @@ __device__ __forceinline__ float conv_element(const KArgs& a, const Desc& d, int
       if (iw < 0 || iw >= d.W) continue;
       const float* xr = x + (((int64_t)n * d.H + ih) * d.W + iw) * d.Cp;
       const float* wr = w + (r * d.kw + s) * d.Cp;
-      for (int c = 0; c < d.C; ++c) acc += xr[c] * wr[c];
+      if constexpr (RARE) {
+#pragma unroll 1
+        for (int c = 0; c < d.C; ++c) acc += xr[c] * wr[c];
+      } else {
+        for (int c = 0; c < d.C; ++c) acc += xr[c] * wr[c];
+      }
     }
   }
   return acc;

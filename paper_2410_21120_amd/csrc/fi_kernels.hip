@@ -72,8 +72,9 @@ __global__ void __launch_bounds__(256) stage_kernel(KArgs a) {
 }
 
 // ---------------------------------------------------------------------------------
-// direct convolution / FC: one thread per output element.  fp32 models, where a tensor
-// is larger than the 32-bit offsets of the matrix kernel reach.
+// direct convolution / FC: one thread per output element.  fp32 models: layers of so few
+// channels and products that a matrix tile would stay mostly empty, and tensors larger
+// than the 32-bit offsets of the matrix kernel reach.
 // ---------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) conv_direct_kernel(KArgs a) {
   int p, bid;
@@ -87,7 +88,10 @@ __global__ void __launch_bounds__(256) conv_direct_kernel(KArgs a) {
   const int64_t m = idx / d.Cop;
   float v = 0.0f;
   if (o < d.Co) {
-    v = conv_element(a, d, m, o) + reinterpret_cast<const float*>(a.wbase + d.b_off)[o];
+    const int q = (int)(m % d.Wo);
+    const int pp = (int)((m / d.Wo) % d.Ho);
+    const int n = (int)(m / ((int64_t)d.Wo * d.Ho));
+    v = conv_element<false>(a, d, n, pp, q, o) + reinterpret_cast<const float*>(a.wbase + d.b_off)[o];
     if (d.r_off != kNone) v += reinterpret_cast<const float*>(a.abase + d.r_off)[m * d.Cop + o];
     v = activate(v, d.act);
   }

@@ -174,14 +174,18 @@ __global__ void __launch_bounds__(NW * 64) conv_kwave_kernel(KArgs a) {
         const float4 v = *reinterpret_cast<const float4*>(&part[(w * 32 + row) * EPS + c]);
         sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
       }
-      if (F32 && (d.pad | d.pad_w) != 0) {
+      if (F32 && __builtin_expect(__builtin_isnan((sum.x + sum.y) + (sum.z + sum.w)) && (d.pad | d.pad_w) != 0, 0)) {
         // A tap outside the image reads zero here, and zero times a weight that is not finite is no zero: such a sum is
         // taken again over the taps inside the image only.
-#pragma nounroll
+        int again_p = p;
+        asm volatile("" : "+s"(again_p));   // (the descriptor is read again: its fields take no registers before)
+        const Desc& e = a.d[again_p];
+        const int g = m / e.Wo, n = g / e.Ho;
+#pragma unroll 1
         for (int t = 0; t < 4; ++t) {
           const float v = t == 0 ? sum.x : t == 1 ? sum.y : t == 2 ? sum.z : sum.w;
-          if (!__builtin_isnan(v) || o + t >= d.Co) continue;
-          const float again = conv_element(a, d, m, o + t);
+          if (!__builtin_isnan(v) || o + t >= e.Co) continue;
+          const float again = conv_element<true>(a, e, n, g - n * e.Ho, m - g * e.Wo, o + t);
           sum.x = t == 0 ? again : sum.x; sum.y = t == 1 ? again : sum.y; sum.z = t == 2 ? again : sum.z; sum.w = t == 3 ? again : sum.w;
         }
       }
