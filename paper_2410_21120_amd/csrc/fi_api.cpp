@@ -735,6 +735,23 @@ static bool takes_kwave(const fi_dag* g, const Node& nd, int B) {
   return kwave_fits(B, nd.H, nd.W, nd.Cp, nd.Ho, nd.Wo, nd.Co, (int64_t)nd.k * nd.kw, nd.Kp, 2);
 }
 
+// fp32: whether one thread per output element is over before the reduction-sharing kernel, whose tile costs the same
+// however few of its 64 columns and however little of a step's 32 elements a convolution fills.  Both estimates are in
+// microseconds and fit 736 layers measured alone (1 to 64 channels in, 1 to 128 out, 1x1 to 7x7, 64 to 524 288 rows, and fully
+// connected ones): the direct kernel takes 6 us per million outputs, 0.7 us per million products and 0.13 us per element of
+// the serial sum; the sharing one 14 ns per 64 x 64 tile and round of steps (50 ns with element-wise fetches), a quarter for a
+// 32 x 32 tile.  Geometric means: direct alone 37.5 us, sharing alone 21.2, by this rule 16.55, the better of the two 16.45; at the
+// ends 1 -> 1 channels, 3x3, 1024 x 1024 20 us direct and 686 shared, 512 -> 1000 features 68 and 9.5.  Past 256 elements the direct
+// kernel's strided reads of a row are slower than that (32 -> 1, 5x5, 8 x 256 x 256: 2454 and 520 us).
+static bool direct_is_shorter(int64_t rows, int64_t Co, int64_t K, bool scalar, int tile) {
+  if (K > 256) return false;
+  const int64_t side = kwave_side(tile), waves = tile == KW_32x8 ? 8 : 4, steps = (K + 31) / 32;
+  const double tiles = (double)((rows + side - 1) / side) * (double)((Co + side - 1) / side) * (side == 64 ? 1.0 : 0.25);
+  const double shared = (scalar ? 3.0 : 1.0) + tiles * (double)((steps + waves - 1) / waves) * (scalar ? 0.050 : 0.014);
+  const double outputs = (double)rows * (double)Co * 1e-6;
+  return 6.0 * outputs + 0.7 * outputs * (double)K + 0.13 * (double)K < shared;
+}
+
 // Planner pass: kernel family, tile and reduction split of every node.
 static fi_status choose_kernels(fi_dag* g) {
   const fi_build_opts* opts = &g->opts;
@@ -792,7 +809,7 @@ static fi_status choose_kernels(fi_dag* g) {
           }
           if (takes_kwave(g, nd, B)) { nd.kind = K_CONV_KWAVE; nd.tile = KW_32x8; nd.splits = 1; }
         } else {
-          // fp32 models: the reduction-sharing kernel.  The tile depends on the node's own shape only (it fixes the
+          // fp32 models: the reduction-sharing kernel, or one thread per output element.  Kernel and tile depend on the node's own shape only (it fixes the
           // summation order): 64 x 64 where that gives most compute units a workgroup, 32 x 32 below.  (ResNet-18,
           // MobileNetV2, 2 x SqueezeNet 1.1 in fp32, batch 4 / 8 / 8: 402 / 711 / 646 us with the line at 192 tiles,
           // 432 / 745 / 657 at 64, 408 / 712 / 661 at 400.)
@@ -801,9 +818,12 @@ static fi_status choose_kernels(fi_dag* g) {
           nd.kind = K_CONV_DIRECT;
           if (nd.op == FI_FC ? kwave_fits(B, 1, 1, cp, 1, 1, nd.Co, 1, nd.Kp, 4)
                              : kwave_fits(B, nd.H, nd.W, cp, nd.Ho, nd.Wo, nd.Co, (int64_t)nd.k * nd.kw, nd.Kp, 4)) {
-            nd.kind = K_CONV_KWAVE;
-            nd.tile = ((M + 63) / 64) * ((nd.Co + 63) / 64) >= 192 ? KW_64x4 : KW_32x8;
-            if (cp % 4) nd.tile |= KW_SCALAR;
+            const int tile = ((M + 63) / 64) * ((nd.Co + 63) / 64) >= 192 ? KW_64x4 : KW_32x8;
+            const int64_t K = nd.op == FI_FC ? (int64_t)nd.H * nd.W * nd.C : (int64_t)nd.k * nd.kw * nd.C;
+            if (!direct_is_shorter(M, nd.Co, K, cp % 4 != 0, tile)) {
+              nd.kind = K_CONV_KWAVE;
+              nd.tile = tile | (cp % 4 ? KW_SCALAR : 0);
+            }
           }
         }
         break;

@@ -23,7 +23,7 @@ inline uint64_t align_up(uint64_t v, uint64_t a = kAlign) { return (v + a - 1) /
 // Kernel families.  A launch runs one family over 1..FI_MAX_GROUP problems.
 enum Kind : int32_t {
   K_STAGE = 0,        // caller's NHWC input -> channel-padded copy in the activation arena
-  K_CONV_DIRECT = 1,  // one thread per output element (fp32 models beyond what K_CONV_KWAVE addresses)
+  K_CONV_DIRECT = 1,  // one thread per output element (fp32: few channels, short reductions, and beyond what K_CONV_KWAVE addresses)
   K_CONV_MFMA = 2,    // implicit GEMM on the matrix cores (bf16 weights, bf16 activations)
   K_DWCONV = 3,
   K_MAXPOOL = 4,

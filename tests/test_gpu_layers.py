@@ -118,6 +118,16 @@ def test_conv_f32_weights_that_are_not_finite(case):
     assert harness.rel_l2(y[finite], ref[finite]) <= 2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23
 
 
+@pytest.mark.parametrize("case", [(1, 8, 3, 1, 1, 61, 57, 5), (3, 3, 1, 1, 0, 97, 89, 3), (5, 7, 3, 2, 1, 301, 199, 5), (8, 8, 1, 1, 0, 67, 129, 4), (2, 1, 2, 2, 0, 131, 67, 9)])
+def test_conv_f32_of_few_products(case):
+    """fp32 convolutions of few channels and products, one thread per output element, with a residual; held like the above."""
+    cin, cout, k, s, p, h, w, b = case
+    m = zoo.Model("c", "f32", cin, h, w)
+    a = m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.NONE)
+    m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.RELU, residual=a)
+    _run_case(m, 930 + cin + cout, b, tol=2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23, kernels=[("conv_direct", 2)])
+
+
 def test_conv_f32_beyond_the_shared_reduction():
     """2^24 output rows, one more than the shared-reduction kernel decodes: the element-wise kernel, held like the above."""
     m = zoo.Model("c", "f32", 1, 4096, 4096)

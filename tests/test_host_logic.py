@@ -86,6 +86,24 @@ def test_grouping_reduces_launches_only():
     assert qg.act_bytes == qu.act_bytes
 
 
+@pytest.mark.parametrize("layer, kernel", [
+    ((1, 1, 3, 1, 1024, 1), "conv_direct"), ((1, 8, 3, 1, 512, 1), "conv_direct"), ((3, 3, 1, 0, 512, 1), "conv_direct"), ((2, 2, 1, 0, 256, 2), "conv_direct"),
+    ((4, 4, 1, 0, 256, 4), "conv_direct"), ((8, 8, 1, 0, 256, 4), "conv_direct"),
+    ((3, 64, 7, 3, 224, 1), "conv_kwave 64x64x4 scalar"), ((16, 16, 3, 1, 128, 4), "conv_kwave 64x64x4"), ((16, 96, 1, 0, 112, 8), "conv_kwave 64x64x4"),
+    ((32, 1, 5, 2, 256, 1), "conv_kwave 64x64x4"), ((3, 16, 3, 1, 32, 1), "conv_kwave 32x32x8 scalar"), ((256, 2, 1, 0, 64, 4), "conv_kwave 64x64x4"),
+    ((16, 8, 5, 2, 4096, 1), "conv_direct")])   # (2^24 rows: more than the matrix kernel decodes)
+def test_fp32_layers_of_few_products_keep_the_element_kernel(layer, kernel):
+    """An fp32 convolution whose matrix tiles would stay mostly empty runs one thread per output element."""
+    cin, cout, k, pad, hw, batch = layer
+    m = zoo.Model("c", "f32", cin, hw, hw)
+    m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=1, pad=pad, act=zoo.NONE)
+    m.shapes()
+    blob = gen.make_blob(m, 1)
+    spec, keep = fi.make_spec(m, blob.ctypes.data, blob.nbytes)
+    d = fi.Dag([spec], batch, fi.HostAllocators(), keepalive=(keep, blob))
+    assert [L.kernel for L in d.launches()][1:] == [kernel]
+
+
 def test_activation_arena_liveness_non_overlap():
     for fams in (["resnet50", "mobilenetv2", "vgg16"], ["resnet18"] * 3, ["tiny", "tiny"]):
         d, _, _ = _build(fams, 3, hw=64 if fams[0] != "tiny" else 32)
