@@ -103,7 +103,7 @@ class fi_launch_info(C.Structure):
     # the 32 x 32 blocks on the diagonal of grouped weights; x waves that share the reduction; "scalar": element-wise fetch.
     TILES = {b"conv_mfma_128x128": {5: "deep"},   # three reduction tiles in flight
              b"conv_patch": {0: "256x32", 1: "256x64", 2: "256x64 diag", 3: "512x128", 4: "512x64 diag"},
-             b"conv_kwave": {0: "64x64x4", 1: "32x32x8", 8: "64x64x4 scalar", 9: "32x32x8 scalar"}}
+             b"conv_kwave": {0: "64x64x4", 1: "32x32x8", 2: "64x64x8", 8: "64x64x4 scalar", 9: "32x32x8 scalar"}}
 
     @property
     def kernel(self):

@@ -722,8 +722,9 @@ static void assign_run_positions(fi_dag* g) {
 // three-model DAG at batch 8, a four-model serving round, 3x GoogLeNet at batch 13 and 4x DenseNet-121 at batch 32:
 // 220 / 1185 / 1022 / 633 / 3694 us without this kernel, 173 / 1128 / 827 / 617 / 3437 us with it up to 128 64x64 tiles
 // from 16 reduction tiles of 64 elements on; from 8 tiles on 165 / 1128 / 829 / 660 / 3438 us.  (64x64 tiles instead of
-// 32x32 for the larger half of the range: 1129 / 862 / 616 / 3540 us.)  Sixteen rows or less fill half a tile at most and
-// leave a workgroup per 32 output channels: the split over workgroups keeps them.
+// 32x32 for the larger half of the range: 1129 / 862 / 616 / 3540 us.)  Sixteen rows or less keep the split over workgroups, and
+// the bits, that they had before this kernel; that is not a line of speed (512 -> 512, 3x3, 9 rows 16.1 us split and 11.7 shared,
+// 2048 -> 512 pointwise, 16 rows 15.0 and 9.3, 1024 -> 2048, 16 rows, eight members 21.8 and 11.1).
 static bool takes_kwave(const fi_dag* g, const Node& nd, int B) {
   if (g->members[(size_t)nd.model].spec.act_dtype != FI_BF16 || nd.Cp == 4 || walks_groups(nd, FI_BF16)) return false;
   const int64_t M = (int64_t)B * nd.Ho * nd.Wo;
@@ -733,6 +734,34 @@ static bool takes_kwave(const fi_dag* g, const Node& nd, int B) {
     if (in.op == FI_MUL || (in.op == FI_DWCONV2D && in.k == 1)) return false;
   }
   return kwave_fits(B, nd.H, nd.W, nd.Cp, nd.Ho, nd.Wo, nd.Co, (int64_t)nd.k * nd.kw, nd.Kp, 2);
+}
+
+// bf16 problems on the shared-reduction kernel, once all are known: 64x64 tiles, which fetch half as much per product, where a launch has
+// the workgroups for it.  (The eight partial sums are the same ones: the same bits, so the rule may look at the launch.)  A
+// compute unit holds two workgroups of 32x32 tiles or one of 64x64; a round of the latter takes about 1.5 times as long.
+// Measured alone at 32x32 / 64x64, and on the tile kernel with its split reduction (us): 512 -> 512, 3x3, 7 x 7, batch 16, one member
+// 19.7 / 21.0 / 31.4, two 31.1 / 21.9 / 35.1, four 49.3 / 37.2 / 47.7, eight 87.5 / 70.8 / 70.7; 1024 -> 2048, 7 x 7, batch 5,
+// eight 47.4 / 38.6 / 36.2; 128 -> 32, 3x3, 28 x 28, batch 8 (half of a 64x64 tile's columns), eight 23.0 / 34.1 / 33.6.
+static void widen_shared_reductions(fi_dag* g) {
+  if (g->wdtype != FI_BF16) return;
+  struct Work { int64_t problems, small, large; };   // of the problems that share a launch
+  std::map<std::pair<int, int>, Work> launches;
+  auto tiles = [&](const Node& nd, int64_t side) { return (((int64_t)g->opts.max_batch * nd.Ho * nd.Wo + side - 1) / side) * ((nd.Co + side - 1) / side); };
+  auto widen = [](const Work& w, int64_t lanes) {   // (a launch carries FI_MAX_GROUP problems at most; sibling lanes share the chip)
+    const int64_t n = std::max<int64_t>(w.problems, FI_MAX_GROUP);
+    const int64_t r32 = (w.small * lanes * FI_MAX_GROUP / n + 511) / 512, r64 = (w.large * lanes * FI_MAX_GROUP / n + 255) / 256;
+    return 2 * r32 >= 3 * r64;
+  };
+  for (const Node& nd : g->nodes) {
+    if (nd.kind != K_CONV_KWAVE) continue;
+    Work& w = launches[std::make_pair(nd.run, nd.lane)];
+    ++w.problems; w.small += tiles(nd, 32); w.large += tiles(nd, 64);
+  }
+  for (Node& nd : g->nodes) {
+    if (nd.kind != K_CONV_KWAVE) continue;
+    const Work own = {1, tiles(nd, 32), tiles(nd, 64)};
+    if (widen(g->opts.group_levels ? launches[std::make_pair(nd.run, nd.lane)] : own, g->members[(size_t)nd.model].sibling_lanes)) nd.tile = KW_64x8;
+  }
 }
 
 // fp32: whether one thread per output element is over before the reduction-sharing kernel, whose tile costs the same
@@ -839,6 +868,7 @@ static fi_status choose_kernels(fi_dag* g) {
     }
   }
 
+  widen_shared_reductions(g);
   return FI_OK;
 }
 

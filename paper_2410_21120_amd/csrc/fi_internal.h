@@ -56,9 +56,10 @@ enum Tile : int32_t { T_128x128 = 0, T_128x64 = 1, T_64x64 = 2, T_256x128 = 3, T
 FI_HD inline int tile_bm(int t) { return (t == T_256x128 || t == T_256x64) ? 256 : t == T_64x64 ? 64 : 128; }
 FI_HD inline int tile_bn(int t) { return (t == T_128x128 || t == T_256x128 || t == T_128x128_DEEP) ? 128 : 64; }
 
-// Tiles of the K_CONV_KWAVE kernels: side of the square tile x waves that share its reduction.  KW_SCALAR is added for
+// Tiles of the K_CONV_KWAVE kernels: side of the square tile x waves that share its reduction (the bits depend on the waves, not
+// on the side; fp32 takes the first two, bf16 the last two).  KW_SCALAR is added for
 // fp32 tensors whose channel stride four does not divide.
-enum KwaveTile : int32_t { KW_64x4 = 0, KW_32x8 = 1, KW_NTILES, KW_SCALAR = 8 };
+enum KwaveTile : int32_t { KW_64x4 = 0, KW_32x8 = 1, KW_64x8 = 2, KW_NTILES, KW_SCALAR = 8 };
 FI_HD inline int kwave_side(int t) { return t == KW_32x8 ? 32 : 64; }
 // Tiles of the K_CONV_PATCH kernel: rows x columns; DIAG: groups of at most 32 channels, only the 32 x 32 blocks of the
 // weights on the diagonal are multiplied.  A tile's patch holds rows + 2 W + 2 pixels of 64 channels.

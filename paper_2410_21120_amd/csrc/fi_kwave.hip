@@ -19,6 +19,10 @@
 // bf16), which asks so little of LDS and L1 that a wave may own a whole 64 x 64 tile.  Measured, ResNet-18 in fp32 at
 // batch 4: the 56 x 56 x 64 3x3 layers 20 us each (46 TFLOP/s), the pass 18.2 ms -> 0.40 ms against one thread per
 // output element, whose serial sums also gave way to four or eight shorter ones (closer to the exact value).
+//
+// bf16 problems take eight waves and tiles of 32 x 32, or of 64 x 64 (128 KB of LDS, one workgroup per compute unit) where a launch
+// fills the chip: half the operand bytes per product.  The eight partial sums of an element are the same ones in either
+// tile.  512 -> 512, 3x3, 7 x 7, batch 16, eight members: 87.5 -> 70.8 us.
 #include <hip/hip_runtime.h>
 
 #include "fi_device.h"
@@ -55,7 +59,14 @@ __global__ void __launch_bounds__(NW * 64) conv_kwave_kernel(KArgs a) {
   const Desc d = a.d[p];
   const int batch = a.batch[p];
   const int M = batch * d.Ho * d.Wo;
-  const int m0 = (bid / d.tiles_n) * BM, n0 = (bid % d.tiles_n) * BN;
+  // Neighbouring workgroups (one XCD, one L2) share the larger operand: the rows of a column tile where a bf16 problem's weights
+  // are larger than its input, the columns of a row tile otherwise.
+  // 2048 -> 2048 pointwise, 125 rows, eight members 32.6 -> 26.9 us, 512 -> 1024, 3x3, 100 rows, two members 17.4 -> 13.4.
+  const int tiles_m = (M + BM - 1) / BM;
+  const bool by_column = !F32 && (int64_t)d.Co * d.Kp > (int64_t)batch * d.H * d.W * d.Cp;
+  const int along = by_column ? tiles_m : d.tiles_n;
+  const int outer = bid / along, inner = bid - outer * along;
+  const int m0 = (by_column ? inner : outer) * BM, n0 = (by_column ? outer : inner) * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -244,6 +255,7 @@ int launch_kwave(const Launch& L, const KArgs& args, void* stream, const std::ve
   FI_KWAVE_CASE(true, true, KW_64x4, 2, 4)
   FI_KWAVE_CASE(true, true, KW_32x8, 1, 8)
   FI_KWAVE_CASE(false, false, KW_32x8, 1, 8)
+  FI_KWAVE_CASE(false, false, KW_64x8, 2, 8)
 #undef FI_KWAVE_CASE
   return (int)hipErrorInvalidValue;
 }

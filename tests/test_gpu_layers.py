@@ -149,7 +149,34 @@ def test_conv_bf16_shared_reduction(case):
     c = m.add(zoo.CONV, -1, cin=cin, cout=24, k=k, stride=s, pad=p, act=zoo.HARDSWISH)
     q = m.add(zoo.CONCAT, c, residual=r)
     m.add(zoo.CONV, q, cin=24 + cout, cout=32, k=1, stride=1, pad=0, act=zoo.NONE)
-    _run_case(m, 970 + cin + cout, b, kernels=[("conv_kwave 32x32x8", 3)])
+    _run_case(m, 970 + cin + cout, b, kernels=[("conv_kwave 32x32x8", 1), ("conv_kwave 64x64x8", 2)] if h == 36 else [("conv_kwave 32x32x8", 3)])   # (the last case: two problems share a launch)
+
+
+@pytest.mark.parametrize("case", [(512, 512, 3, 1, 1, 7, 7, 16, 3),    # whole tiles of columns, ragged rows
+                                  (1024, 120, 1, 1, 0, 31, 1, 24, 16), # ragged rows and columns, 16 steps: two per wave
+                                  (120, 248, 3, 2, 1, 13, 11, 9, 16),  # a step that spans two taps, a last step of half its length
+                                  (2048, 512, 1, 1, 0, 5, 5, 5, 16)])  # weights larger than the input
+def test_shared_reduction_in_large_launches_keeps_its_bits(case):
+    """One member has 32x32 tiles, a launch of many members 64x64 ones: the same bits, a residual included."""
+    from tests import harness
+    cin, cout, k, s, p, h, w, b, members = case
+    m = zoo.Model("c", "bf16", cin, h, w)
+    e = m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.NONE)
+    r = m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.HARDSWISH, residual=e)
+    m.add(zoo.MAXPOOL, r, k=1, stride=1, pad=0)
+    m.shapes()
+    blob = gen.make_blob(m, 81)
+    x = gen.make_input(82, b, cin, h, w, "normal", "bf16")
+    outs = []
+    for n, kernel in ((1, "conv_kwave 32x32x8"), (members, "conv_kwave 64x64x8")):
+        g = harness.GpuDag([(m, blob, None)] * n, b)
+        try:
+            assert sum(L.n_problems for L in g.dag.launches() if L.kernel == kernel) == 2 * n, [L.kernel for L in g.dag.launches()]
+            outs.append(g.run(x))
+        finally:
+            g.close()
+    assert all(np.array_equal(y, outs[0][0]) for y in outs[1])
+    harness.check_against_oracle("shared reduction", m, blob, None, x, outs[0][0], rows=[0, b - 1])
 
 
 PATCH_CASES = [  # cin, cout, groups, H, W, batch, tile
