@@ -138,10 +138,15 @@ __global__ void __launch_bounds__(256) conv_direct_kernel(KArgs a) {
 // DEPTH: reduction tiles in flight in registers.  One (a tile's loads overlap the multiply of the tile before) is enough
 // where several workgroups share a compute unit; a launch of few workgroups with a long reduction (one or two per
 // compute unit, nothing else to hide a load behind) takes three, at the price of 64 registers.
-template <int TILE, int BM, int BN, int WGM, int WGN, bool WIDE, bool C4 = false, bool GROUPED = false, int PRE = 0, int DEPTH = 1>
+// RUNS: every problem of the launch is walked in 64-channel runs (below), so the position is the same in every lane and stays
+// in scalar registers.  The 256x64 tile has this form: 64 -> 64, 3x3, 224 x 224, four members at batch 4, 137 -> 115 us alone (118
+// before there was a second walk).  On the smaller tiles, whose launches are short, further kernels or a second loop cost more in
+// instruction fetches than they save (2x ResNet-18 at one image 167.7 -> 170.5 us, a serving round of four models 800 -> 813).
+template <int TILE, int BM, int BN, int WGM, int WGN, bool WIDE, bool C4 = false, bool GROUPED = false, int PRE = 0, int DEPTH = 1, bool RUNS = false>
 __global__ void __launch_bounds__(WGM * WGN * 64) conv_mfma_kernel(KArgs a) {
   static_assert(!GROUPED || (!WIDE && !C4), "the group walk exists for bf16 activations with 8-channel vectors");
   static_assert(DEPTH == 1 || (!WIDE && !C4 && !GROUPED && PRE == 0), "deeper prefetch exists for the plain bf16 convolution");
+  static_assert(!RUNS || (!WIDE && !C4 && !GROUPED && PRE == 0), "the walk over 64-channel runs exists for the plain bf16 convolution");
   static_assert(!PRE || (!C4 && !GROUPED && (!WIDE || PRE == 2)),
                 "input-side stages exist for dense pointwise convolutions: the affine one on bf16 activations, the gate on either");
   constexpr int NT = WGM * WGN * 64;     // threads per workgroup
@@ -241,7 +246,7 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv_mfma_kernel(KArgs a) {
   // channels (the order in which the patch kernel of fi_patch.hip has its operands in LDS, so that both give the same
   // bits); otherwise every channel of a tap, then the next tap.
   // (The patch kernel has no fp32-stored form, and a pointwise convolution has one tap: those keep the plain walk.)
-  const bool tap_inner = !C4 && !WIDE && PRE == 0 && (GROUPED || d.Cp % BK == 0);
+  const bool tap_inner = !C4 && !WIDE && PRE == 0 && (GROUPED || RUNS || d.Cp % BK == 0);
   const int c_step = tap_inner ? 0 : BK;
   const int ntiles_all = GROUPED ? d.k * d.kw * (c_len / BK) : (d.Kp + BK - 1) / BK;
   const int per_split = (ntiles_all + d.splits - 1) / d.splits;
@@ -260,6 +265,17 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv_mfma_kernel(KArgs a) {
     kc = k0 - rs * d.Cp;
     kr = rs / d.kw;
     ks = rs - kr * d.kw;
+  }
+
+  // RUNS: this position past a row's window origin (bytes, this thread's vector) and in a weight row (vectors), and what the next
+  // tap adds to them: within a filter row, into the next one, into the next 64 channels
+  int run_x = 0, run_w = 0, next_row_x = 0, next_run_x = 0, next_run_w = 0;
+  if constexpr (RUNS) {
+    run_x = ((kr * d.W + ks) * d.Cp + kc) * AE;
+    run_w = ((kr * d.kw + ks) * d.Cp + kc - kvec) >> 3;
+    next_row_x = (d.W - d.kw + 1) * d.Cp * AE;
+    next_run_x = (BK - ((d.k - 1) * d.W + d.kw - 1) * d.Cp) * AE;
+    next_run_w = (BK - (d.k * d.kw - 1) * d.Cp) / 8;
   }
 
   f32x16 acc[MI][NI];
@@ -284,7 +300,7 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv_mfma_kernel(KArgs a) {
     /* a fetch past the last tile: the top bit puts every offset out of range (plain arithmetic, so no branch on it) */ \
     const uint32_t dead = (LIVE) ? 0u : OOB;                                                      \
     if constexpr (!C4) {                                                                          \
-      const int tvar = ((kr * d.W + ks) * d.Cp + kc) * AE;                                        \
+      const int tvar = RUNS ? run_x : ((kr * d.W + ks) * d.Cp + kc) * AE;                         \
       _Pragma("unroll") for (int i = 0; i < AR; ++i) {                                            \
         const bool ok = ((a_rc[i] >> kr) & (a_rc[i] >> (16 + ks)) & 1) != 0;                       \
         const uint32_t off = (ok ? (uint32_t)(a_row[i] + tvar) : OOB) | dead;                     \
@@ -326,13 +342,21 @@ __global__ void __launch_bounds__(WGM * WGN * 64) conv_mfma_kernel(KArgs a) {
       pre_t[S][0] = pok ? *reinterpret_cast<const float4*>(pre_b + kc) : make_float4(0, 0, 0, 0); \
       pre_t[S][1] = pok ? *reinterpret_cast<const float4*>(pre_b + kc + 4) : make_float4(0, 0, 0, 0); \
     }                                                                                             \
-    const bool bok = !(b_tail && (KT) == ntiles_all - 1 && kvec >= 32);                           \
+    const bool bok = RUNS || !(b_tail && (KT) == ntiles_all - 1 && kvec >= 32);                           \
     /* position of this tile in a weight row, in 8-element vectors past the thread's own kvec */  \
-    const int wt = tap_inner ? ((kr * d.kw + ks) * d.Cp + kc - kvec) >> 3 : (KT) * (BK / 8);        \
+    const int wt = RUNS ? run_w : tap_inner ? ((kr * d.kw + ks) * d.Cp + kc - kvec) >> 3 : (KT) * (BK / 8); \
     _Pragma("unroll") for (int i = 0; i < BR; ++i)                                                \
         bv[S][i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(wres, (bok ? (uint32_t)(b_row[i] + wt * 16) : OOB) | dead, 0, 0)); \
     kc += c_step;                                                                                 \
-    if (GROUPED || one_wrap) { /* at least 64 channels per tap: the walk leaves a tap at most once per tile */ \
+    if constexpr (RUNS) {                                                                         \
+      const bool row = ++ks == d.kw;                                                              \
+      ks = row ? 0 : ks;                                                                          \
+      kr += row ? 1 : 0;                                                                          \
+      const bool run = kr == d.k;                                                                 \
+      kr = run ? 0 : kr;                                                                          \
+      run_x += run ? next_run_x : row ? next_row_x : d.Cp * AE;                                   \
+      run_w += run ? next_run_w : d.Cp / 8;                                                       \
+    } else if (GROUPED || one_wrap) { /* at least 64 channels per tap: the walk leaves a tap at most once per tile */ \
       const bool over = kc >= c_hi;                                                               \
       kc -= over ? c_len : 0;                                                                     \
       ks += (over || tap_inner) ? 1 : 0;                                                          \
@@ -1767,7 +1791,12 @@ int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::v
 #undef FI_PRE_TILES
       }
       if (L.tile == T_256x128) return go(conv_mfma_kernel<T_256x128, 256, 128, 2, 2, false>, nb, 256, a, s);
-      if (L.tile == T_256x64) return go(conv_mfma_kernel<T_256x64, 256, 64, 4, 1, false>, nb, 256, a, s);
+      if (L.tile == T_256x64) {
+        bool runs = true;
+        for (int i = 0; i < L.n; ++i) runs = runs && hd[(size_t)(L.first_desc + i)].Cp % 64 == 0;
+        if (runs) return go(conv_mfma_kernel<T_256x64, 256, 64, 4, 1, false, false, false, 0, 1, true>, nb, 256, a, s);
+        return go(conv_mfma_kernel<T_256x64, 256, 64, 4, 1, false>, nb, 256, a, s);
+      }
       if (L.tile == T_128x128) return go(conv_mfma_kernel<T_128x128, 128, 128, 2, 2, false>, nb, 256, a, s);
       if (L.tile == T_128x128_DEEP) return go(conv_mfma_kernel<T_128x128_DEEP, 128, 128, 2, 2, false, false, false, 0, 3>, nb, 256, a, s);
       if (L.tile == T_128x64) return go(conv_mfma_kernel<T_128x64, 128, 64, 2, 2, false>, nb, 256, a, s);

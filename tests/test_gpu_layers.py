@@ -248,6 +248,15 @@ def test_fc_f32_shared_reduction(features, batch):
     _run_case(m, 950 + features, batch, tol=2.0 * 350 ** 0.5 * 2.0 ** -23)
 
 
+@pytest.mark.parametrize("cin, k, stride", [(64, 3, 1), (128, 5, 2), (72, 3, 1)])
+def test_conv_256x64_tile_has_the_bits_of_the_small_tile(cin, k, stride):
+    """Images wider than a patch: the 256x64 tile walks 64-channel runs with a loop of its own, other channel strides with the common one."""
+    m = zoo.Model("c", "bf16", cin, 131 if stride == 1 else 263, 125 if stride == 1 else 251)
+    a = m.add(zoo.CONV, -1, cin=cin, cout=64, k=k, stride=stride, pad=k // 2, act=zoo.NONE)
+    m.add(zoo.MAXPOOL, a, k=1, stride=1, pad=0)
+    assert np.isfinite(_same_bits(m, 1, 5, "conv_mfma_64x64", "conv_mfma_256x64")[2]).all()
+
+
 @pytest.mark.parametrize("case", [(32, 21, 35, 2, 24, "conv_mfma_64x64", "conv_patch 256x64 diag"), (32, 7, 220, 1, 12, "conv_mfma_64x64", "conv_patch 512x64 diag"),
                                   (8, 21, 35, 12, 24, "conv_mfma_128x64", "conv_patch 256x64 diag"), (16, 29, 110, 10, 20, "conv_mfma_128x64", "conv_mfma_256x64")])
 def test_grouped_conv_activations_that_are_not_finite(case):
