@@ -527,29 +527,32 @@ static void take_stem_launches(fi_dag* g) {
 static void take_patch_launches(fi_dag* g) {
   if (g->wdtype != FI_BF16) return;
   const int64_t B = g->opts.max_batch;
-  std::map<std::tuple<int, int, int, int, int>, int> same;   // convolutions of one shape that share a launch
-  auto shape = [](const Node& nd) { return std::make_tuple(nd.run, nd.lane, nd.tile, nd.Ho * nd.Wo, nd.Co); };
-  if (g->opts.group_levels)
-    for (const Node& nd : g->nodes)
-      if (nd.kind == K_CONV_MFMA) ++same[shape(nd)];
-  for (Node& nd : g->nodes) {
-    const Member& mb = g->members[(size_t)nd.model];
-    const int adt = mb.spec.act_dtype;
+  auto eligible = [&](const Node& nd) {   // what the kernel computes and addresses, whatever the launch
+    const int adt = g->members[(size_t)nd.model].spec.act_dtype;
     if (nd.kind != K_CONV_MFMA || nd.op != FI_CONV2D || adt != FI_BF16 || nd.out_dtype != FI_BF16 || nd.is_output || nd.elided || nd.pre >= 0 ||
         nd.chain >= 0 || nd.splits != 1)
-      continue;
-    if (nd.k != 3 || nd.kw != 3 || nd.stride != 1 || nd.pad != 1 || nd.pad_w != 1 || nd.Cp % 64 || nd.Co != nd.Cop || nd.Co % 8 || nd.Kp != 9 * nd.Cp) continue;
+      return false;
+    if (nd.k != 3 || nd.kw != 3 || nd.stride != 1 || nd.pad != 1 || nd.pad_w != 1 || nd.Cp % 64 || nd.Co != nd.Cop || nd.Co % 8 || nd.Kp != 9 * nd.Cp) return false;
+    if (nd.groups > 1 && (!walks_groups(nd, adt) || nd.C != nd.Co || 64 % (nd.Co / nd.groups) || nd.Co % 64)) return false;   // a 64-column tile has to read the 64 channels of the same index
     const int64_t ys = nd.root >= 0 ? g->nodes[(size_t)nd.root].Cop : nd.Cop;
-    if ((B * nd.Ho * nd.Wo + 512) * ys * 2 >= (1ll << 31) || (int64_t)nd.Co * nd.Kp * 2 >= (1ll << 31)) continue;   // 32-bit offsets
+    return (B * nd.Ho * nd.Wo + 512) * ys * 2 < (1ll << 31) && (int64_t)nd.Co * nd.Kp * 2 < (1ll << 31);   // 32-bit offsets
+  };
+  std::map<std::tuple<int, int, int, int, int, int, int, int>, int> same;   // such convolutions of one shape that share a launch
+  auto shape = [](const Node& nd) { return std::make_tuple(nd.run, nd.lane, nd.tile, nd.Ho, nd.Wo, nd.Co, nd.Cp, nd.groups); };
+  if (g->opts.group_levels)
+    for (const Node& nd : g->nodes)
+      if (eligible(nd)) ++same[shape(nd)];
+  for (Node& nd : g->nodes) {
+    if (!eligible(nd)) continue;
+    const Member& mb = g->members[(size_t)nd.model];
     const auto it = same.find(shape(nd));
     const int64_t group = it == same.end() ? 1 : std::min<int64_t>((int64_t)it->second * mb.sibling_lanes, FI_MAX_GROUP);
     auto blocks = [&](int t) { return group * ((B * nd.Ho * nd.Wo + patch_bm(t) - 1) / patch_bm(t)) * ((nd.Co + patch_bn(t) - 1) / patch_bn(t)); };
     const int narrow = nd.Co <= 32 ? PT_256x32 : PT_256x64;
     int tile = -1;
-    if (nd.groups > 1) {   // a 64-column tile has to read the 64 channels of the same index
-      const int per = nd.Co / nd.groups;
-      if (!walks_groups(nd, adt) || nd.C != nd.Co || 64 % per || nd.Co % 64 || nd.tile != T_256x64) continue;
-      tile = per > 32 ? PT_256x64 : patch_fits(PT_256x64_DIAG, nd.W) ? PT_256x64_DIAG : PT_512x64_DIAG;
+    if (nd.groups > 1) {
+      if (nd.tile != T_256x64) continue;
+      tile = nd.Co / nd.groups > 32 ? PT_256x64 : patch_fits(PT_256x64_DIAG, nd.W) ? PT_256x64_DIAG : PT_512x64_DIAG;
     } else if (nd.tile == T_256x64) {
       tile = narrow;
     } else if (nd.tile == T_256x128) {

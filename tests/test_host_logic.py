@@ -104,6 +104,28 @@ def test_fp32_layers_of_few_products_keep_the_element_kernel(layer, kernel):
     assert [L.kernel for L in d.launches()][1:] == [kernel]
 
 
+def test_patch_launches_count_the_convolutions_they_carry():
+    """The patch kernel's lines are in workgroups of one launch.  A 1x1 convolution beside a 3x3 of the same size, output channels and
+    tile stays on the tile kernel and must not count: 42 images of 28 x 28 x 256 are 130 tiles of 512x128, below the line of 256 (two
+    members: 260)."""
+    def kernels(members, pointwise):
+        m = zoo.Model("c", "bf16", 64, 28, 28)
+        a = m.add(zoo.CONV, -1, cin=64, cout=128, k=1, stride=1, pad=0, act=zoo.RELU)
+        wide = m.add(zoo.CONV, -1, cin=64, cout=1152, k=1, stride=1, pad=0, act=zoo.RELU)
+        b = m.add(zoo.CONV, a, cin=128, cout=256, k=3, stride=1, pad=1, act=zoo.NONE)
+        c = m.add(zoo.CONV, wide, cin=1152, cout=256 if pointwise else 8, k=1, stride=1, pad=0, act=zoo.NONE)
+        q = m.add(zoo.CONCAT, b, residual=c)
+        m.add(zoo.CONV, q, cin=512 if pointwise else 264, cout=8, k=1, stride=1, pad=0, act=zoo.NONE)
+        m.shapes()
+        blob = gen.make_blob(m, 1)
+        made = [fi.make_spec(m, blob.ctypes.data, blob.nbytes) for _ in range(members)]
+        d = fi.Dag([s for s, _ in made], 42, fi.HostAllocators(), keepalive=(blob, [k for _, k in made]), separate_chains=True)
+        return [L.kernel for L in d.launches() if L.level == 2]
+    assert "conv_patch 256x64" in kernels(1, False) and "conv_patch 512x128" in kernels(2, False)
+    with_pointwise = kernels(1, True)
+    assert "conv_patch 256x64" in with_pointwise and "conv_mfma_256x128" in with_pointwise
+
+
 def test_activation_arena_liveness_non_overlap():
     for fams in (["resnet50", "mobilenetv2", "vgg16"], ["resnet18"] * 3, ["tiny", "tiny"]):
         d, _, _ = _build(fams, 3, hw=64 if fams[0] != "tiny" else 32)
