@@ -150,6 +150,15 @@ __device__ __forceinline__ void runs_to_fragments(const uint32_t (&pk)[4][2], ui
     }
 }
 
+typedef __attribute__((address_space(3))) void lds_void;
+
+// One direct load: lane l's N bytes at `off` go to at + N * l (zeros where `off` is out of range).
+template <int N>
+__device__ __forceinline__ void load_lds(const __amdgpu_buffer_rsrc_t res, uint8_t* at, uint32_t off) {
+  if constexpr (N == 16) __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void*)at, 16, off, 0, 0, 0);
+  else __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void*)at, 4, off, 0, 0, 0);
+}
+
 // One element of an fp32 convolution, output pixel (n, pp, q) and channel o: the taps inside the image, one after the other.
 // RARE: for a path that is hardly ever taken (short code: it is fetched with the code around it).
 template <bool RARE>

@@ -101,8 +101,8 @@ struct Desc {
                                  // when the pool is part of the launch)
   int32_t xs, ys;                // elements between neighbouring pixels of the input / output: Cp / Cop, or the channel stride of the
                                  // concatenation the tensor is stored inside (read by the depthwise kernels and by MFMA convolutions
-                                 // with an input-side stage, written by the bf16 vector kernels and the MFMA convolution; every other
-                                 // kernel sees xs == Cp, ys == Cop: launch_kernel checks)
+                                 // with an input-side stage, written by the bf16 vector kernels and the matrix convolutions: tile, shared-reduction and patch kernel; every
+                                 // other kernel sees xs == Cp, ys == Cop: launch_kernel and the kernels' own launchers check)
   uint64_t pw_off, pb_off;       // MFMA conv with a stage on its input side.  pre_kind 1, per-channel affine: scale (bf16 [Cp]) and
                                  // shift (fp32 [Cp]) in the weight arena.  pre_kind 2, per-(image, channel) gate: pw_off is the gate
                                  // tensor [batch][Cp] (bf16) in the activation region.  kNone where unused

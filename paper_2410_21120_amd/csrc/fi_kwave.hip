@@ -30,15 +30,6 @@
 
 namespace fi {
 
-typedef __attribute__((address_space(3))) void lds_void;
-
-// One direct load: lane l's N bytes at `off` go to at + N * l (zeros where `off` is out of range).
-template <int N>
-__device__ __forceinline__ void load_lds(const __amdgpu_buffer_rsrc_t res, uint8_t* at, uint32_t off) {
-  if constexpr (N == 16) __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void*)at, 16, off, 0, 0, 0);
-  else __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void*)at, 4, off, 0, 0, 0);
-}
-
 // F32: fp32 weights and activations.  SCALAR: a channel stride that four does not divide (an RGB input): rows are not
 // 16-byte aligned and a piece may span two filter taps, so every element is fetched by itself (4-byte loads, no swizzle).
 template <bool F32, bool SCALAR, int MI, int NI, int NW>

@@ -27,12 +27,6 @@
 namespace fi {
 namespace {
 
-typedef __attribute__((address_space(3))) void lds_void;
-
-__device__ __forceinline__ void load_lds16(const __amdgpu_buffer_rsrc_t res, uint8_t* at, uint32_t off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void*)at, 16, off, 0, 0, 0);
-}
-
 // NW waves, each owns 64 rows of the tile.  PX: pixels the patch holds.  DIAG: a grouped convolution with groups of at
 // most 32 channels: of a tap's 64 x 64 weights only the two 32 x 32 blocks on the diagonal are other than zero.
 template <int TILE, bool DIAG>
@@ -82,7 +76,7 @@ __global__ void __launch_bounds__(patch_bm(TILE)) conv_patch_kernel(KArgs a) {
     const uint32_t dead = fetched < T ? 0u : OOB;
 #pragma unroll
     for (int i = 0; i < LPB; ++i)
-      load_lds16(wres, ring + f_stage * STAGE_B + (wave + i * NW) * 1024, (w_row[i] + (uint32_t)f_off) | dead);
+      load_lds<16>(wres, ring + f_stage * STAGE_B + (wave + i * NW) * 1024, (w_row[i] + (uint32_t)f_off) | dead);
     ++fetched;
     f_stage = f_stage == 2 ? 0 : f_stage + 1;
     const bool wrap = ++f_tap == 9;
@@ -94,7 +88,7 @@ __global__ void __launch_bounds__(patch_bm(TILE)) conv_patch_kernel(KArgs a) {
     for (int i = wave; i < nload; i += NW) {
       const int g = g0 + i * 8 + lrow;
       const uint32_t off = (g >= 0 && g < npix) ? (uint32_t)(g * Cp * 2 + c_off) : OOB;
-      load_lds16(xres, smem + i * 1024, off);
+      load_lds<16>(xres, smem + i * 1024, off);
     }
   };
   fetch_b();
