@@ -59,6 +59,7 @@ def main():
     ap.add_argument("--swap-requests", type=int, default=1000, help="requests of the swap-churn stream that are replayed (the stream has 1000)")
     ap.add_argument("--launch-table", default=None, metavar="FILE",
                     help="also write the per-launch roofline table (every launch beside its own roofline ceiling) as markdown")
+    ap.add_argument("--detail", default=None, metavar="FILE", help="also write the whole result, the row of every launch included, as JSON")
     ap.add_argument("--member-chunks", type=int, default=2,
                     help="fi_build_opts.member_chunks of the timed DAG: the early, activation-heavy levels run for one chunk of a lane's "
                          "members after the other (smaller activation arena, more launches); 0 = every level for all members together")
@@ -319,7 +320,11 @@ def main():
         sw["fused_vs_per_model"] = {k: sw["fused"][k] / sw["per_model"][k] for k in ("p50_ms", "p95_ms", "p99_ms")}
         res["serving"] = serving(fi, torch, gen, zoo, alloc, stream)
         res["cpu_baseline"] = cpu_baseline(members[0], x, len(members))
-    print(json.dumps(res))
+    if a.detail:
+        with open(a.detail, "w") as fh:
+            json.dump(res, fh, indent=1)
+    # the line holds the summary: the rows of launches and kernels (four fifths of the text) go to --detail and --launch-table
+    print(json.dumps({k: v for k, v in res.items() if k not in ("per_launch", "kernels", "paper_context")}))
 
 
 # HBM traffic of the dominant kernel from rocprofv3 --pmc (FETCH_SIZE, WRITE_SIZE; KiB per dispatch,
