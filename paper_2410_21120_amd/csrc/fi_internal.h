@@ -207,6 +207,11 @@ int launch_chain(const Launch& L, const KArgs& a, void* stream, const std::vecto
 // Implemented in fi_kwave.hip: a K_CONV_KWAVE launch.  Returns a hipError_t as int.
 int launch_kwave(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);
 
+// Implemented in fi_stream.hip: a K_CONV_MFMA launch of pointwise convolutions whose rows stream (descriptors and batches filled in).
+// stream_fits says whether a launch is one, and with which blocks of columns and pieces of a row launch_stream takes it.
+bool stream_fits(const Launch& L, const KArgs& a, int* nb, int* nch);
+int launch_stream(const Launch& L, const KArgs& a, int nb, int nch, void* stream);
+
 // Implemented in fi_patch.hip: a K_CONV_PATCH launch.  Returns a hipError_t as int.
 int launch_patch(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);
 

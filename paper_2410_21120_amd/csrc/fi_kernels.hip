@@ -1733,6 +1733,10 @@ int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::v
       return wb ? (int)hipErrorInvalidValue : go(conv_direct_kernel, nb, 256, a, s);
     case K_CONV_MFMA:
       if (!wb) return (int)hipErrorInvalidValue;
+      {   // many rows and a short reduction: they stream (the same bits, so the choice is made for the batches of this pass)
+        int cols = 0, pieces = 0;
+        if (stream_fits(L, a, &cols, &pieces)) return launch_stream(L, a, cols, pieces, stream);
+      }
       if (hd[(size_t)L.first_desc].Cp == 4) {  // 4-channel model input
         if (!ab) {
           if (L.tile == T_128x128) return go(conv_mfma_kernel<T_128x128, 128, 128, 2, 2, true, true>, nb, 256, a, s);

@@ -1,0 +1,299 @@
+// Pointwise convolutions of many rows and a short reduction: rows stream through waves that never meet.
+//
+// Such a layer is bound by HBM: each row is read once, each output row written once, and the weights (at most 128 columns x 384
+// elements) stay on chip.  The tile kernel of fi_kernels.hip gives a workgroup one 128-row tile, whose life is a prologue, one to
+// six reduction tiles with two barriers each and one tile of loads in flight, and an epilogue: 2.0 to 3.4 TB/s.  Here eight waves share
+// the weights in LDS (one workgroup per compute unit, loaded once) and each takes blocks of 32 rows on its own: a lane loads
+// the 16-byte pieces that the matrix instruction wants of it straight into registers, the whole next block requested piece by piece
+// while this one is multiplied (up to 128 KB in flight per compute unit), no barrier after the start.  Outputs turn through a 4 KB patch of the wave's own, so
+// that whole cache lines leave: 16-byte pieces straight from the accumulators' layout, 32 bytes of a row at a time, written past the
+// cache cost 166 us where the tile took 69 (112 x 112, fp32 rows, 16 -> 64 channels).
+//
+// Measured alone, tile kernel -> this one (us): DenseNet-121, four members at batch 32, 56 x 56, affine and ReLU on the way in, 64 / 128 /
+// 192 / 256 -> 128 channels 54.1 / 61.4 / 74.6 / 90.3 -> 40.5 / 40.8 / 59.7 / 65.1 (3.8 to 5.0 TB/s; a copy reaches 5.2); MobileNetV3-Large, fp32 rows,
+// two members at batch 32, 112 x 112, 16 -> 16 60.6 -> 37.6, 16 -> 64 69.3 -> 52.9, 56 x 56, 24 -> 72 35.4 -> 26.5.
+// Wider outputs would read every row once per 128 columns, at different times: 256 -> 256 channels, 56 x 56, 69.6 -> 124.6 us, so they keep the tile.
+//
+// The order of the sums (ascending channels, 16 per instruction, from zero; for fp32 rows the small halves first) and the epilogue's operations are the
+// tile kernel's, so the bits are the same whichever kernel a launch takes.
+#include <hip/hip_runtime.h>
+
+#include "fi_device.h"
+#include "fi_internal.h"
+
+namespace fi {
+namespace {
+
+constexpr int SW = 8;   // waves of a workgroup
+
+// WIDE: fp32-stored activations, multiplied as hi + lo bf16 halves.  PRE: 1 = per-channel affine and activation on the way in.
+// NB: 32-column blocks of a workgroup's weights.  NCH: 128-byte pieces of a row (64 bf16 or 32 fp32 elements).
+template <bool WIDE, int PRE, int NB, int NCH>
+__global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
+  constexpr int AE = WIDE ? 4 : 2, CE = 128 / AE;   // elements of a piece
+  constexpr int ST = CE / 16;                       // 16-element steps of a piece
+  constexpr int V = WIDE ? 2 : 1;                   // 16-byte vectors per lane and step
+  constexpr int BN = NB * 32;
+  constexpr int KW = (NCH * CE + 63) / 64;          // 64-element pieces of a weight row
+  constexpr int W_BYTES = KW * BN * 128, KP = KW * 64;
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[W_BYTES + SW * 4096 + BN * 4 + (PRE == 1 ? KP * 6 : 0)];
+  static_assert(sizeof(smem) <= 160 * 1024, "LDS of a compute unit");
+  float* const bias_s = reinterpret_cast<float*>(smem + W_BYTES + SW * 4096);
+  float* const shift_s = bias_s + BN;
+  bf16_t* const scale_s = reinterpret_cast<bf16_t*>(shift_s + KP);
+
+  int p, bid;
+  if (!find_problem_at(a, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), p, bid)) return;
+  const Desc d = a.d[p];
+  const int batch = a.batch[p];
+  const int M = batch * d.Ho * d.Wo, T = (M + 31) >> 5;
+  const int slabs = (d.Cop + BN - 1) / BN, groups = (a.first_block[p + 1] - a.first_block[p]) / slabs;
+  const int n0 = bid % slabs * BN, grp = bid / slabs;
+  const int t0 = (int)((int64_t)T * grp / groups), t1 = (int)((int64_t)T * (grp + 1) / groups);   // this workgroup's blocks of 32 rows
+  const int tid = threadIdx.x, lane = tid & 63, r31 = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+      a.abase + d.x_off, 0, M > 0 ? (int)((((int64_t)M - 1) * d.xs + d.Cp) * AE) : 0, 0x00020000);
+  const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(a.wbase + d.w_off), 0, (int)((int64_t)d.Co * d.Kp * 2), 0x00020000);
+
+  u32x4 av[NCH][ST][V];   // a block of rows, requested one block ahead
+  int t = t0 + wave;
+  uint32_t row = (uint32_t)((t * 32 + r31) * d.xs * AE + half * 8 * AE);
+  auto request = [&](int c, uint32_t at) {
+#pragma unroll
+    for (int s = 0; s < ST; ++s) {
+      const uint32_t off = c * CE + s * 16 + half * 8 < d.Cp ? at + (uint32_t)((c * CE + s * 16) * AE) : OOB;
+#pragma unroll
+      for (int v = 0; v < V; ++v) av[c][s][v] = __builtin_amdgcn_raw_buffer_load_b128(xres, off + 16 * v, 0, 0);
+    }
+  };
+
+  // weights: 8 rows of 128 bytes per instruction, the 16-byte pieces of a row permuted at the source (piece ^ row % 8)
+  const int lrow = lane >> 3, piece = (lane & 7) ^ lrow;
+  for (int i = wave; i < KW * (BN / 8); i += SW) {
+    const int kc = i / (BN / 8), r = i % (BN / 8) * 8 + lrow;
+    const int k = kc * 64 + piece * 8;
+    load_lds<16>(wres, smem + i * 1024, k < d.Kp ? (uint32_t)((n0 + r) * d.Kp + k) * 2 : OOB);   // (rows past Co lie past the buffer's end)
+  }
+  for (int i = tid; i < BN; i += SW * 64) bias_s[i] = n0 + i < d.Cop ? reinterpret_cast<const float*>(a.wbase + d.b_off)[n0 + i] : 0.0f;
+  if constexpr (PRE == 1)
+    for (int i = tid; i < KP; i += SW * 64) {
+      scale_s[i] = i < d.Cp ? reinterpret_cast<const bf16_t*>(a.wbase + d.pw_off)[i] : (bf16_t)0;
+      shift_s[i] = i < d.Cp ? reinterpret_cast<const float*>(a.wbase + d.pb_off)[i] : 0.0f;
+    }
+  {
+    const uint32_t live = t < t1 ? row : OOB;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) request(c, live);
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+
+  const bool has_res = d.r_off != kNone, stream_out = (int64_t)M * d.Cop * AE > (int64_t)STREAM_OUT_BYTES;
+  const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(
+      a.abase + (has_res ? d.r_off : 0), 0, has_res ? (int)((int64_t)M * d.Cop * AE) : 0, 0x00020000);
+  const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(
+      a.abase + d.y_off, 0, M > 0 ? (int)((((int64_t)M - 1) * d.ys + d.Cop) * AE) : 0, 0x00020000);
+  const uint32_t next = (uint32_t)(SW * 32) * (uint32_t)d.xs * AE;
+  const int bsw = r31 & 7;
+  uint8_t* const patch = smem + W_BYTES + wave * 4096;
+  const Activation<false> act(d.act);
+  const bool hardswish = d.act == FI_ACT_HARDSWISH;
+  constexpr bool RESIDENT = !PRE && NCH * ST * NB * 4 <= 32;   // a weight fragment is 4 registers: few of them stay there for the life of the workgroup
+  int fresh = 0;
+  const Activation<false> pre_act(d.pre_act);
+  for (; t < t1; t += SW) {
+    if constexpr (!RESIDENT) asm volatile("" : "+v"(fresh));   // (zero: keeps the reads of weights, bias and scale in the loop, where there are registers for them)
+    f32x16 acc[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[j][e] = 0.0f;
+    row += next;
+    const uint32_t live = t + SW < t1 ? row : OOB;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+#pragma unroll
+      for (int s = 0; s < ST; ++s) {
+        const int k = c * CE + s * 16;   // (this lane: elements k + 8 half .. + 7)
+        bf16x8 hi, lo;
+        if constexpr (WIDE) {
+          u32x4 h, l;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float x0 = __uint_as_float(av[c][s][e >> 1][(2 * e) & 3]), x1 = __uint_as_float(av[c][s][e >> 1][(2 * e + 1) & 3]);
+            const uint32_t h0 = f2bf(x0), h1 = f2bf(x1);
+            h[e] = h0 | (h1 << 16);
+            l[e] = pack_bf16x2(x0 - __uint_as_float(h0 << 16), x1 - __uint_as_float(h1 << 16));
+          }
+          hi = __builtin_bit_cast(bf16x8, h);
+          lo = __builtin_bit_cast(bf16x8, l);
+        } else if constexpr (PRE == 1) {
+          const u32x4 sc = *reinterpret_cast<const u32x4*>(scale_s + k + 8 * half + fresh);
+          const float4 s0 = *reinterpret_cast<const float4*>(shift_s + k + 8 * half + fresh), s1 = *reinterpret_cast<const float4*>(shift_s + k + 8 * half + 4 + fresh);
+          const float sh[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+          float v[8];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const uint32_t xw = av[c][s][0][e];
+            v[2 * e] = __fadd_rn(__fmul_rn(__uint_as_float(xw << 16), __uint_as_float(sc[e] << 16)), sh[2 * e]);
+            v[2 * e + 1] = __fadd_rn(__fmul_rn(__uint_as_float(xw & 0xFFFF0000u), __uint_as_float(sc[e] & 0xFFFF0000u)), sh[2 * e + 1]);
+          }
+          float va[4] = {v[0], v[1], v[2], v[3]}, vb[4] = {v[4], v[5], v[6], v[7]};
+          pre_act.apply(va); pre_act.apply(vb);   // (identity, ReLU or ReLU6: the planner folds no other)
+          u32x4 h;
+#pragma unroll
+          for (int e = 0; e < 2; ++e) { h[e] = pack_bf16x2(va[2 * e], va[2 * e + 1]); h[2 + e] = pack_bf16x2(vb[2 * e], vb[2 * e + 1]); }
+          hi = __builtin_bit_cast(bf16x8, h);
+        } else {
+          hi = __builtin_bit_cast(bf16x8, av[c][s][0]);
+        }
+        const uint8_t* const W = smem + (k >> 6) * (BN * 128) + r31 * 128 + fresh + ((((k & 63) / 8 + half) ^ bsw) << 4);
+        bf16x8 bfr[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) bfr[j] = *reinterpret_cast<const bf16x8*>(W + j * 32 * 128);
+        if constexpr (WIDE)   // small terms first
+#pragma unroll
+          for (int j = 0; j < NB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], lo, acc[j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], hi, acc[j], 0, 0, 0);
+      }
+      request(c, live);   // the same piece of the next block
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // A lane holds, for pixel (lane & 31), runs of four consecutive channels: bias, residual, activation, the one rounding.
+    const int m = t * 32 + r31;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      float v[16];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int cl = j * 32 + 8 * g + 4 * half;
+        const float4 b = *reinterpret_cast<const float4*>(bias_s + cl + fresh);
+        v[4 * g] = acc[j][4 * g] + b.x; v[4 * g + 1] = acc[j][4 * g + 1] + b.y; v[4 * g + 2] = acc[j][4 * g + 2] + b.z; v[4 * g + 3] = acc[j][4 * g + 3] + b.w;
+      }
+      if (WIDE || has_res) {   // (fp32 rows: no residual adds +0.0, as on the tiles)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int c = n0 + j * 32 + 8 * g + 4 * half;
+          const uint32_t off = c < d.Cop ? (uint32_t)((m * d.Cop + c) * AE) : OOB;
+          if constexpr (WIDE) {
+            const u32x4 r = __builtin_amdgcn_raw_buffer_load_b128(rres, off, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * g + e] += __uint_as_float(r[e]);
+          } else {
+            const u32x2 r = __builtin_amdgcn_raw_buffer_load_b64(rres, off, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * g + e] += __uint_as_float((e & 1) ? r[e >> 1] & 0xFFFF0000u : r[e >> 1] << 16);
+          }
+        }
+      }
+      if (hardswish) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = act_hardswish(v[e]);
+      } else {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          float q[4] = {v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+          act.apply(q);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[4 * g + e] = q[e];
+        }
+      }
+      // Through a patch of the wave's own (32 rows of 128 bytes), so that whole cache lines leave.
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        if constexpr (WIDE) {
+          *reinterpret_cast<float4*>(patch + r31 * 128 + (((2 * g + half) ^ bsw) << 4)) = make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
+        } else {
+          const u32x2 pk = {pack_bf16x2(v[4 * g], v[4 * g + 1]), pack_bf16x2(v[4 * g + 2], v[4 * g + 3])};
+          *reinterpret_cast<u32x2*>(patch + r31 * 128 + ((((j & 1) * 4 + g) ^ bsw) << 4) + 8 * half) = pk;
+        }
+      }
+      if (!WIDE && (j & 1) == 0 && j + 1 < NB) continue;   // (bf16: two blocks of columns make a line)
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's own LDS writes precede its reads
+      const int c = n0 + (WIDE ? j * 32 + (lane & 7) * 4 : j / 2 * 64 + (lane & 7) * 8);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = i * 8 + lrow;
+        const u32x4 o = *reinterpret_cast<const u32x4*>(patch + r * 128 + (((lane & 7) ^ lrow) << 4));
+        const uint32_t off = c < d.Cop ? (uint32_t)(((t * 32 + r) * d.ys + c) * AE) : OOB;
+        if (stream_out) __builtin_amdgcn_raw_buffer_store_b128(o, yres, off, 0, 2);
+        else __builtin_amdgcn_raw_buffer_store_b128(o, yres, off, 0, 0);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+  }
+}
+
+template <bool WIDE, int PRE, int NB, int NCH>
+int go_stream(int blocks, const KArgs& a, hipStream_t s) {
+  if (blocks <= 0) return (int)hipSuccess;
+  hipLaunchKernelGGL((conv_stream_kernel<WIDE, PRE, NB, NCH>), dim3((unsigned)blocks), dim3(SW * 64), 0, s, a);
+  return (int)hipGetLastError();
+}
+
+}  // namespace
+
+// Whether a launch of pointwise convolutions streams, and with which blocks of columns and pieces of a row.  (The rule may look at the
+// launch: the bits are the tile kernel's.)  Rows enough to pay for the weights that every workgroup loads first: 512 blocks of 32 rows, from three pieces on
+// 256 per piece.  4x MobileNetV3-Large at batch 32 1912 us without this kernel, 1824 / 1815 / 1807 from 2048 / 1024 / 512 blocks on (28 x 28
+// layers of one to four pieces); 4x DenseNet-121 2972, 2855 / 2851 / 2873 (the 14 x 14 layers of four to six pieces lose).
+bool stream_fits(const Launch& L, const KArgs& a, int* nb, int* nch) {
+  const bool wide = L.adtype != FI_BF16;
+  const int es = wide ? 4 : 2, ce = 128 / es;
+  int64_t tiles = 0;
+  int cop = 0, pieces = 0;
+  const int pre = a.d[0].pre_kind;
+  if (pre == 2 || (wide && pre)) return false;
+  for (int i = 0; i < L.n; ++i) {
+    const Desc& t = a.d[i];
+    const int64_t m = (int64_t)a.batch[i] * t.Ho * t.Wo;
+    if (a.batch[i] < 0 || t.pre_kind != pre || (t.act > FI_ACT_RELU6 && t.act != FI_ACT_HARDSWISH) || (pre == 1 && t.pre_act > FI_ACT_RELU6) || t.k != 1 || t.kw != 1 || t.stride != 1 || t.pad != 0 || t.pad_w != 0 || t.gin > 0 || t.splits != 1 || t.ext || t.out_f32 ||
+        t.Cp % 8 || t.Co != t.Cop || t.Cop % 8 || t.ys % (16 / es) || t.xs % (16 / es) || t.Kp < t.Cp || t.Kp % 8 || (pre == 0 && t.xs != t.Cp) ||
+        m >= (1 << 24) || (m + 2 * SW * 32) * t.xs * es >= (1ll << 31) || (m + 32) * (t.ys > t.Cop ? t.ys : t.Cop) * es >= (1ll << 31) ||
+        ((int64_t)t.Co + 128) * t.Kp * 2 >= (1ll << 31))
+      return false;
+    tiles += (m + 31) / 32;
+    cop = cop > t.Cop ? cop : t.Cop;
+    pieces = pieces > (t.Cp + ce - 1) / ce ? pieces : (t.Cp + ce - 1) / ce;
+  }
+  if (tiles < 512 || tiles < 256 * pieces || pieces > 6 || cop > 128) return false;
+  *nb = cop <= 32 ? 1 : cop <= 64 ? 2 : 4;
+  *nch = pieces <= 4 ? pieces : 6;
+  return true;
+}
+
+int launch_stream(const Launch& L, const KArgs& args, int nb, int nch, void* stream) {
+  KArgs a = args;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  int64_t tiles = 0, blocks = 0;
+  for (int i = 0; i < L.n; ++i) tiles += ((int64_t)a.batch[i] * a.d[i].Ho * a.d[i].Wo + 31) / 32 * ((a.d[i].Cop + nb * 32 - 1) / (nb * 32));
+  for (int i = 0; i < L.n; ++i) {   // one workgroup per compute unit, shared out by the blocks of rows and columns
+    const int64_t rows = ((int64_t)a.batch[i] * a.d[i].Ho * a.d[i].Wo + 31) / 32, slabs = (a.d[i].Cop + nb * 32 - 1) / (nb * 32);
+    int64_t groups = (256 * rows + tiles - 1) / tiles;
+    if (groups > (rows + SW - 1) / SW) groups = (rows + SW - 1) / SW;
+    a.first_block[i] = (int32_t)blocks;
+    blocks += groups * slabs;
+  }
+  for (int i = L.n; i <= FI_MAX_GROUP; ++i) a.first_block[i] = (int32_t)blocks;
+  const int n = (int)blocks;
+  const bool wide = L.adtype != FI_BF16;
+  const int pre = a.d[0].pre_kind;
+#define FI_NCH(WIDE, PRE, NB)                                                                      \
+  if (wide == (WIDE) && pre == (PRE) && nb == (NB)) {                                              \
+    if (nch == 1) return go_stream<WIDE, PRE, NB, 1>(n, a, s);                                     \
+    if (nch == 2) return go_stream<WIDE, PRE, NB, 2>(n, a, s);                                     \
+    if (nch == 3) return go_stream<WIDE, PRE, NB, 3>(n, a, s);                                     \
+    if (nch == 4) return go_stream<WIDE, PRE, NB, 4>(n, a, s);                                     \
+    if (nch == 6) return go_stream<WIDE, PRE, NB, 6>(n, a, s);                                     \
+  }
+  FI_NCH(false, 0, 1) FI_NCH(false, 0, 2) FI_NCH(false, 0, 4)
+  FI_NCH(false, 1, 1) FI_NCH(false, 1, 2) FI_NCH(false, 1, 4)
+  FI_NCH(true, 0, 1) FI_NCH(true, 0, 2) FI_NCH(true, 0, 4)
+#undef FI_NCH
+  return (int)hipErrorInvalidValue;
+}
+
+}  // namespace fi

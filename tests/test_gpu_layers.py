@@ -239,6 +239,55 @@ def test_conv_patch_has_the_bits_of_the_tile_kernel(case):
     assert np.isfinite(_same_bits(m, few, many, small, "conv_patch " + tile)[2]).all()
 
 
+def _bits_and_parity(m, act_dtype, few, many, seed=71):
+    """The first images of a batch of `many` have the bits that a batch of `few` gives them, and meet the oracle."""
+    from tests import harness
+    m.shapes()
+    blob = gen.make_blob(m, seed, bias_std=0.1)
+    x = gen.make_input(seed + 1, many, m.in_c, m.in_h, m.in_w, "normal", m.dtype)
+    g = harness.GpuDag([(m, blob, act_dtype)], many)
+    try:
+        large, small = g.run(x)[0], g.run(x[:few])[0]
+    finally:
+        g.close()
+    assert np.isfinite(large).all() and np.array_equal(large[:few], small)
+    wide = act_dtype == "f32"
+    last = x[-1:]   # (the ragged end of the launch)
+    ref = harness.oracle_nhwc(m, blob, last, not wide)
+    assert harness.rel_l2(large[-1:], ref) <= (F32_TOL if wide else 2e-3)
+    assert harness.elem_excess(large[-1:], ref, harness.ELEM_C_F32 if wide else harness.ELEM_C_BF16) <= 1.0
+
+
+# rows of 61 x 53 pixels: 6 images are 607 blocks of 32 (the last of 6 rows), above the line of one or two pieces of 128 bytes; 16 images are 1617
+@pytest.mark.parametrize("cin, cout, act_dtype, many", [(8, 8, None, 6), (72, 24, None, 6), (64, 128, None, 6), (128, 40, None, 6), (328, 104, None, 16),
+                                                        (16, 64, "f32", 6), (24, 72, "f32", 6), (40, 8, "f32", 6), (184, 96, "f32", 16)])
+def test_pointwise_rows_that_stream(cin, cout, act_dtype, many):
+    """Many rows and a short reduction stream through waves of their own; one image (102 blocks) keeps the tile kernel: the same bits.
+    Partial pieces and blocks of columns, a residual, every activation the kernel has."""
+    m = zoo.Model("c", "bf16", 8, 61, 53)
+    e = m.add(zoo.CONV, -1, cin=8, cout=cin, k=1, stride=1, pad=0, act=zoo.RELU6)
+    a = m.add(zoo.CONV, e, cin=cin, cout=cout, k=1, stride=1, pad=0, act=zoo.HARDSWISH)
+    a = m.add(zoo.CONV, a, cin=cout, cout=cin if cin <= 128 else 16, k=1, stride=1, pad=0, act=zoo.RELU, residual=e if cin <= 128 else zoo.NO_RESIDUAL)
+    m.add(zoo.MAXPOOL, a, k=1, stride=1, pad=0)
+    _bits_and_parity(m, act_dtype, 1, many)
+
+
+@pytest.mark.parametrize("first, grow, act", [(64, 32, zoo.RELU), (40, 24, zoo.RELU6), (128, 72, zoo.NONE)])
+def test_dense_layers_that_stream(first, grow, act):
+    """Dense layers whose rows stream: an affine stage on the way in, the input a prefix of a concatenation's tensor."""
+    m = zoo.Model("c", "bf16", 8, 61, 53)
+    t = m.add(zoo.CONV, -1, cin=8, cout=first, k=1, stride=1, pad=0, act=zoo.RELU)
+    c = first
+    for _ in range(2):
+        a = m.add(zoo.DWCONV, t, cin=c, cout=c, k=1, stride=1, pad=0, act=act)
+        a = m.add(zoo.CONV, a, cin=c, cout=128, k=1, stride=1, pad=0, act=zoo.RELU)
+        a = m.add(zoo.CONV, a, cin=128, cout=grow, k=1, stride=1, pad=0, act=zoo.NONE)
+        t = m.add(zoo.CONCAT, t, residual=a)
+        c += grow
+    m.add(zoo.MAXPOOL, t, k=1, stride=1, pad=0)
+    _bits_and_parity(m, None, 1, 16)
+
+
 @pytest.mark.parametrize("features, batch", [(1000, 4), (1001, 33), (7, 1)])
 def test_fc_f32_shared_reduction(features, batch):
     """fp32 fully connected layers over a flattened map (a reduction of 3 x 2 x 50 elements: not a whole step)."""
