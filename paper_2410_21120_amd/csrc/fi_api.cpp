@@ -775,13 +775,26 @@ static void widen_shared_reductions(fi_dag* g) {
 // 32 x 32 tile.  Geometric means: direct alone 37.5 us, sharing alone 21.2, by this rule 16.55, the better of the two 16.45; at the
 // ends 1 -> 1 channels, 3x3, 1024 x 1024 20 us direct and 686 shared, 512 -> 1000 features 68 and 9.5.  Past 256 elements the direct
 // kernel's strided reads of a row are slower than that (32 -> 1, 5x5, 8 x 256 x 256: 2454 and 520 us).
-static bool direct_is_shorter(int64_t rows, int64_t Co, int64_t K, bool scalar, int tile) {
-  if (K > 256) return false;
+struct F32Cost { double direct, shared; };
+static F32Cost f32_cost(int64_t rows, int64_t Co, int64_t K, bool scalar, int tile) {
   const int64_t side = kwave_side(tile), waves = tile == KW_32x8 ? 8 : 4, steps = (K + 31) / 32;
   const double tiles = (double)((rows + side - 1) / side) * (double)((Co + side - 1) / side) * (side == 64 ? 1.0 : 0.25);
-  const double shared = (scalar ? 3.0 : 1.0) + tiles * (double)((steps + waves - 1) / waves) * (scalar ? 0.050 : 0.014);
   const double outputs = (double)rows * (double)Co * 1e-6;
-  return 6.0 * outputs + 0.7 * outputs * (double)K + 0.13 * (double)K < shared;
+  return {6.0 * outputs + 0.7 * outputs * (double)K + 0.13 * (double)K,
+          (scalar ? 3.0 : 1.0) + tiles * (double)((steps + waves - 1) / waves) * (scalar ? 0.050 : 0.014)};
+}
+static bool direct_is_shorter(const F32Cost& c, int64_t K) { return K <= 256 && c.direct < c.shared; }
+
+// fp32 convolutions of one to three channels: the kernel that holds patch and weights in LDS, where it is ahead of both by a margin
+// (the estimate of the sharing kernel is high by up to a quarter).  0.4 us per tap and 27 ns per workgroup of 16 x 16 pixels x 32 channels,
+// fit on 72 layers (3 channels to 16, 32 and 64, 3x3 and 7x7, stride 1 and 2, sides 32 to 224, batch 1 and 4).  At the ends, other
+// kernel -> this one (us): 3 -> 64, 7x7 stride 2, 224 x 224, batch 4 67 -> 40, 160 x 160 37.5 -> 34.3, 128 x 128 23 -> 32; 3x3 stride 2,
+// 224 x 224, batch 4 53 -> 24, 128 x 128 18.2 -> 17.2, 128 x 128, batch 1 10.7 -> 14.5.
+static bool takes_rgb(const Node& nd, int64_t batch, int64_t K, const F32Cost& c) {
+  if (nd.op != FI_CONV2D || nd.Cp > 3 || nd.C != nd.Cp || rgb_lds(nd.k, nd.kw, nd.stride, nd.Cp) > KW_RGB_LDS) return false;
+  const double groups = (double)batch * (double)((nd.Ho + 15) / 16) * (double)((nd.Wo + 15) / 16) * (double)((nd.Co + 31) / 32);
+  const double us = 3.5 + 0.4 * (double)(nd.k * nd.kw) + 0.027 * groups;
+  return us < 0.75 * c.shared && (K > 256 || us < 0.75 * c.direct);
 }
 
 // Planner pass: kernel family, tile and reduction split of every node.
@@ -852,9 +865,11 @@ static fi_status choose_kernels(fi_dag* g) {
                              : kwave_fits(B, nd.H, nd.W, cp, nd.Ho, nd.Wo, nd.Co, (int64_t)nd.k * nd.kw, nd.Kp, 4)) {
             const int tile = ((M + 63) / 64) * ((nd.Co + 63) / 64) >= 192 ? KW_64x4 : KW_32x8;
             const int64_t K = nd.op == FI_FC ? (int64_t)nd.H * nd.W * nd.C : (int64_t)nd.k * nd.kw * nd.C;
-            if (!direct_is_shorter(M, nd.Co, K, cp % 4 != 0, tile)) {
+            const F32Cost cost = f32_cost(M, nd.Co, K, cp % 4 != 0, tile);
+            const bool rgb = takes_rgb(nd, B, K, cost);
+            if (rgb || !direct_is_shorter(cost, K)) {
               nd.kind = K_CONV_KWAVE;
-              nd.tile = tile | (cp % 4 ? KW_SCALAR : 0);
+              nd.tile = tile | (cp % 4 ? KW_SCALAR : 0) | (rgb ? KW_RGB : 0);
             }
           }
         }
@@ -1208,7 +1223,7 @@ static void fill_descriptors(fi_dag* g) {
       if (nd.out_dtype == FI_F32 && adt != FI_F32 && !nd.is_output) d.Cop = nd.Cop;  // fp32 rows keep the padded stride
       d.tiles_n = L.kind == K_CONV_MFMA ? (nd.Co + tile_bn(L.tile) - 1) / tile_bn(L.tile) : 0;
       if (L.kind == K_CONV_PATCH) d.tiles_n = (nd.Co + patch_bn(L.tile) - 1) / patch_bn(L.tile);
-      if (L.kind == K_CONV_KWAVE) { const int side = kwave_side(L.tile & ~KW_SCALAR); d.tiles_n = (nd.Co + side - 1) / side; }
+      if (L.kind == K_CONV_KWAVE) { const int side = kwave_side(L.tile); d.tiles_n = (nd.Co + side - 1) / side; }
       d.splits = std::max(1, nd.splits);
       if (walks_groups(nd, adt) || (nd.kind == K_CONV_PATCH && nd.groups > 1)) { d.gin = nd.C / nd.groups; d.gout = nd.Co / nd.groups; }
       {
@@ -1370,7 +1385,7 @@ fi_status fi_launch(const fi_dag* g, int32_t i, fi_launch_info* o) {
   if (!g || !o || i < 0 || i >= (int32_t)g->launches.size()) { set_error("bad launch index"); return FI_EINVAL; }
   const Launch& L = g->launches[(size_t)i];
   std::memset(o, 0, sizeof(*o));
-  o->lane = L.lane; o->tile = L.tile;
+  o->lane = L.lane; o->tile = L.kind == K_CONV_KWAVE ? L.tile & ~KW_RGB : L.tile;
   o->level = L.level; o->kind = L.kind; o->n_problems = L.n;
   o->first_node = (L.nodes.empty() || L.kind == K_STAGE) ? -1 : L.nodes[0];
   o->macs_per_image = L.macs; o->bytes_per_image = L.act_bytes; o->weight_bytes = L.weight_bytes;

@@ -58,9 +58,14 @@ FI_HD inline int tile_bn(int t) { return (t == T_128x128 || t == T_256x128 || t 
 
 // Tiles of the K_CONV_KWAVE kernels: side of the square tile x waves that share its reduction (the bits depend on the waves, not
 // on the side; fp32 takes the first two, bf16 the last two).  KW_SCALAR is added for
-// fp32 tensors whose channel stride four does not divide.
-enum KwaveTile : int32_t { KW_64x4 = 0, KW_32x8 = 1, KW_64x8 = 2, KW_NTILES, KW_SCALAR = 8 };
-FI_HD inline int kwave_side(int t) { return t == KW_32x8 ? 32 : 64; }
+// fp32 tensors whose channel stride four does not divide, KW_RGB for those of them with one to three channels whose weights and
+// input patch fit LDS: a kernel of its own, which has no tile choice (the rule looks at the node's own shape: the sums are ordered differently).
+enum KwaveTile : int32_t { KW_64x4 = 0, KW_32x8 = 1, KW_64x8 = 2, KW_NTILES, KW_SCALAR = 8, KW_RGB = 16 };
+constexpr int64_t KW_RGB_LDS = 64 << 10;
+inline int64_t rgb_lds(int64_t k, int64_t kw, int64_t stride, int64_t C) {   // bytes: 32 outputs' weights, the patch under 16 x 16 pixels
+  return 4 * C * (k * kw * 32 + (15 * stride + k) * (15 * stride + kw));
+}
+FI_HD inline int kwave_side(int t) { return (t & ~(KW_SCALAR | KW_RGB)) == KW_32x8 ? 32 : 64; }
 // Tiles of the K_CONV_PATCH kernel: rows x columns; DIAG: groups of at most 32 channels, only the 32 x 32 blocks of the
 // weights on the diagonal are multiplied.  A tile's patch holds rows + 2 W + 2 pixels of 64 channels.
 enum PatchTile : int32_t { PT_256x32 = 0, PT_256x64 = 1, PT_256x64_DIAG = 2, PT_512x128 = 3, PT_512x64_DIAG = 4, PT_NTILES };

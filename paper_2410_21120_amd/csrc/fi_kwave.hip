@@ -31,6 +31,38 @@
 
 namespace fi {
 
+// Finishes four consecutive channels [o, o + 4) of an fp32 output pixel m from their sums.
+__device__ __forceinline__ void finish_f32(const KArgs& a, const Desc& d, int p, int m, int o, float4 sum) {
+  if (__builtin_expect(__builtin_isnan((sum.x + sum.y) + (sum.z + sum.w)) && (d.pad | d.pad_w) != 0, 0)) {
+    // A tap outside the image reads zero here, and zero times a weight that is not finite is no zero: such a sum is
+    // taken again over the taps inside the image only.
+    int again_p = p;
+    asm volatile("" : "+s"(again_p));   // (the descriptor is read again: its fields take no registers before)
+    const Desc& e = a.d[again_p];
+    const int g = m / e.Wo, n = g / e.Ho;
+#pragma unroll 1
+    for (int t = 0; t < 4; ++t) {
+      const float v = t == 0 ? sum.x : t == 1 ? sum.y : t == 2 ? sum.z : sum.w;
+      if (!__builtin_isnan(v) || o + t >= e.Co) continue;
+      const float again = conv_element<true>(a, e, n, g - n * e.Ho, m - g * e.Wo, o + t);
+      sum.x = t == 0 ? again : sum.x; sum.y = t == 1 ? again : sum.y; sum.z = t == 2 ? again : sum.z; sum.w = t == 3 ? again : sum.w;
+    }
+  }
+  if (d.Cop % 4 == 0) {
+    finish_row4<float>(a, d, p, m, o, sum);
+    return;
+  }
+  // fp32 rows of any channel count: no vector of four is aligned
+  const float s[4] = {sum.x, sum.y, sum.z, sum.w};
+  for (int t = 0; t < 4 && o + t < d.Co; ++t) {
+    float v = s[t] + reinterpret_cast<const float*>(a.wbase + d.b_off)[o + t];
+    if (d.r_off != kNone) v += reinterpret_cast<const float*>(a.abase + d.r_off)[(int64_t)m * d.Cop + o + t];
+    v = activate(v, d.act);
+    if (d.ext) static_cast<float*>(a.ext_out[p])[(int64_t)m * d.Co + o + t] = v;
+    else reinterpret_cast<float*>(a.abase + d.y_off)[(int64_t)m * d.Cop + o + t] = v;
+  }
+}
+
 // F32: fp32 weights and activations.  SCALAR: a channel stride that four does not divide (an RGB input): rows are not
 // 16-byte aligned and a piece may span two filter taps, so every element is fetched by itself (4-byte loads, no swizzle).
 template <bool F32, bool SCALAR, int MI, int NI, int NW>
@@ -177,34 +209,143 @@ __global__ void __launch_bounds__(NW * 64) conv_kwave_kernel(KArgs a) {
         const float4 v = *reinterpret_cast<const float4*>(&part[(w * 32 + row) * EPS + c]);
         sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
       }
-      if (F32 && __builtin_expect(__builtin_isnan((sum.x + sum.y) + (sum.z + sum.w)) && (d.pad | d.pad_w) != 0, 0)) {
-        // A tap outside the image reads zero here, and zero times a weight that is not finite is no zero: such a sum is
-        // taken again over the taps inside the image only.
-        int again_p = p;
-        asm volatile("" : "+s"(again_p));   // (the descriptor is read again: its fields take no registers before)
-        const Desc& e = a.d[again_p];
-        const int g = m / e.Wo, n = g / e.Ho;
-#pragma unroll 1
-        for (int t = 0; t < 4; ++t) {
-          const float v = t == 0 ? sum.x : t == 1 ? sum.y : t == 2 ? sum.z : sum.w;
-          if (!__builtin_isnan(v) || o + t >= e.Co) continue;
-          const float again = conv_element<true>(a, e, n, g - n * e.Ho, m - g * e.Wo, o + t);
-          sum.x = t == 0 ? again : sum.x; sum.y = t == 1 ? again : sum.y; sum.z = t == 2 ? again : sum.z; sum.w = t == 3 ? again : sum.w;
-        }
+      if constexpr (F32) finish_f32(a, d, p, m, o, sum);
+      else finish_row4<TA>(a, d, p, m, o, sum);
+    }
+  }
+}
+
+// fp32 convolutions of one to three channels (the first layer of an unconverted model): a thread owns four pixels x eight output
+// channels, in vector arithmetic.  The kernel above fetches such rows element by element (a channel stride that four does not divide), 64
+// loads of 4 bytes per lane and step: 112 x 112 x 64, 7x7 stride 2, batch 4 67 us at 14 TFLOP/s.  Here a workgroup owns 16 x 16 pixels x 32
+// channels, with the input patch under them and the weights, [tap][channel][output], in LDS: one round of loads, then a
+// wave reads an input value for 8 products and the eight weights as two broadcasts for 32: 37 us for that layer.  Bound: the LDS reads and
+// their latency, 0.4 us per tap.  (Without the patch, a tap's pixels requested one tap ahead, every tap waits for memory: 57 us.)  A filter row's products are
+// summed first, then the rows: short serial sums, as close to the exact value as the sums shared among waves above.
+template <int C>
+__global__ void __launch_bounds__(256) conv_rgb_kernel(KArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];   // weights [k * kw * C][32], patch [PH][PW * C]
+  int p, bid;
+  if (!find_problem_at(a, (int)blockIdx.x, p, bid)) return;
+  const Desc d = a.d[p];
+  const int slabs = (d.Co + 31) / 32, bw = (d.Wo + 15) / 16, bh = (d.Ho + 15) / 16;
+  const int n0 = bid % slabs * 32;
+  bid /= slabs;
+  const int q0 = bid % bw * 16, p0 = bid / bw % bh * 16, n = bid / bw / bh;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int K = d.k * d.kw * C, pitch = (15 * d.stride + d.kw) * C, rows = 15 * d.stride + d.k;
+  float* const patch = lds + K * 32;
+  {
+    // eight loads of a thread at a time, the first of each kind requested together: one memory latency, not one per element
+    const float* const w = reinterpret_cast<const float*>(a.wbase + d.w_off);
+    const int ih0 = p0 * d.stride - d.pad, iw0 = q0 * d.stride - d.pad_w;
+    const float* const x = reinterpret_cast<const float*>(a.abase + d.x_off) + (int64_t)n * d.H * d.W * C;
+    const float inv_pitch = 1.0f / (float)pitch, inv_k = 1.0f / (float)K;
+    const int lo = -iw0 * C, hi = (d.W - iw0) * C;   // the elements of a patch row that are inside the image
+    const int nw = K * 32, nx = rows * pitch;
+    for (int u0 = tid; u0 < nw || u0 < nx; u0 += 8 * 256) {
+      float wv[8], xv[8];
+      int to[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int u = u0 + t * 256, o = fast_div(u, K, inv_k), k = u - o * K;
+        to[t] = k * 32 + o;
+        wv[t] = u < nw && n0 + o < d.Co ? w[(int64_t)(n0 + o) * d.Kp + k] : 0.0f;
       }
-      if (!F32 || d.Cop % 4 == 0) {
-        finish_row4<TA>(a, d, p, m, o, sum);
-      } else {   // fp32 rows of any channel count: no vector of four is aligned
-        const float s[4] = {sum.x, sum.y, sum.z, sum.w};
-        for (int t = 0; t < 4 && o + t < d.Co; ++t) {
-          float v = s[t] + reinterpret_cast<const float*>(a.wbase + d.b_off)[o + t];
-          if (d.r_off != kNone) v += reinterpret_cast<const float*>(a.abase + d.r_off)[(int64_t)m * d.Cop + o + t];
-          v = activate(v, d.act);
-          if (d.ext) static_cast<float*>(a.ext_out[p])[(int64_t)m * d.Co + o + t] = v;
-          else reinterpret_cast<float*>(a.abase + d.y_off)[(int64_t)m * d.Cop + o + t] = v;
-        }
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int u = u0 + t * 256, r = fast_div(u, pitch, inv_pitch), c = u - r * pitch;
+        const bool ok = u < nx && (unsigned)(ih0 + r) < (unsigned)d.H && c >= lo && c < hi;
+        xv[t] = ok ? x[((int64_t)(ih0 + r) * d.W + iw0) * C + c] : 0.0f;
+      }
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int u = u0 + t * 256;
+        if (u < nw) lds[to[t]] = wv[t];
+        if (u < nx) patch[u] = xv[t];
       }
     }
+  }
+  __syncthreads();
+  const int g0 = wave * 8;
+  if (n0 + g0 >= d.Cop) return;
+  // pixels: column lane & 15, rows (lane >> 4) + 4 i
+  const float* xp[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) xp[i] = patch + ((lane >> 4) + 4 * i) * d.stride * pitch + (lane & 15) * d.stride * C;
+  float acc[4][8], row[4][8];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int o = 0; o < 8; ++o) acc[i][o] = 0.0f;
+  const float* wt = lds + g0;
+  for (int r = 0; r < d.k; ++r) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int o = 0; o < 8; ++o) row[i][o] = 0.0f;
+#pragma unroll 3
+    for (int s = 0; s < d.kw * C; s += C) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const float4 w0 = *reinterpret_cast<const float4*>(wt + c * 32), w1 = *reinterpret_cast<const float4*>(wt + c * 32 + 4);
+        const float wv[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float v = xp[i][s + c];
+#pragma unroll
+          for (int o = 0; o < 8; ++o) row[i][o] = __builtin_fmaf(v, wv[o], row[i][o]);
+        }
+      }
+      wt += C * 32;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      xp[i] += pitch;
+#pragma unroll
+      for (int o = 0; o < 8; ++o) acc[i][o] += row[i][o];
+    }
+  }
+  const int q = q0 + (lane & 15), o = n0 + g0;
+  // The common case is finished from registers; an element in doubt (NaN beside padding), a residual, the caller's buffer or rows of any
+  // channel count take the general way.
+  bool plain = d.r_off == kNone && !d.ext && d.Cop % 8 == 0;
+  float4 b0 = make_float4(0, 0, 0, 0), b1 = b0;
+  if (plain) {
+    b0 = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(a.wbase + d.b_off) + o);
+    b1 = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(a.wbase + d.b_off) + o + 4);
+    float sum = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int t = 0; t < 8; ++t) sum += acc[i][t];
+    plain = !__builtin_isnan(sum);
+  }
+  if (plain) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float bias[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+#pragma unroll
+      for (int t = 0; t < 8; ++t) acc[i][t] += bias[t];
+      activate_n<8>(acc[i], d.act);
+      const int pp = p0 + (lane >> 4) + 4 * i;
+      if (pp < d.Ho && q < d.Wo) {
+        float* const y = reinterpret_cast<float*>(a.abase + d.y_off) + ((int64_t)(n * d.Ho + pp) * d.Wo + q) * d.Cop + o;
+        *reinterpret_cast<float4*>(y) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+        *reinterpret_cast<float4*>(y + 4) = make_float4(acc[i][4], acc[i][5], acc[i][6], acc[i][7]);
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int pp = p0 + (lane >> 4) + 4 * i;
+    if (pp >= d.Ho || q >= d.Wo) continue;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (o + 4 * h < d.Cop)
+        finish_f32(a, d, p, (n * d.Ho + pp) * d.Wo + q, o + 4 * h, make_float4(acc[i][4 * h], acc[i][4 * h + 1], acc[i][4 * h + 2], acc[i][4 * h + 3]));
   }
 }
 
@@ -219,11 +360,13 @@ int launch_kwave(const Launch& L, const KArgs& args, void* stream, const std::ve
   const bool f32 = L.wdtype == FI_F32;
   if (L.n < 1 || L.n > FI_MAX_GROUP || (f32 ? L.adtype != FI_F32 : L.adtype != FI_BF16)) return (int)hipErrorInvalidValue;
   const bool scalar = (L.tile & KW_SCALAR) != 0;
-  const int tile = L.tile & ~KW_SCALAR;
-  if (tile >= KW_NTILES || (scalar && !f32)) return (int)hipErrorInvalidValue;
+  const bool rgb = (L.tile & KW_RGB) != 0;
+  const int tile = L.tile & ~(KW_SCALAR | KW_RGB);
+  if (tile >= KW_NTILES || (scalar && !f32) || (rgb && !scalar)) return (int)hipErrorInvalidValue;
   const int side = kwave_side(tile), es = f32 ? 4 : 2;
   KArgs a = args;
   int64_t blocks = 0;
+  int lds = 0;
   for (int i = 0; i < L.n; ++i) {
     const Desc& t = hd[(size_t)(L.first_desc + i)];
     a.d[i] = t;
@@ -234,12 +377,26 @@ int launch_kwave(const Launch& L, const KArgs& args, void* stream, const std::ve
         !kwave_fits(b, t.H, t.W, t.Cp, t.Ho, t.Wo, t.Co, t.k * t.kw, t.Kp, es))
       return (int)hipErrorInvalidValue;
     a.first_block[i] = (int32_t)blocks;
-    blocks += ((int64_t)b * t.Ho * t.Wo + side - 1) / side * t.tiles_n;
+    if (rgb) {   // 16 x 16 pixels x 32 channels
+      const int64_t bytes = rgb_lds(t.k, t.kw, t.stride, t.Cp);
+      if (t.Cp != a.d[0].Cp || t.Cp > 3 || t.C != t.Cp || bytes > KW_RGB_LDS) return (int)hipErrorInvalidValue;
+      lds = bytes > lds ? (int)bytes : lds;
+      blocks += (int64_t)b * ((t.Ho + 15) / 16) * ((t.Wo + 15) / 16) * ((t.Co + 31) / 32);
+    } else {
+      blocks += ((int64_t)b * t.Ho * t.Wo + side - 1) / side * t.tiles_n;
+    }
     if (blocks > 0x7FFFFFFF) return (int)hipErrorInvalidConfiguration;
   }
   for (int i = L.n; i <= FI_MAX_GROUP; ++i) a.first_block[i] = (int32_t)blocks;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int nb = (int)blocks;
+  if (rgb) {
+    if (nb <= 0) return (int)hipSuccess;
+    if (a.d[0].Cp == 1) hipLaunchKernelGGL(conv_rgb_kernel<1>, dim3((unsigned)nb), dim3(256), lds, s, a);
+    else if (a.d[0].Cp == 2) hipLaunchKernelGGL(conv_rgb_kernel<2>, dim3((unsigned)nb), dim3(256), lds, s, a);
+    else hipLaunchKernelGGL(conv_rgb_kernel<3>, dim3((unsigned)nb), dim3(256), lds, s, a);
+    return (int)hipGetLastError();
+  }
 #define FI_KWAVE_CASE(F32, SCALAR, T, MI, NW) \
   if (f32 == (F32) && scalar == (SCALAR) && tile == (T)) return go_kwave(conv_kwave_kernel<F32, SCALAR, MI, MI, NW>, nb, NW, a, s);
   FI_KWAVE_CASE(true, false, KW_64x4, 2, 4)

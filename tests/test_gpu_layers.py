@@ -87,6 +87,18 @@ def test_conv_f32_shared_reduction(case):
     _run_case(m, 900 + cin + cout, b, tol=2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23, kernels=[("conv_kwave " + tile, 2)])
 
 
+# (with 16 x 16 pixels x 32 channels a workgroup: ragged pixel and channel blocks, channel counts that 4 and 8 do not divide, strides, a
+# patch wider than the image's padding, one and two input channels)
+@pytest.mark.parametrize("case", [(3, 64, 3, 1, 1, 101, 97, 4), (3, 70, 7, 2, 3, 229, 221, 4), (1, 36, 5, 2, 2, 263, 255, 4), (2, 39, 3, 2, 0, 250, 203, 8)])
+def test_conv_f32_patch_of_few_channels(case):
+    """fp32 convolutions of one to three channels over an input patch in LDS, with a residual; the bound of the shared reduction."""
+    cin, cout, k, s, p, h, w, b = case
+    m = zoo.Model("c", "f32", cin, h, w)
+    a = m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.NONE)
+    m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.HARDSWISH, residual=a)
+    _run_case(m, 940 + cin + cout, b, tol=2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23)
+
+
 @pytest.mark.parametrize("case", [(64, 40, 3, 1, 1, 61, 57, 4, "64x64x4"), (3, 64, 7, 2, 3, 161, 157, 4, "64x64x4 scalar"),
                                   (5, 33, 3, 1, 1, 9, 11, 1, "32x32x8 scalar"), (36, 31, 5, 2, 2, 9, 11, 1, "32x32x8")])
 def test_conv_f32_weights_that_are_not_finite(case):
