@@ -57,9 +57,11 @@ __global__ void __launch_bounds__(patch_bm(TILE)) conv_patch_kernel(KArgs a) {
       const_cast<uint8_t*>(a.wbase + d.w_off), 0, (int)((int64_t)d.Co * d.Kp * 2), 0x00020000);
 
   // A load instruction brings 8 rows of 128 bytes; lane l's 16 bytes land at l * 16, so the pieces of a row are permuted
-  // at the source (piece ^ row % 8), which spreads the operand reads over the banks (0.47 to 0.49 conflict cycles per active LDS cycle are left:
-  // VGG-16 at batch 64, DenseNet-121; waves wait 36 to 47 % of their cycles).
-  const int lrow = lane >> 3, piece = (lane & 7) ^ lrow;
+  // at the source (piece ^ row / 2 % 8): sixteen neighbouring rows, which an operand read takes at once, lie in sixteen different
+  // places of 16 bytes, all banks.  (With piece ^ row % 8, eight places: 0.47 to 0.49 conflict cycles per active LDS cycle on VGG-16 at batch 64 and
+  // DenseNet-121; now 0.03 to 0.14 and half the active cycles, DenseNet's 56 x 56 layers 58.5 -> 55.9 us, the matrix-bound ones unchanged: waves wait
+  // 34 to 37 % of their cycles.)
+  const int lrow = lane >> 3, piece = (lane & 7) ^ ((4 * wave + (lrow >> 1)) & 7);   // (a wave's loads are an even number of eight rows apart)
   const int c_lo = d.gin > 0 ? n0 : 0;         // a grouped convolution's columns read the channels of the same index
   const int nchunks = d.gin > 0 ? 1 : Cp >> 6;
   const int T = nchunks * 9;
@@ -146,10 +148,10 @@ __global__ void __launch_bounds__(patch_bm(TILE)) conv_patch_kernel(KArgs a) {
       const int px = wave * 64 + i * 32 + r31 + kr * W + ks;
       const bool ok = ((okr[i] >> kr) & (okc[i] >> ks) & 1) != 0;
       at[i] = smem + (ok ? px : PX - 1) * 128;
-      sw[i] = ((px & 7) ^ half) << 4;
+      sw[i] = (((px >> 1) & 7) ^ half) << 4;
     }
     const uint8_t* const Bs = ring + stage * STAGE_B + r31 * 128;
-    const int bsw = ((r31 & 7) ^ half) << 4;
+    const int bsw = (((r31 >> 1) & 7) ^ half) << 4;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       bf16x8 af[MI], bfr[NI];

@@ -69,11 +69,12 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
     }
   };
 
-  // weights: 8 rows of 128 bytes per instruction, the 16-byte pieces of a row permuted at the source (piece ^ row % 8)
-  const int lrow = lane >> 3, piece = (lane & 7) ^ lrow;
+  // weights: 8 rows of 128 bytes per instruction, the 16-byte pieces of a row permuted at the source (piece ^ row / 2 % 8: sixteen rows read from
+  // sixteen places of 16 bytes, all banks)
+  const int lrow = lane >> 3;
   for (int i = wave; i < KW * (BN / 8); i += SW) {
     const int kc = i / (BN / 8), r = i % (BN / 8) * 8 + lrow;
-    const int k = kc * 64 + piece * 8;
+    const int k = kc * 64 + ((lane & 7) ^ ((r >> 1) & 7)) * 8;
     load_lds<16>(wres, smem + i * 1024, k < d.Kp ? (uint32_t)((n0 + r) * d.Kp + k) * 2 : OOB);   // (rows past Co lie past the buffer's end)
   }
   for (int i = tid; i < BN; i += SW * 64) bias_s[i] = n0 + i < d.Cop ? reinterpret_cast<const float*>(a.wbase + d.b_off)[n0 + i] : 0.0f;
@@ -96,7 +97,7 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
   const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(
       a.abase + d.y_off, 0, M > 0 ? (int)((((int64_t)M - 1) * d.ys + d.Cop) * AE) : 0, 0x00020000);
   const uint32_t next = (uint32_t)(SW * 32) * (uint32_t)d.xs * AE;
-  const int bsw = r31 & 7;
+  const int bsw = (r31 >> 1) & 7;
   uint8_t* const patch = smem + W_BYTES + wave * 4096;
   const Activation<false> act(d.act);
   const bool hardswish = d.act == FI_ACT_HARDSWISH;
@@ -217,7 +218,7 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = i * 8 + lrow;
-        const u32x4 o = *reinterpret_cast<const u32x4*>(patch + r * 128 + (((lane & 7) ^ lrow) << 4));
+        const u32x4 o = *reinterpret_cast<const u32x4*>(patch + r * 128 + (((lane & 7) ^ ((r >> 1) & 7)) << 4));
         const uint32_t off = c < d.Cop ? (uint32_t)(((t * 32 + r) * d.ys + c) * AE) : OOB;
         if (stream_out) __builtin_amdgcn_raw_buffer_store_b128(o, yres, off, 0, 2);
         else __builtin_amdgcn_raw_buffer_store_b128(o, yres, off, 0, 0);
