@@ -349,7 +349,7 @@ def sources_sha256():
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2410_21120_amd", "csrc")
-    for f in ("fi_internal.h", "fi_device.h", "fi_plan.cpp", "fi_api.cpp", "fi_kernels.hip", "fi_chain.hip", "fi_stem.hip", "fi_kwave.hip", "fi_patch.hip", "fi_stream.hip"):
+    for f in ("fi_internal.h", "fi_device.h", "fi_plan.cpp", "fi_api.cpp", "fi_kernels.hip", "fi_chain.hip", "fi_stem.hip", "fi_kwave.hip", "fi_patch.hip", "fi_stream.hip", "fi_pool.hip"):
         with open(os.path.join(csrc, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

@@ -41,6 +41,8 @@ enum Kind : int32_t {
                       // set: the pool node carries the launch); tile bits 1.. = which convolution
   K_CONV_KWAVE = 15,  // implicit GEMM whose waves share the reduction of one tile (fp32 models; bf16 problems of few tiles and a long reduction)
   K_CONV_PATCH = 16,  // 3x3 stride-1 convolution whose nine taps are read from one input patch in LDS
+  K_CONV_POOL = 17,   // 3x3 stride-1 convolution of 64 to 64 channels on wide images and the 2x2 stride-2 max-pool that alone reads it (the
+                      // pool node carries the launch)
   K_NKINDS
 };
 
@@ -219,6 +221,9 @@ int launch_stream(const Launch& L, const KArgs& a, int nb, int nch, void* stream
 
 // Implemented in fi_patch.hip: a K_CONV_PATCH launch.  Returns a hipError_t as int.
 int launch_patch(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);
+
+// Implemented in fi_pool.hip: a K_CONV_POOL launch.  Returns a hipError_t as int.
+int launch_pool(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);
 
 // Implemented in fi_stem.hip: a K_STEM launch, and the workgroups one of its problems takes.  Returns a hipError_t as int.
 int launch_stem(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);

@@ -1700,6 +1700,7 @@ int static_scratch(void** ptr, uint64_t* bytes) {
 int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::vector<Desc>& hd) {
   if (L.kind == K_CHAIN) return launch_chain(L, args, stream, hd);
   if (L.kind == K_STEM) return launch_stem(L, args, stream, hd);
+  if (L.kind == K_CONV_POOL) return launch_pool(L, args, stream, hd);
   if (L.kind == K_CONV_PATCH) return launch_patch(L, args, stream, hd);
   if (L.kind == K_CONV_KWAVE) return launch_kwave(L, args, stream, hd);
   hipStream_t s = static_cast<hipStream_t>(stream);

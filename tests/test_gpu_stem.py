@@ -207,3 +207,35 @@ def test_stem_launch_full_size_batch32_equals_general_kernels():
     assert "conv_stem_pool" in names
     for a, b in zip(fast, plain):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("h,w,act,batch,members", [(224, 224, zoo.RELU, 2, 1), (97, 131, zoo.RELU, 3, 2), (33, 92, zoo.NONE, 5, 1), (2, 255, zoo.RELU6, 1, 3), (161, 100, zoo.NONE, 9, 2)])
+def test_wide_convolution_and_its_pool_equal_separate_launches_bitwise(h, w, act, batch, members):
+    """A 3x3 convolution of 64 to 64 channels on an image wider than the patch kernel's, with its 2x2 pool in one launch: ragged blocks of
+    16 x 16 pixels, odd sizes (a last row and column that no window reads), negative maxima, values that are not finite, batches below the handle's."""
+    from tests import harness
+    models = []
+    for _ in range(members):
+        m = zoo.Model(f"wide{h}x{w}", "bf16", 3, h, w)
+        a = m.add(zoo.CONV, zoo.MODEL_INPUT, cin=3, cout=64, k=3, stride=1, pad=1, act=zoo.RELU)
+        a = m.add(zoo.CONV, a, cin=64, cout=64, k=3, stride=1, pad=1, act=act)
+        a = m.add(zoo.MAXPOOL, a, k=2, stride=2, pad=0)
+        m.add(zoo.CONV, a, cin=64, cout=16, k=1, stride=1, pad=0, act=zoo.NONE)
+        models.append(m.shapes())
+    mem = [(m, gen.make_blob(m, 5300 + i), None) for i, m in enumerate(models)]
+    x = gen.make_input(53 + h, batch, 3, h, w, "normal", "bf16")
+    fast, names = _run(mem, x)
+    plain, pnames = _run(mem, x, separate_stem=True)
+    assert "conv_pool" in names and "maxpool" not in names and "conv_pool" not in pnames and "maxpool" in pnames
+    for i, (a, b) in enumerate(zip(fast, plain)):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
+        ref = harness.oracle_nhwc(models[i], mem[i][1], x[-1:], True)
+        assert harness.rel_l2(a[-1:], ref) <= 2e-3 and harness.elem_excess(a[-1:], ref, harness.ELEM_C_BF16) <= 1.0
+    g = harness.GpuDag(mem, batch + 2)   # (a batch below the handle's, values that are not finite among its images)
+    try:
+        x[0, 0, h // 2, w // 2], x[-1, 2, 0, w - 1], x[-1, 1, h - 1, 0] = np.inf, np.nan, -np.inf
+        odd = g.run(x)
+    finally:
+        g.close()
+    for a, b in zip(odd, _run(mem, x, separate_stem=True)[0]):
+        assert np.array_equal(a, b, equal_nan=True)
