@@ -520,7 +520,7 @@ static void take_stem_launches(fi_dag* g) {
 // Planner pass, after take_stem_launches: a 3x3 stride-1 convolution of 64 to 64 channels (bf16, identity / ReLU / ReLU6) on images wider than the
 // patch kernel holds (below: its 256-row patches), whose ONLY reader is a 2x2 stride-2 max-pool: one launch, carried by the pool node; the convolution's
 // output is stored nowhere.  Same bits as the separate launches.  The kernel fills every compute unit's registers for its whole life, so it is
-taken where no other lane needs them: VGG-16 at batch 64 2513 -> 2434 us; a three-model DAG at batch 8 on three lanes 1074 -> 1093 with it, 1062 without.
+// taken where no other lane needs them: VGG-16 at batch 64 2513 -> 2434 us; a three-model DAG at batch 8 on three lanes 1074 -> 1093 with it, 1062 without.
 static void take_pool_launches(fi_dag* g) {
   if (g->opts.separate_stem || g->wdtype != FI_BF16 || g->n_lanes > 1) return;
   const int32_t total = (int32_t)g->nodes.size();
