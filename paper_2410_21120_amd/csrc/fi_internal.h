@@ -218,6 +218,8 @@ int launch_kwave(const Launch& L, const KArgs& a, void* stream, const std::vecto
 // stream_fits says whether a launch is one, and with which blocks of columns and pieces of a row launch_stream takes it.
 bool stream_fits(const Launch& L, const KArgs& a, int* nb, int* nch);
 int launch_stream(const Launch& L, const KArgs& a, int nb, int nch, void* stream);
+bool long_fits(const Launch& L, const KArgs& a);   // ... or of rows of any length behind an affine stage
+int launch_long(const Launch& L, const KArgs& a, void* stream);
 
 // Implemented in fi_patch.hip: a K_CONV_PATCH launch.  Returns a hipError_t as int.
 int launch_patch(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);

@@ -1737,6 +1737,7 @@ int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::v
       {   // many rows and a short reduction: they stream (the same bits, so the choice is made for the batches of this pass)
         int cols = 0, pieces = 0;
         if (stream_fits(L, a, &cols, &pieces)) return launch_stream(L, a, cols, pieces, stream);
+        if (long_fits(L, a)) return launch_long(L, a, stream);
       }
       if (hd[(size_t)L.first_desc].Cp == 4) {  // 4-channel model input
         if (!ab) {

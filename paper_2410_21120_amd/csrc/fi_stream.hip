@@ -26,6 +26,89 @@ namespace {
 
 constexpr int SW = 8;   // waves of a workgroup
 
+// max(x * scale + shift, 0) of eight channels: product and sum rounded separately, one rounding to bf16 (the depthwise kernel's operations).
+__device__ __forceinline__ bf16x8 affine_relu(u32x4 x, const u32x4 (&scale)[2], const u32x4 (&shift)[2]) {
+  u32x4 h;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float s0 = __uint_as_float(scale[e >> 1][(2 * e) & 3]), s1 = __uint_as_float(scale[e >> 1][(2 * e + 1) & 3]);
+    const float b0 = __uint_as_float(shift[e >> 1][(2 * e) & 3]), b1 = __uint_as_float(shift[e >> 1][(2 * e + 1) & 3]);
+    h[e] = pack_bf16x2(fmaxf(__fadd_rn(__fmul_rn(__uint_as_float(x[e] << 16), s0), b0), 0.0f),
+                       fmaxf(__fadd_rn(__fmul_rn(__uint_as_float(x[e] & 0xFFFF0000u), s1), b1), 0.0f));
+  }
+  return __builtin_bit_cast(bf16x8, h);
+}
+
+// A lane holds, for pixel (lane & 31) of 32, runs of four consecutive channels: bias, residual, activation, the one rounding.
+template <bool WIDE, int NB>
+__device__ __forceinline__ void finish_rows(const Desc& d, const f32x16 (&acc)[NB], int row0, int n0, int lane, const float* bias, uint8_t* patch, const Activation<false>& act,
+                                            const __amdgpu_buffer_rsrc_t rres, bool has_res, const __amdgpu_buffer_rsrc_t yres, bool stream_out) {
+  constexpr int AE = WIDE ? 4 : 2;
+  const int r31 = lane & 31, half = lane >> 5, lrow = lane >> 3, bsw = (r31 >> 1) & 7;
+  const bool hardswish = d.act == FI_ACT_HARDSWISH;
+  const int m = row0 + r31;
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    float v[16];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int cl = j * 32 + 8 * g + 4 * half;
+      const float4 b = *reinterpret_cast<const float4*>(bias + cl);
+      v[4 * g] = acc[j][4 * g] + b.x; v[4 * g + 1] = acc[j][4 * g + 1] + b.y; v[4 * g + 2] = acc[j][4 * g + 2] + b.z; v[4 * g + 3] = acc[j][4 * g + 3] + b.w;
+    }
+    if (WIDE || has_res) {   // (fp32 rows: no residual adds +0.0, as on the tiles)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int c = n0 + j * 32 + 8 * g + 4 * half;
+        const uint32_t off = c < d.Cop ? (uint32_t)((m * d.Cop + c) * AE) : OOB;
+        if constexpr (WIDE) {
+          const u32x4 r = __builtin_amdgcn_raw_buffer_load_b128(rres, off, 0, 0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[4 * g + e] += __uint_as_float(r[e]);
+        } else {
+          const u32x2 r = __builtin_amdgcn_raw_buffer_load_b64(rres, off, 0, 0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[4 * g + e] += __uint_as_float((e & 1) ? r[e >> 1] & 0xFFFF0000u : r[e >> 1] << 16);
+        }
+      }
+    }
+    if (hardswish) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] = act_hardswish(v[e]);
+    } else {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float q[4] = {v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
+        act.apply(q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * g + e] = q[e];
+      }
+    }
+    // Through a patch of the wave's own (32 rows of 128 bytes), so that whole cache lines leave.
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      if constexpr (WIDE) {
+        *reinterpret_cast<float4*>(patch + r31 * 128 + (((2 * g + half) ^ bsw) << 4)) = make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
+      } else {
+        const u32x2 pk = {pack_bf16x2(v[4 * g], v[4 * g + 1]), pack_bf16x2(v[4 * g + 2], v[4 * g + 3])};
+        *reinterpret_cast<u32x2*>(patch + r31 * 128 + ((((j & 1) * 4 + g) ^ bsw) << 4) + 8 * half) = pk;
+      }
+    }
+    if (!WIDE && (j & 1) == 0 && j + 1 < NB) continue;   // (bf16: two blocks of columns make a line)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's own LDS writes precede its reads
+    const int c = n0 + (WIDE ? j * 32 + (lane & 7) * 4 : j / 2 * 64 + (lane & 7) * 8);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = i * 8 + lrow;
+      const u32x4 o = *reinterpret_cast<const u32x4*>(patch + r * 128 + (((lane & 7) ^ ((r >> 1) & 7)) << 4));
+      const uint32_t off = c < d.Cop ? (uint32_t)(((row0 + r) * d.ys + c) * AE) : OOB;
+      if (stream_out) __builtin_amdgcn_raw_buffer_store_b128(o, yres, off, 0, 2);
+      else __builtin_amdgcn_raw_buffer_store_b128(o, yres, off, 0, 0);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+}
+
 // WIDE: fp32-stored activations, multiplied as hi + lo bf16 halves.  PRE: 1 = per-channel affine and activation on the way in.
 // NB: 32-column blocks of a workgroup's weights.  NCH: 128-byte pieces of a row (64 bf16 or 32 fp32 elements).
 template <bool WIDE, int PRE, int NB, int NCH>
@@ -36,11 +119,11 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
   constexpr int BN = NB * 32;
   constexpr int KW = (NCH * CE + 63) / 64;          // 64-element pieces of a weight row
   constexpr int W_BYTES = KW * BN * 128, KP = KW * 64;
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[W_BYTES + SW * 4096 + BN * 4 + (PRE == 1 ? KP * 6 : 0)];
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[W_BYTES + SW * 4096 + BN * 4 + (PRE == 1 ? KP * 8 : 0)];
   static_assert(sizeof(smem) <= 160 * 1024, "LDS of a compute unit");
   float* const bias_s = reinterpret_cast<float*>(smem + W_BYTES + SW * 4096);
   float* const shift_s = bias_s + BN;
-  bf16_t* const scale_s = reinterpret_cast<bf16_t*>(shift_s + KP);
+  float* const scale_s = shift_s + KP;
 
   int p, bid;
   if (!find_problem_at(a, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), p, bid)) return;
@@ -80,7 +163,7 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
   for (int i = tid; i < BN; i += SW * 64) bias_s[i] = n0 + i < d.Cop ? reinterpret_cast<const float*>(a.wbase + d.b_off)[n0 + i] : 0.0f;
   if constexpr (PRE == 1)
     for (int i = tid; i < KP; i += SW * 64) {
-      scale_s[i] = i < d.Cp ? reinterpret_cast<const bf16_t*>(a.wbase + d.pw_off)[i] : (bf16_t)0;
+      scale_s[i] = i < d.Cp ? bf2f(reinterpret_cast<const bf16_t*>(a.wbase + d.pw_off)[i]) : 0.0f;
       shift_s[i] = i < d.Cp ? reinterpret_cast<const float*>(a.wbase + d.pb_off)[i] : 0.0f;
     }
   {
@@ -100,10 +183,8 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
   const int bsw = (r31 >> 1) & 7;
   uint8_t* const patch = smem + W_BYTES + wave * 4096;
   const Activation<false> act(d.act);
-  const bool hardswish = d.act == FI_ACT_HARDSWISH;
   constexpr bool RESIDENT = !PRE && NCH * ST * NB * 4 <= 32;   // a weight fragment is 4 registers: few of them stay there for the life of the workgroup
   int fresh = 0;
-  const Activation<false> pre_act(d.pre_act);
   for (; t < t1; t += SW) {
     if constexpr (!RESIDENT) asm volatile("" : "+v"(fresh));   // (zero: keeps the reads of weights, bias and scale in the loop, where there are registers for them)
     f32x16 acc[NB];
@@ -131,22 +212,10 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
           hi = __builtin_bit_cast(bf16x8, h);
           lo = __builtin_bit_cast(bf16x8, l);
         } else if constexpr (PRE == 1) {
-          const u32x4 sc = *reinterpret_cast<const u32x4*>(scale_s + k + 8 * half + fresh);
-          const float4 s0 = *reinterpret_cast<const float4*>(shift_s + k + 8 * half + fresh), s1 = *reinterpret_cast<const float4*>(shift_s + k + 8 * half + 4 + fresh);
-          const float sh[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
-          float v[8];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const uint32_t xw = av[c][s][0][e];
-            v[2 * e] = __fadd_rn(__fmul_rn(__uint_as_float(xw << 16), __uint_as_float(sc[e] << 16)), sh[2 * e]);
-            v[2 * e + 1] = __fadd_rn(__fmul_rn(__uint_as_float(xw & 0xFFFF0000u), __uint_as_float(sc[e] & 0xFFFF0000u)), sh[2 * e + 1]);
-          }
-          float va[4] = {v[0], v[1], v[2], v[3]}, vb[4] = {v[4], v[5], v[6], v[7]};
-          pre_act.apply(va); pre_act.apply(vb);   // (identity, ReLU or ReLU6: the planner folds no other)
-          u32x4 h;
-#pragma unroll
-          for (int e = 0; e < 2; ++e) { h[e] = pack_bf16x2(va[2 * e], va[2 * e + 1]); h[2 + e] = pack_bf16x2(vb[2 * e], vb[2 * e + 1]); }
-          hi = __builtin_bit_cast(bf16x8, h);
+          const u32x4* const sc = reinterpret_cast<const u32x4*>(scale_s + k + 8 * half + fresh);
+          const u32x4* const sh = reinterpret_cast<const u32x4*>(shift_s + k + 8 * half + fresh);
+          const u32x4 scale[2] = {sc[0], sc[1]}, shift[2] = {sh[0], sh[1]};
+          hi = affine_relu(av[c][s][0], scale, shift);
         } else {
           hi = __builtin_bit_cast(bf16x8, av[c][s][0]);
         }
@@ -163,69 +232,117 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
       request(c, live);   // the same piece of the next block
       __builtin_amdgcn_sched_barrier(0);
     }
-    // A lane holds, for pixel (lane & 31), runs of four consecutive channels: bias, residual, activation, the one rounding.
-    const int m = t * 32 + r31;
+    finish_rows<WIDE, NB>(d, acc, t * 32, n0, lane, bias_s + fresh, patch, act, rres, has_res, yres, stream_out);
+  }
+}
+
+// The same, for rows of any length behind an affine stage with ReLU (DenseNet's layers beyond 384 channels, or of too few rows to pay for resident
+// weights): four waves, a block of 32 rows each, the weights of 64 channels at a time through a ring of three stages in LDS (one barrier per
+// 64 channels), the rows four pieces ahead in registers, scale and shift as tables in LDS, read before the barrier.  Bound: what a compute unit takes
+// from L2 (32 KB per piece in 0.9 us).  DenseNet-121, four members at batch 32, 14 x 14, 288 / 480 / 672 / 960 -> 128 channels: 17.2 / 22.0 / 26.0 / 32.0 us on the
+// 128x64 tile, 15.2 / 18.2 / 21.3 / 25.0 here.
+constexpr int LW = 4, LK = 1792;   // waves of a workgroup, the longest reduction (its tables leave room for two workgroups per compute unit)
+
+__global__ void __launch_bounds__(LW * 64, 2) conv_long_kernel(KArgs a) {
+  constexpr int NB = 4, BN = 128, NS = 3, STAGE = BN * 128, D = 4;   // columns; stages of the weights' ring; pieces of a row in registers
+  constexpr int AT_PATCH = NS * STAGE, AT_BIAS = AT_PATCH + LW * 4096, AT_SHIFT = AT_BIAS + BN * 4, AT_SCALE = AT_SHIFT + LK * 4;
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[AT_SCALE + LK * 4];   // (one array: operand reads must not wait for the direct loads)
+  static_assert(sizeof(smem) <= 80 * 1024, "two workgroups per compute unit");   // (one array: operand reads must not wait for the direct loads)
+  float* const bias_s = reinterpret_cast<float*>(smem + AT_BIAS);
+  float* const shift_s = reinterpret_cast<float*>(smem + AT_SHIFT);
+  float* const scale_s = reinterpret_cast<float*>(smem + AT_SCALE);
+
+  int p, bid;
+  if (!find_problem_at(a, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), p, bid)) return;
+  const Desc d = a.d[p];
+  const int M = a.batch[p] * d.Ho * d.Wo, slabs = (d.Cop + BN - 1) / BN;
+  const int tid = threadIdx.x, lane = tid & 63, r31 = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n0 = bid % slabs * BN, row0 = bid / slabs * (LW * 32) + wave * 32;
+  const int pieces = (d.Cp + 63) >> 6;
+  const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+      a.abase + d.x_off, 0, M > 0 ? (int)((((int64_t)M - 1) * d.xs + d.Cp) * 2) : 0, 0x00020000);
+  const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(a.wbase + d.w_off), 0, (int)((int64_t)d.Co * d.Kp * 2), 0x00020000);
+
+  for (int i = tid; i < pieces * 64; i += LW * 64) {
+    scale_s[i] = i < d.Cp ? bf2f(reinterpret_cast<const bf16_t*>(a.wbase + d.pw_off)[i]) : 0.0f;
+    shift_s[i] = i < d.Cp ? reinterpret_cast<const float*>(a.wbase + d.pb_off)[i] : 0.0f;
+  }
+  if (tid < BN) bias_s[tid] = n0 + tid < d.Cop ? reinterpret_cast<const float*>(a.wbase + d.b_off)[n0 + tid] : 0.0f;
+
+  u32x4 av[D][4];
+  const uint32_t row = (uint32_t)((row0 + r31) * d.xs + half * 8) * 2;   // (rows past M lie past the buffer's end)
+  auto request = [&](int u, int c) {
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      float v[16];
+    for (int s = 0; s < 4; ++s)
+      av[u][s] = __builtin_amdgcn_raw_buffer_load_b128(xres, c * 64 + s * 16 + half * 8 < d.Cp ? row + (uint32_t)(c * 128 + s * 32) : OOB, 0, 0);
+  };
+  // weights: 8 rows of 128 bytes per instruction, pieces of 16 bytes permuted at the source (piece ^ row / 2 % 8)
+  const int lrow = lane >> 3, piece = (lane & 7) ^ ((4 * wave + (lrow >> 1)) & 7);
+  const uint32_t w_row = (uint32_t)((n0 + wave * 8 + lrow) * d.Kp + piece * 8) * 2, w_step = (uint32_t)(LW * 8) * (uint32_t)d.Kp * 2;   // (rows past Co: past the end)
+  auto weights = [&](int c, int stage) {
+    const uint32_t dead = c * 64 + piece * 8 < d.Kp ? 0u : OOB;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int cl = j * 32 + 8 * g + 4 * half;
-        const float4 b = *reinterpret_cast<const float4*>(bias_s + cl + fresh);
-        v[4 * g] = acc[j][4 * g] + b.x; v[4 * g + 1] = acc[j][4 * g + 1] + b.y; v[4 * g + 2] = acc[j][4 * g + 2] + b.z; v[4 * g + 3] = acc[j][4 * g + 3] + b.w;
-      }
-      if (WIDE || has_res) {   // (fp32 rows: no residual adds +0.0, as on the tiles)
+    for (int i = 0; i < 4; ++i)
+      load_lds<16>(wres, smem + stage * STAGE + (wave + LW * i) * 1024, (w_row + w_step * i + (uint32_t)(c * 128)) | dead);
+  };
+  request(0, 0);
+  request(1, 1);
+  weights(0, 0);
+  request(2, 2);
+  weights(1, 1);
+  request(3, 3);
+
+  f32x16 acc[NB];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int c = n0 + j * 32 + 8 * g + 4 * half;
-          const uint32_t off = c < d.Cop ? (uint32_t)((m * d.Cop + c) * AE) : OOB;
-          if constexpr (WIDE) {
-            const u32x4 r = __builtin_amdgcn_raw_buffer_load_b128(rres, off, 0, 0);
+  for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * g + e] += __uint_as_float(r[e]);
-          } else {
-            const u32x2 r = __builtin_amdgcn_raw_buffer_load_b64(rres, off, 0, 0);
+    for (int e = 0; e < 16; ++e) acc[j][e] = 0.0f;
+  const int bsw = (r31 >> 1) & 7;
+  int stage = 0;
+  for (int c0 = 0; c0 < pieces; c0 += D) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * g + e] += __uint_as_float((e & 1) ? r[e >> 1] & 0xFFFF0000u : r[e >> 1] << 16);
-          }
+    for (int u = 0; u < D; ++u) {
+      const int c = c0 + u;
+      if (c >= pieces) break;
+      u32x4 scale[4][2], shift[4][2];   // (native vectors: of a float4 the compiler believes that it may be what a direct load brings, and waits for all of them)
+      if (c == 0) __syncthreads();   // (the tables are complete)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          scale[s][h] = *reinterpret_cast<const u32x4*>(smem + AT_SCALE + (c * 64 + s * 16 + 8 * half + 4 * h) * 4);
+          shift[s][h] = *reinterpret_cast<const u32x4*>(smem + AT_SHIFT + (c * 64 + s * 16 + 8 * half + 4 * h) * 4);
         }
+      // this wave's share of the piece's weights is in LDS (requested behind them: two pieces of rows and one of weights; past the last piece
+      // the requests are out of range, so that they are always as many), and it has read the stage before to the end
+      asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      const int into = stage == 0 ? NS - 1 : stage - 1;   // the stage that the piece before had
+      weights(c + 2, into);
+      __builtin_amdgcn_sched_barrier(0);
+      const uint8_t* const S = smem + stage * STAGE + r31 * 128;
+      stage = stage == NS - 1 ? 0 : stage + 1;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const bf16x8 x = affine_relu(av[u][s], scale[s], shift[s]);
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(S + j * 4096 + (((2 * s + half) ^ bsw) << 4)), x, acc[j], 0, 0, 0);
       }
-      if (hardswish) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = act_hardswish(v[e]);
-      } else {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float q[4] = {v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]};
-          act.apply(q);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[4 * g + e] = q[e];
-        }
-      }
-      // Through a patch of the wave's own (32 rows of 128 bytes), so that whole cache lines leave.
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        if constexpr (WIDE) {
-          *reinterpret_cast<float4*>(patch + r31 * 128 + (((2 * g + half) ^ bsw) << 4)) = make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
-        } else {
-          const u32x2 pk = {pack_bf16x2(v[4 * g], v[4 * g + 1]), pack_bf16x2(v[4 * g + 2], v[4 * g + 3])};
-          *reinterpret_cast<u32x2*>(patch + r31 * 128 + ((((j & 1) * 4 + g) ^ bsw) << 4) + 8 * half) = pk;
-        }
-      }
-      if (!WIDE && (j & 1) == 0 && j + 1 < NB) continue;   // (bf16: two blocks of columns make a line)
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's own LDS writes precede its reads
-      const int c = n0 + (WIDE ? j * 32 + (lane & 7) * 4 : j / 2 * 64 + (lane & 7) * 8);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = i * 8 + lrow;
-        const u32x4 o = *reinterpret_cast<const u32x4*>(patch + r * 128 + (((lane & 7) ^ ((r >> 1) & 7)) << 4));
-        const uint32_t off = c < d.Cop ? (uint32_t)(((t * 32 + r) * d.ys + c) * AE) : OOB;
-        if (stream_out) __builtin_amdgcn_raw_buffer_store_b128(o, yres, off, 0, 2);
-        else __builtin_amdgcn_raw_buffer_store_b128(o, yres, off, 0, 0);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      request(u, c + D);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (nothing lands in LDS any more)
+  const bool has_res = d.r_off != kNone, stream_out = (int64_t)M * d.Cop * 2 > (int64_t)STREAM_OUT_BYTES;
+  const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(
+      a.abase + (has_res ? d.r_off : 0), 0, has_res ? (int)((int64_t)M * d.Cop * 2) : 0, 0x00020000);
+  const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(
+      a.abase + d.y_off, 0, M > 0 ? (int)((((int64_t)M - 1) * d.ys + d.Cop) * 2) : 0, 0x00020000);
+  finish_rows<false, NB>(d, acc, row0, n0, lane, bias_s, smem + AT_PATCH + wave * 4096, Activation<false>(d.act), rres, has_res, yres, stream_out);
 }
 
 template <bool WIDE, int PRE, int NB, int NCH>
@@ -237,6 +354,43 @@ int go_stream(int blocks, const KArgs& a, hipStream_t s) {
 
 }  // namespace
 
+// What both kernels compute and address; `past`: rows past the last whose offsets they form.
+static bool streams(const Desc& t, int batch, bool wide, int past) {
+  const int es = wide ? 4 : 2;
+  const int64_t m = (int64_t)batch * t.Ho * t.Wo, ys = t.ys > t.Cop ? t.ys : t.Cop;
+  if (batch < 0 || t.k != 1 || t.kw != 1 || t.stride != 1 || t.pad != 0 || t.pad_w != 0 || t.gin > 0 || t.splits != 1 || t.ext || t.out_f32) return false;
+  if (t.pre_kind > 1 || (t.pre_kind == 1 && (wide || t.pre_act != FI_ACT_RELU)) || (t.pre_kind == 0 && t.xs != t.Cp)) return false;
+  if (t.act > FI_ACT_RELU6 && t.act != FI_ACT_HARDSWISH) return false;
+  if (t.Cp % 8 || t.Co != t.Cop || t.Cop % 8 || t.ys % (16 / es) || t.xs % (16 / es) || t.Kp < t.Cp || t.Kp % 8) return false;
+  return m < (1 << 24) && (m + past) * t.xs * es < (1ll << 31) && (m + past) * ys * es < (1ll << 31) && ((int64_t)t.Co + 128) * t.Kp * 2 < (1ll << 31);
+}
+
+// Whether a launch is one of affine stages and rows of any length.  (The bits are the tile kernel's: the rule may look at the launch.)  From 128
+// workgroups on: fewer leave the chip idle (7 x 7, 640 channels, four members, 52 workgroups 17.0 us on the tile, 19.7 here).
+bool long_fits(const Launch& L, const KArgs& a) {
+  int64_t blocks = 0;
+  for (int i = 0; i < L.n; ++i) {
+    const Desc& t = a.d[i];
+    const int64_t m = (int64_t)a.batch[i] * t.Ho * t.Wo;
+    if (!streams(t, a.batch[i], L.adtype != FI_BF16, LW * 32) || t.pre_kind != 1 || t.Cp > LK) return false;
+    blocks += (m + LW * 32 - 1) / (LW * 32) * ((t.Cop + 127) / 128);
+  }
+  return blocks >= 128;
+}
+
+int launch_long(const Launch& L, const KArgs& args, void* stream) {
+  KArgs a = args;
+  int64_t blocks = 0;
+  for (int i = 0; i < L.n; ++i) {
+    a.first_block[i] = (int32_t)blocks;
+    blocks += ((int64_t)a.batch[i] * a.d[i].Ho * a.d[i].Wo + LW * 32 - 1) / (LW * 32) * ((a.d[i].Cop + 127) / 128);
+  }
+  for (int i = L.n; i <= FI_MAX_GROUP; ++i) a.first_block[i] = (int32_t)blocks;
+  if (blocks <= 0) return (int)hipSuccess;
+  hipLaunchKernelGGL(conv_long_kernel, dim3((unsigned)blocks), dim3(LW * 64), 0, static_cast<hipStream_t>(stream), a);
+  return (int)hipGetLastError();
+}
+
 // Whether a launch of pointwise convolutions streams, and with which blocks of columns and pieces of a row.  (The rule may look at the
 // launch: the bits are the tile kernel's.)  Rows enough to pay for the weights that every workgroup loads first: 512 blocks of 32 rows, from three pieces on
 // 256 per piece.  4x MobileNetV3-Large at batch 32 1912 us without this kernel, 1824 / 1815 / 1807 from 2048 / 1024 / 512 blocks on (28 x 28
@@ -247,21 +401,16 @@ bool stream_fits(const Launch& L, const KArgs& a, int* nb, int* nch) {
   int64_t tiles = 0;
   int cop = 0, pieces = 0;
   const int pre = a.d[0].pre_kind;
-  if (pre == 2 || (wide && pre)) return false;
   for (int i = 0; i < L.n; ++i) {
     const Desc& t = a.d[i];
     const int64_t m = (int64_t)a.batch[i] * t.Ho * t.Wo;
-    if (a.batch[i] < 0 || t.pre_kind != pre || (t.act > FI_ACT_RELU6 && t.act != FI_ACT_HARDSWISH) || (pre == 1 && t.pre_act > FI_ACT_RELU6) || t.k != 1 || t.kw != 1 || t.stride != 1 || t.pad != 0 || t.pad_w != 0 || t.gin > 0 || t.splits != 1 || t.ext || t.out_f32 ||
-        t.Cp % 8 || t.Co != t.Cop || t.Cop % 8 || t.ys % (16 / es) || t.xs % (16 / es) || t.Kp < t.Cp || t.Kp % 8 || (pre == 0 && t.xs != t.Cp) ||
-        m >= (1 << 24) || (m + 2 * SW * 32) * t.xs * es >= (1ll << 31) || (m + 32) * (t.ys > t.Cop ? t.ys : t.Cop) * es >= (1ll << 31) ||
-        ((int64_t)t.Co + 128) * t.Kp * 2 >= (1ll << 31))
-      return false;
+    if (!streams(t, a.batch[i], wide, 2 * SW * 32) || t.pre_kind != pre) return false;
     tiles += (m + 31) / 32;
     cop = cop > t.Cop ? cop : t.Cop;
     pieces = pieces > (t.Cp + ce - 1) / ce ? pieces : (t.Cp + ce - 1) / ce;
   }
   if (tiles < 512 || tiles < 256 * pieces || pieces > 6 || cop > 128) return false;
-  *nb = cop <= 32 ? 1 : cop <= 64 ? 2 : 4;
+  *nb = pre || cop > 64 ? 4 : cop > 32 ? 2 : 1;
   *nch = pieces <= 4 ? pieces : 6;
   return true;
 }
@@ -291,7 +440,7 @@ int launch_stream(const Launch& L, const KArgs& args, int nb, int nch, void* str
     if (nch == 6) return go_stream<WIDE, PRE, NB, 6>(n, a, s);                                     \
   }
   FI_NCH(false, 0, 1) FI_NCH(false, 0, 2) FI_NCH(false, 0, 4)
-  FI_NCH(false, 1, 1) FI_NCH(false, 1, 2) FI_NCH(false, 1, 4)
+  FI_NCH(false, 1, 4)
   FI_NCH(true, 0, 1) FI_NCH(true, 0, 2) FI_NCH(true, 0, 4)
 #undef FI_NCH
   return (int)hipErrorInvalidValue;

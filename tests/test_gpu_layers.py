@@ -284,8 +284,10 @@ def test_pointwise_rows_that_stream(cin, cout, act_dtype, many):
     _bits_and_parity(m, act_dtype, 1, many)
 
 
-@pytest.mark.parametrize("first, grow, act", [(64, 32, zoo.RELU), (40, 24, zoo.RELU6), (128, 72, zoo.NONE)])
-def test_dense_layers_that_stream(first, grow, act):
+# 16 images: 1617 blocks of 32 rows; 6 images: 607, too few for resident weights from three pieces of 64 channels on; 440 channels are seven pieces
+@pytest.mark.parametrize("first, grow, act, many", [(64, 32, zoo.RELU, 16), (40, 24, zoo.RELU6, 16), (128, 72, zoo.NONE, 16), (64, 32, zoo.RELU, 6), (136, 40, zoo.RELU, 6),
+                                                    (200, 56, zoo.RELU, 6), (440, 72, zoo.RELU, 6)])
+def test_dense_layers_that_stream(first, grow, act, many):
     """Dense layers whose rows stream: an affine stage on the way in, the input a prefix of a concatenation's tensor."""
     m = zoo.Model("c", "bf16", 8, 61, 53)
     t = m.add(zoo.CONV, -1, cin=8, cout=first, k=1, stride=1, pad=0, act=zoo.RELU)
@@ -297,7 +299,7 @@ def test_dense_layers_that_stream(first, grow, act):
         t = m.add(zoo.CONCAT, t, residual=a)
         c += grow
     m.add(zoo.MAXPOOL, t, k=1, stride=1, pad=0)
-    _bits_and_parity(m, None, 1, 16)
+    _bits_and_parity(m, None, 1, many)
 
 
 @pytest.mark.parametrize("features, batch", [(1000, 4), (1001, 33), (7, 1)])
