@@ -109,7 +109,10 @@ __device__ __forceinline__ void finish_rows(const Desc& d, const f32x16 (&acc)[N
   }
 }
 
-// WIDE: fp32-stored activations, multiplied as hi + lo bf16 halves.  PRE: 1 = per-channel affine and activation on the way in.
+// WIDE: fp32-stored activations, multiplied as hi + lo bf16 halves.  PRE: 1 = per-channel affine and ReLU on the way in.
+// PRE 2 (not a pointwise convolution): 3x3 over the four-channel staged input, the first layer of the mobile families.  A row's 36 elements
+// are gathered tap by tap (8 or 16 bytes) from the pixels around it, which neighbouring rows share in the vector cache.  MobileNetV3-Large, fp32
+// rows, 112 x 112 x 16, two members at batch 32: 74.9 us on the tile kernel, 38 here.
 // NB: 32-column blocks of a workgroup's weights.  NCH: 128-byte pieces of a row (64 bf16 or 32 fp32 elements).
 template <bool WIDE, int PRE, int NB, int NCH>
 __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
@@ -136,14 +139,43 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, r31 = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
-      a.abase + d.x_off, 0, M > 0 ? (int)((((int64_t)M - 1) * d.xs + d.Cp) * AE) : 0, 0x00020000);
+      a.abase + d.x_off, 0, M > 0 ? (int)((PRE == 2 ? (int64_t)batch * d.H * d.W * 4 : ((int64_t)M - 1) * d.xs + d.Cp) * AE) : 0, 0x00020000);
   const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(a.wbase + d.w_off), 0, (int)((int64_t)d.Co * d.Kp * 2), 0x00020000);
 
   u32x4 av[NCH][ST][V];   // a block of rows, requested one block ahead
   int t = t0 + wave;
   uint32_t row = (uint32_t)((t * 32 + r31) * d.xs * AE + half * 8 * AE);
+  // PRE 2: where the block of rows to request has its windows (the first tap's row, column and byte offset)
+  int ih0 = 0, iw0 = 0;
+  auto window = [&](int block) {
+    const int m = block * 32 + r31, mm = m < M ? m : 0;
+    const int q1 = fast_div(mm, d.Wo, 1.0f / (float)d.Wo), n = fast_div(q1, d.Ho, 1.0f / (float)d.Ho);
+    ih0 = m < M ? (q1 - n * d.Ho) * d.stride - d.pad : -(1 << 20);   // (rows past M read as zero)
+    iw0 = (mm - q1 * d.Wo) * d.stride - d.pad_w;
+    row = (uint32_t)(((n * d.H + ih0) * d.W + iw0) * 4 * AE);
+  };
+  if constexpr (PRE == 2) window(t);
   auto request = [&](int c, uint32_t at) {
+    if constexpr (PRE == 2) {
+#pragma unroll
+      for (int s = 0; s < ST; ++s)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {   // this lane's two taps of the step: 4 (c ST + s) + 2 half + v
+          const int tap0 = 4 * (c * ST + s) + v, tap1 = tap0 + 2;
+          const int r = half ? tap1 / 3 : tap0 / 3, q = half ? tap1 % 3 : tap0 % 3;
+          const bool ok = r < 3 && (unsigned)(ih0 + r) < (unsigned)d.H && (unsigned)(iw0 + q) < (unsigned)d.W;
+          const uint32_t off = ok ? (row + (uint32_t)((r * d.W + q) * 4 * AE)) | (at & OOB) : OOB;
+          if constexpr (WIDE) {
+            av[c][s][v % V] = __builtin_amdgcn_raw_buffer_load_b128(xres, off, 0, 0);
+          } else {
+            const u32x2 px = __builtin_amdgcn_raw_buffer_load_b64(xres, off, 0, 0);
+            av[c][s][0][2 * v] = px[0];
+            av[c][s][0][2 * v + 1] = px[1];
+          }
+        }
+      return;
+    }
 #pragma unroll
     for (int s = 0; s < ST; ++s) {
       const uint32_t off = c * CE + s * 16 + half * 8 < d.Cp ? at + (uint32_t)((c * CE + s * 16) * AE) : OOB;
@@ -167,7 +199,7 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
       shift_s[i] = i < d.Cp ? reinterpret_cast<const float*>(a.wbase + d.pb_off)[i] : 0.0f;
     }
   {
-    const uint32_t live = t < t1 ? row : OOB;
+    const uint32_t live = t < t1 ? PRE == 2 ? 0u : row : OOB;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) request(c, live);
   }
@@ -192,8 +224,9 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
     for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[j][e] = 0.0f;
-    row += next;
-    const uint32_t live = t + SW < t1 ? row : OOB;
+    if constexpr (PRE == 2) window(t + SW);
+    else row += next;
+    const uint32_t live = t + SW < t1 ? PRE == 2 ? 0u : row : OOB;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
 #pragma unroll
@@ -358,12 +391,18 @@ int go_stream(int blocks, const KArgs& a, hipStream_t s) {
 static bool streams(const Desc& t, int batch, bool wide, int past) {
   const int es = wide ? 4 : 2;
   const int64_t m = (int64_t)batch * t.Ho * t.Wo, ys = t.ys > t.Cop ? t.ys : t.Cop;
+  if (t.Cp == 4)   // 3x3 over the four-channel staged input
+    return batch >= 0 && t.k == 3 && t.kw == 3 && t.stride >= 1 && t.gin == 0 && t.pre_kind == 0 && t.splits == 1 && !t.ext && !t.out_f32 && t.xs == 4 && t.Kp == 64 && t.Co == t.Cop &&
+           t.Cop % 8 == 0 && t.ys % (16 / es) == 0 && (t.act <= FI_ACT_RELU6 || t.act == FI_ACT_HARDSWISH) && m < (1 << 24) - 1024 &&
+           (int64_t)batch * t.H * t.W * 4 * es < (1ll << 31) && (m + past) * ys * es < (1ll << 31);
   if (batch < 0 || t.k != 1 || t.kw != 1 || t.stride != 1 || t.pad != 0 || t.pad_w != 0 || t.gin > 0 || t.splits != 1 || t.ext || t.out_f32) return false;
   if (t.pre_kind > 1 || (t.pre_kind == 1 && (wide || t.pre_act != FI_ACT_RELU)) || (t.pre_kind == 0 && t.xs != t.Cp)) return false;
   if (t.act > FI_ACT_RELU6 && t.act != FI_ACT_HARDSWISH) return false;
   if (t.Cp % 8 || t.Co != t.Cop || t.Cop % 8 || t.ys % (16 / es) || t.xs % (16 / es) || t.Kp < t.Cp || t.Kp % 8) return false;
   return m < (1 << 24) && (m + past) * t.xs * es < (1ll << 31) && (m + past) * ys * es < (1ll << 31) && ((int64_t)t.Co + 128) * t.Kp * 2 < (1ll << 31);
 }
+
+static int stream_pre(const Desc& t) { return t.Cp == 4 ? 2 : t.pre_kind; }   // (the kernel's PRE)
 
 // Whether a launch is one of affine stages and rows of any length.  (The bits are the tile kernel's: the rule may look at the launch.)  From 128
 // workgroups on: fewer leave the chip idle (7 x 7, 640 channels, four members, 52 workgroups 17.0 us on the tile, 19.7 here).
@@ -400,17 +439,18 @@ bool stream_fits(const Launch& L, const KArgs& a, int* nb, int* nch) {
   const int es = wide ? 4 : 2, ce = 128 / es;
   int64_t tiles = 0;
   int cop = 0, pieces = 0;
-  const int pre = a.d[0].pre_kind;
+  const int pre = stream_pre(a.d[0]);
   for (int i = 0; i < L.n; ++i) {
     const Desc& t = a.d[i];
     const int64_t m = (int64_t)a.batch[i] * t.Ho * t.Wo;
-    if (!streams(t, a.batch[i], wide, 2 * SW * 32) || t.pre_kind != pre) return false;
+    if (!streams(t, a.batch[i], wide, 2 * SW * 32) || stream_pre(t) != pre) return false;
     tiles += (m + 31) / 32;
     cop = cop > t.Cop ? cop : t.Cop;
-    pieces = pieces > (t.Cp + ce - 1) / ce ? pieces : (t.Cp + ce - 1) / ce;
+    const int k = t.Cp == 4 ? 36 : t.Cp;
+    pieces = pieces > (k + ce - 1) / ce ? pieces : (k + ce - 1) / ce;
   }
   if (tiles < 512 || tiles < 256 * pieces || pieces > 6 || cop > 128) return false;
-  *nb = pre || cop > 64 ? 4 : cop > 32 ? 2 : 1;
+  *nb = pre == 1 || cop > 64 ? 4 : cop > 32 ? 2 : 1;
   *nch = pieces <= 4 ? pieces : 6;
   return true;
 }
@@ -430,7 +470,13 @@ int launch_stream(const Launch& L, const KArgs& args, int nb, int nch, void* str
   for (int i = L.n; i <= FI_MAX_GROUP; ++i) a.first_block[i] = (int32_t)blocks;
   const int n = (int)blocks;
   const bool wide = L.adtype != FI_BF16;
-  const int pre = a.d[0].pre_kind;
+  const int pre = stream_pre(a.d[0]);
+  if (pre == 2) {
+#define FI_GATHER(NB) if (nb == (NB)) return wide ? go_stream<true, 2, NB, 2>(n, a, s) : go_stream<false, 2, NB, 1>(n, a, s);
+    FI_GATHER(1) FI_GATHER(2) FI_GATHER(4)
+#undef FI_GATHER
+    return (int)hipErrorInvalidValue;
+  }
 #define FI_NCH(WIDE, PRE, NB)                                                                      \
   if (wide == (WIDE) && pre == (PRE) && nb == (NB)) {                                              \
     if (nch == 1) return go_stream<WIDE, PRE, NB, 1>(n, a, s);                                     \

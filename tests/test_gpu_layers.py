@@ -284,6 +284,15 @@ def test_pointwise_rows_that_stream(cin, cout, act_dtype, many):
     _bits_and_parity(m, act_dtype, 1, many)
 
 
+@pytest.mark.parametrize("cout, stride, pad, act_dtype", [(16, 2, 1, "f32"), (40, 1, 0, "f32"), (104, 2, 0, "f32"), (24, 2, 1, None), (64, 1, 1, "f32"), (136, 2, 1, None), (40, 1, 1, None)])
+def test_first_layers_that_stream(cout, stride, pad, act_dtype):
+    """3x3 convolutions over the model input gather their rows tap by tap: ragged blocks of rows and columns, windows over every border."""
+    m = zoo.Model("c", "bf16", 3, 123 if stride == 2 else 61, 107 if stride == 2 else 53)
+    a = m.add(zoo.CONV, -1, cin=3, cout=cout, k=3, stride=stride, pad=pad, act=zoo.HARDSWISH if cout == 16 else zoo.RELU6)
+    m.add(zoo.MAXPOOL, a, k=1, stride=1, pad=0)
+    _bits_and_parity(m, act_dtype, 1, 6)
+
+
 # 16 images: 1617 blocks of 32 rows; 6 images: 607, too few for resident weights from three pieces of 64 channels on; 440 channels are seven pieces
 @pytest.mark.parametrize("first, grow, act, many", [(64, 32, zoo.RELU, 16), (40, 24, zoo.RELU6, 16), (128, 72, zoo.NONE, 16), (64, 32, zoo.RELU, 6), (136, 40, zoo.RELU, 6),
                                                     (200, 56, zoo.RELU, 6), (440, 72, zoo.RELU, 6)])
