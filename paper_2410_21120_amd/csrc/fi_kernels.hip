@@ -1389,6 +1389,82 @@ __global__ void __launch_bounds__(256) dwconv_strip_kernel(KArgs a) {
   }
 }
 
+// 3x3 stride 1, two rows of four outputs per thread: the four input rows are loaded once (three pixels per output instead of four and a
+// half).  Bound: the vector cache's loads.  fp32 rows, two members at batch 32, strip kernel -> this one: 112 x 112 x 16 39.5 -> 35.0 us, 56 x 56 x 72 40.5 ->
+// 37.8, 14 x 14 x 672 29.2 -> 25.9.  From 384 workgroups on (14 x 14 x 480, 420 workgroups 22.8 -> 20.0); below, half as many threads leave the
+// chip idle (14 x 14 x 200, 175 workgroups 15.3 -> 18.5).  Every output adds its taps in the strip kernel's order: the same bits.
+template <typename TA>
+__global__ void __launch_bounds__(256) dwconv_block_kernel(KArgs a) {
+  constexpr int S = 4, NPIX = S + 2;
+  int p, bid;
+  if (!find_problem(a, K_DWCONV, 0, p, bid)) return;
+  const Desc d = a.d[p];
+  const int batch = a.batch[p];
+  const int cv = d.Cop / 8, strips = (d.Wo + S - 1) / S, bands = (d.Ho + 1) / 2;
+  const int64_t idx = (int64_t)bid * 256 + threadIdx.x;
+  if (idx >= (int64_t)batch * bands * strips * cv) return;
+  const int c8 = (int)(idx % cv) * 8;
+  const int64_t t = idx / cv;
+  const int q0 = (int)(t % strips) * S;
+  const int p0 = (int)((t / strips) % bands) * 2;
+  const int n = (int)(t / ((int64_t)strips * bands));
+  const TA* const xn = reinterpret_cast<const TA*>(a.abase + d.x_off) + (int64_t)n * d.H * d.W * d.xs + c8;
+  const bf16_t* const w = reinterpret_cast<const bf16_t*>(a.wbase + d.w_off) + c8;
+  float acc[2][S][8];
+#pragma unroll
+  for (int o = 0; o < 2; ++o)
+#pragma unroll
+    for (int j = 0; j < S; ++j)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[o][j][i] = 0.0f;
+  const int ih0 = p0 - d.pad, iw0 = q0 - d.pad;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int ih = ih0 + r;
+    if ((unsigned)ih >= (unsigned)d.H) continue;   // a row outside the image adds nothing
+    const TA* const xr = xn + (int64_t)ih * d.W * d.xs;
+    float xv[NPIX][8];
+#pragma unroll
+    for (int c = 0; c < NPIX; ++c) {
+      const int iw = iw0 + c;
+      const bool ok = (unsigned)iw < (unsigned)d.W;
+      load8(xr + (ok ? (int64_t)iw * d.xs : 0), xv[c]);   // always a valid address; masked below
+#pragma unroll
+      for (int i = 0; i < 8; ++i) xv[c][i] = ok ? xv[c][i] : 0.0f;
+    }
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      if (r - o < 0 || r - o > 2) continue;   // this input row is row r - o of output row o's window
+#pragma unroll
+      for (int sx = 0; sx < 3; ++sx) {
+        float wv[8];
+        load8(w + ((r - o) * 3 + sx) * d.Cp, wv);
+#pragma unroll
+        for (int j = 0; j < S; ++j)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) acc[o][j][i] += xv[j + sx][i] * wv[i];
+      }
+    }
+  }
+  float bv[8];
+  load8(reinterpret_cast<const float*>(a.wbase + d.b_off) + c8, bv);
+#pragma unroll
+  for (int o = 0; o < 2; ++o) {
+    if (p0 + o >= d.Ho) break;
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+      const int q = q0 + j;
+      if (q >= d.Wo) break;
+      const int64_t m = ((int64_t)n * d.Ho + p0 + o) * d.Wo + q;
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = acc[o][j][i] + bv[i];
+      activate_n<8>(v, d.act);
+      store8(reinterpret_cast<TA*>(a.abase + d.y_off) + m * d.ys + c8, v);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------
 // global average pooling, 8 channels per thread
 // ---------------------------------------------------------------------------------
@@ -1812,6 +1888,19 @@ int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::v
       const bool vec = hd[(size_t)L.first_desc].vec != 0;
       if (vec && hd[(size_t)L.first_desc].tiles_n > 1) {   // the planner found one filter size and stride for the whole launch
         const int ks = hd[(size_t)L.first_desc].k, st = hd[(size_t)L.first_desc].stride;
+        if (ks == 3 && st == 1) {
+          bool plain = true;
+          int64_t blocks2 = 0;
+          KArgs a2 = a;
+          for (int i = 0; i <= FI_MAX_GROUP; ++i) {
+            a2.first_block[i] = (int32_t)blocks2;
+            if (i >= L.n) continue;
+            const Desc& t = a.d[i];
+            plain = plain && t.r_off == kNone && !t.ext && t.Co == t.Cop;
+            blocks2 += ((int64_t)a.batch[i] * ((t.Ho + 1) / 2) * ((t.Wo + 3) / 4) * (t.Cop / 8) + 255) / 256;
+          }
+          if (plain && blocks2 >= 384) return ab ? go(dwconv_block_kernel<bf16_t>, (int)blocks2, 256, a2, s) : go(dwconv_block_kernel<float>, (int)blocks2, 256, a2, s);
+        }
 #define FI_DW_STRIP(K, T) if (ks == K && st == T) return ab ? go(dwconv_strip_kernel<bf16_t, K, T>, nb, 256, a, s) : go(dwconv_strip_kernel<float, K, T>, nb, 256, a, s);
         FI_DW_STRIP(3, 1) FI_DW_STRIP(3, 2) FI_DW_STRIP(5, 1) FI_DW_STRIP(5, 2) FI_DW_STRIP(7, 1) FI_DW_STRIP(7, 2)
 #undef FI_DW_STRIP

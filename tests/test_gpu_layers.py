@@ -293,6 +293,16 @@ def test_first_layers_that_stream(cout, stride, pad, act_dtype):
     _bits_and_parity(m, act_dtype, 1, 6)
 
 
+@pytest.mark.parametrize("h, w, c, pad, act_dtype, many", [(61, 53, 160, 1, None, 12), (60, 50, 136, 0, "f32", 18), (33, 30, 248, 1, "f32", 24)])
+def test_depthwise_two_rows_per_thread(h, w, c, pad, act_dtype, many):
+    """3x3 stride-1 depthwise layers of 384 workgroups or more compute two rows per thread; one image keeps one row: the same bits."""
+    m = zoo.Model("c", "bf16", 8, h, w)
+    a = m.add(zoo.CONV, -1, cin=8, cout=c, k=1, stride=1, pad=0, act=zoo.RELU)
+    a = m.add(zoo.DWCONV, a, cin=c, cout=c, k=3, stride=1, pad=pad, act=zoo.HARDSWISH if c == 160 else zoo.RELU6)
+    m.add(zoo.MAXPOOL, a, k=1, stride=1, pad=0)
+    _bits_and_parity(m, act_dtype, 1, many)
+
+
 # 16 images: 1617 blocks of 32 rows; 6 images: 607, too few for resident weights from three pieces of 64 channels on; 440 channels are seven pieces
 @pytest.mark.parametrize("first, grow, act, many", [(64, 32, zoo.RELU, 16), (40, 24, zoo.RELU6, 16), (128, 72, zoo.NONE, 16), (64, 32, zoo.RELU, 6), (136, 40, zoo.RELU, 6),
                                                     (200, 56, zoo.RELU, 6), (440, 72, zoo.RELU, 6)])
