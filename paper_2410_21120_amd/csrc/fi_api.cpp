@@ -1008,8 +1008,10 @@ static void build_schedule(fi_dag* g) {
         continue;
       }
       const int adt = g->members[(size_t)nd.model].spec.act_dtype;
-      const int pre_kind = (nd.pre < 0 || nd.kind == K_STEM || nd.kind == K_CONV_POOL) ? 0 : g->nodes[(size_t)nd.pre].kind == K_MUL ? 2 : 1;
-      const auto key = std::make_tuple(nd.kind, nd.tile, nd.lane * 64 + pre_kind * 16 + (walks_groups(nd, adt) ? 8 : 0) + (nd.kind == K_CONV_MFMA && nd.Cp == 4 ? 4 : 0) + adt * 2 +
+      // problems of one launch share the stage on their input side, or (a kernel built for each of one to three channels) the channel count
+      const int form = nd.kind == K_CONV_KWAVE && (nd.tile & KW_RGB) ? nd.Cp
+                       : (nd.pre < 0 || nd.kind == K_STEM || nd.kind == K_CONV_POOL) ? 0 : g->nodes[(size_t)nd.pre].kind == K_MUL ? 2 : 1;
+      const auto key = std::make_tuple(nd.kind, nd.tile, nd.lane * 64 + form * 16 + (walks_groups(nd, adt) ? 8 : 0) + (nd.kind == K_CONV_MFMA && nd.Cp == 4 ? 4 : 0) + adt * 2 +
                                        ((nd.kind == K_CONV_MFMA || nd.kind == K_FC) && nd.splits > 1 ? 1 : 0));
       auto it = open.find(key);
       if (!opts->group_levels || it == open.end() || g->launches[(size_t)it->second].n >= FI_MAX_GROUP) {

@@ -99,6 +99,17 @@ def test_conv_f32_patch_of_few_channels(case):
     _run_case(m, 940 + cin + cout, b, tol=2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23)
 
 
+def test_conv_f32_few_channel_siblings():
+    """Sibling layers of two, three, one and three channels, 3x3 stride 2 on 224 x 224: held like the above."""
+    m = zoo.Model("c", "f32", 3, 224, 224)
+    sides = [m.add(zoo.CONV, -1, cin=3, cout=c, k=1, stride=1, pad=0, act=zoo.NONE) for c in (2, 3, 1, 3)]
+    wide = [m.add(zoo.CONV, a, cin=c, cout=32, k=3, stride=2, pad=1, act=zoo.RELU) for a, c in zip(sides, (2, 3, 1, 3))]
+    t = wide[0]
+    for w in wide[1:]:
+        t = m.add(zoo.CONCAT, t, residual=w)
+    _run_case(m, 950, 4, tol=2.0 * ((9 * 3) ** 0.5 + 3 ** 0.5) * 2.0 ** -23)   # (the roundings of both layers)
+
+
 @pytest.mark.parametrize("case", [(64, 40, 3, 1, 1, 61, 57, 4, "64x64x4"), (3, 64, 7, 2, 3, 161, 157, 4, "64x64x4 scalar"),
                                   (5, 33, 3, 1, 1, 9, 11, 1, "32x32x8 scalar"), (36, 31, 5, 2, 2, 9, 11, 1, "32x32x8")])
 def test_conv_f32_weights_that_are_not_finite(case):

@@ -104,6 +104,22 @@ def test_fp32_layers_of_few_products_keep_the_element_kernel(layer, kernel):
     assert [L.kernel for L in d.launches()][1:] == [kernel]
 
 
+def test_few_channel_launches_hold_one_channel_count():
+    """The kernel of fp32 layers of one to three channels is built for a channel count: sibling layers of other counts are launches of their own."""
+    m = zoo.Model("c", "f32", 3, 224, 224)
+    sides = [m.add(zoo.CONV, -1, cin=3, cout=c, k=1, stride=1, pad=0, act=zoo.NONE) for c in (2, 3, 1, 3)]
+    wide = [m.add(zoo.CONV, a, cin=c, cout=64, k=3, stride=2, pad=1, act=zoo.RELU) for a, c in zip(sides, (2, 3, 1, 3))]
+    t = wide[0]
+    for w in wide[1:]:
+        t = m.add(zoo.CONCAT, t, residual=w)
+    m.shapes()
+    blob = gen.make_blob(m, 1)
+    spec, keep = fi.make_spec(m, blob.ctypes.data, blob.nbytes)
+    d = fi.Dag([spec], 4, fi.HostAllocators(), keepalive=(keep, blob))
+    launch = [d.nodes()[w].launch for w in wide]
+    assert launch[1] == launch[3] and len(set(launch)) == 3   # (the two of three channels share one)
+
+
 def test_patch_launches_count_the_convolutions_they_carry():
     """The patch kernel's lines are in workgroups of one launch.  A 1x1 convolution beside a 3x3 of the same size, output channels and
     tile stays on the tile kernel and must not count: 42 images of 28 x 28 x 256 are 130 tiles of 512x128, below the line of 256 (two
