@@ -142,6 +142,23 @@ def test_patch_launches_count_the_convolutions_they_carry():
     assert "conv_patch 256x64" in with_pointwise and "conv_mfma_256x128" in with_pointwise
 
 
+def test_the_convolution_and_pool_launch_leaves_room_for_swaps():
+    """A DAG of one architecture takes VGG's second layer and its pool in one launch, one of two lanes does not: replacing a member by a smaller
+    one of another architecture must not need more memory than the first plan (a swap into the loaded allocation would be refused)."""
+    def info(fams):
+        specs, keep = [], []
+        for f in fams:
+            m = zoo.FAMILIES[f](hw=224)
+            blob = gen.make_blob(m, 1)
+            s, k = fi.make_spec(m, blob.ctypes.data, blob.nbytes)
+            specs.append(s)
+            keep.append((k, blob))
+        return fi.fi_footprint(specs, fi.make_opts(8, fi.HostAllocators()))
+    same, mixed = info(["vgg16", "vgg16"]), info(["vgg16", "vgg11"])
+    assert same.n_lanes == 1 and mixed.n_lanes == 2
+    assert mixed.device_bytes <= same.device_bytes
+
+
 def test_activation_arena_liveness_non_overlap():
     for fams in (["resnet50", "mobilenetv2", "vgg16"], ["resnet18"] * 3, ["tiny", "tiny"]):
         d, _, _ = _build(fams, 3, hw=64 if fams[0] != "tiny" else 32)
