@@ -110,6 +110,8 @@ __global__ void __launch_bounds__(512, 2) conv_pool_kernel(KArgs a) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     fetch(buf ^ 1);
+    asm volatile("" ::: "memory");   // (the count above holds if the block's two stores come behind)
+    __builtin_amdgcn_sched_barrier(0);
     f32x16 acc[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)

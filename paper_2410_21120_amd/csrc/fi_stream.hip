@@ -320,12 +320,13 @@ __global__ void __launch_bounds__(LW * 64, 2) conv_long_kernel(KArgs a) {
     for (int i = 0; i < 4; ++i)
       load_lds<16>(wres, smem + stage * STAGE + (wave + LW * i) * 1024, (w_row + w_step * i + (uint32_t)(c * 128)) | dead);
   };
-  request(0, 0);
-  request(1, 1);
+  // The loop's count of outstanding loads holds if the weights stand before the rows: the compiler must not mix them.
   weights(0, 0);
-  request(2, 2);
   weights(1, 1);
-  request(3, 3);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < D; ++u) request(u, u);
 
   f32x16 acc[NB];
 #pragma unroll
@@ -348,8 +349,8 @@ __global__ void __launch_bounds__(LW * 64, 2) conv_long_kernel(KArgs a) {
           scale[s][h] = *reinterpret_cast<const u32x4*>(smem + AT_SCALE + (c * 64 + s * 16 + 8 * half + 4 * h) * 4);
           shift[s][h] = *reinterpret_cast<const u32x4*>(smem + AT_SHIFT + (c * 64 + s * 16 + 8 * half + 4 * h) * 4);
         }
-      // this wave's share of the piece's weights is in LDS (requested behind them: two pieces of rows and one of weights; past the last piece
-      // the requests are out of range, so that they are always as many), and it has read the stage before to the end
+      // this wave's share of the piece's weights is in LDS (requested behind them: at least two pieces of rows and one of weights; past the last
+      // piece the requests are out of range, so that they are always as many), and it has read the stage before to the end
       asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
