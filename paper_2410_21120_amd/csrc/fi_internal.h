@@ -183,6 +183,27 @@ struct KArgs {
   Desc d[FI_MAX_GROUP];          // the launch's problems: read through the scalar cache, no memory round trip
 };
 
+// Kernels whose workgroups walk several blocks of work each, one workgroup per compute unit: `units` workgroups at most are shared out to the n
+// problems of a launch, by their blocks, no more than most[i] to problem i, one at least where there is work.  (A share rounded up on its own
+// makes a few workgroups too many, which start when the others have ended: three VGG-16 layers of 224 x 224 on 258 workgroups took 37 us, on 256 25 us.)
+inline void share_workgroups(const int64_t* blocks, const int64_t* most, int n, int64_t units, int64_t* groups) {
+  int64_t total = 0, left = units;
+  for (int i = 0; i < n; ++i) { total += blocks[i]; left -= blocks[i] > 0; }
+  const int64_t pool = left > 0 ? left : 0;
+  for (int i = 0; i < n; ++i) {
+    groups[i] = blocks[i] > 0 ? 1 + pool * blocks[i] / total : 0;
+    if (groups[i] > most[i]) groups[i] = most[i];
+    left -= blocks[i] > 0 ? groups[i] - 1 : 0;
+  }
+  for (; left > 0; --left) {   // what rounding left over: where a workgroup has most to do
+    int at = -1;
+    for (int i = 0; i < n; ++i)
+      if (blocks[i] > 0 && groups[i] < most[i] && (at < 0 || blocks[i] * groups[at] > blocks[at] * groups[i])) at = i;
+    if (at < 0) return;
+    ++groups[at];
+  }
+}
+
 // What the request aggregator needs to know about a handle (filled by serving_info in fi_api.cpp).
 struct ServingInfo {
   int32_t n_models = 0, max_batch = 0, per_member_inputs = 0, state = 0;

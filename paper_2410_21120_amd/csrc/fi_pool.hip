@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(512, 2) conv_pool_kernel(KArgs a) {
 int launch_pool(const Launch& L, const KArgs& args, void* stream, const std::vector<Desc>& hd) {
   if (L.n < 1 || L.n > FI_MAX_GROUP || L.wdtype != FI_BF16 || L.adtype != FI_BF16) return (int)hipErrorInvalidValue;
   KArgs a = args;
-  int64_t total = 0, blocks = 0, share[FI_MAX_GROUP];
+  int64_t blocks = 0, share[FI_MAX_GROUP], groups[FI_MAX_GROUP];
   for (int i = 0; i < L.n; ++i) {
     const Desc& t = hd[(size_t)(L.first_desc + i)];
     a.d[i] = t;
@@ -178,14 +178,13 @@ int launch_pool(const Launch& L, const KArgs& args, void* stream, const std::vec
         b * t.H * t.W * 128 >= (1ll << 31) || b * t.Ho * t.Wo * t.ys * 2 >= (1ll << 31))
       return (int)hipErrorInvalidValue;
     share[i] = b * ((t.H + 15) / 16) * ((t.W + 15) / 16);
-    total += share[i];
   }
-  if (total == 0) return (int)hipSuccess;
-  for (int i = 0; i < L.n; ++i) {   // one workgroup per compute unit, shared out by the blocks of pixels
+  share_workgroups(share, share, L.n, 256, groups);
+  for (int i = 0; i < L.n; ++i) {
     a.first_block[i] = (int32_t)blocks;
-    const int64_t g = (256 * share[i] + total - 1) / total;
-    blocks += g < share[i] ? g : share[i];
+    blocks += groups[i];
   }
+  if (blocks == 0) return (int)hipSuccess;
   for (int i = L.n; i <= FI_MAX_GROUP; ++i) a.first_block[i] = (int32_t)blocks;
   hipLaunchKernelGGL(conv_pool_kernel, dim3((unsigned)blocks), dim3(512), 0, static_cast<hipStream_t>(stream), a);
   return (int)hipGetLastError();

@@ -459,14 +459,15 @@ bool stream_fits(const Launch& L, const KArgs& a, int* nb, int* nch) {
 int launch_stream(const Launch& L, const KArgs& args, int nb, int nch, void* stream) {
   KArgs a = args;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int64_t tiles = 0, blocks = 0;
-  for (int i = 0; i < L.n; ++i) tiles += ((int64_t)a.batch[i] * a.d[i].Ho * a.d[i].Wo + 31) / 32 * ((a.d[i].Cop + nb * 32 - 1) / (nb * 32));
-  for (int i = 0; i < L.n; ++i) {   // one workgroup per compute unit, shared out by the blocks of rows and columns
-    const int64_t rows = ((int64_t)a.batch[i] * a.d[i].Ho * a.d[i].Wo + 31) / 32, slabs = (a.d[i].Cop + nb * 32 - 1) / (nb * 32);
-    int64_t groups = (256 * rows + tiles - 1) / tiles;
-    if (groups > (rows + SW - 1) / SW) groups = (rows + SW - 1) / SW;
+  int64_t blocks = 0, rows[FI_MAX_GROUP], most[FI_MAX_GROUP], groups[FI_MAX_GROUP];
+  for (int i = 0; i < L.n; ++i) {
+    rows[i] = ((int64_t)a.batch[i] * a.d[i].Ho * a.d[i].Wo + 31) / 32;
+    most[i] = (rows[i] + SW - 1) / SW;
+  }
+  share_workgroups(rows, most, L.n, 256, groups);
+  for (int i = 0; i < L.n; ++i) {
     a.first_block[i] = (int32_t)blocks;
-    blocks += groups * slabs;
+    blocks += groups[i] * ((a.d[i].Cop + nb * 32 - 1) / (nb * 32));
   }
   for (int i = L.n; i <= FI_MAX_GROUP; ++i) a.first_block[i] = (int32_t)blocks;
   const int n = (int)blocks;

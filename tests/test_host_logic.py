@@ -4,6 +4,8 @@ planners, packing, the state machine and the error paths.  No kernel is launched
 import ctypes as C
 import os
 import re
+import shutil
+import subprocess
 
 import numpy as np
 import pytest
@@ -785,3 +787,49 @@ def test_member_chunks_shrink_the_activation_arena():
     one, _, _ = _build(["resnet50", "vgg16"], 4, hw=128, member_chunks=2)
     ref, _, _ = _build(["resnet50", "vgg16"], 4, hw=128)
     assert one.query().act_bytes == ref.query().act_bytes and one.query().n_launches == ref.query().n_launches
+
+
+SHARES = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "fi_internal.h"
+// 256 in total (fewer only where the problems have no use for more), one at least where there is work, no more than most[i], and no workgroup
+// that another problem, with longer shares even then, could use better
+int main() {
+  uint32_t seed = 7;
+  auto rnd = [&](uint32_t n) { seed = seed * 1664525u + 1013904223u; return (int64_t)((seed >> 8) % n); };
+  for (int c = 0; c < 20000; ++c) {
+    const int n = 1 + (int)rnd(FI_MAX_GROUP);
+    int64_t blocks[FI_MAX_GROUP], most[FI_MAX_GROUP], g[FI_MAX_GROUP], sum = 0, room = 0;
+    const int64_t same = 1 + rnd(3000), cut = 1 + rnd(8);
+    for (int i = 0; i < n; ++i) {
+      blocks[i] = c % 4 == 0 ? same : rnd(6) == 0 ? 0 : rnd(1 + (uint32_t)rnd(c % 3 ? 40 : 500000));
+      most[i] = (blocks[i] + cut - 1) / cut;
+    }
+    fi::share_workgroups(blocks, most, n, 256, g);
+    for (int i = 0; i < n; ++i) {
+      if (g[i] < (blocks[i] > 0) || g[i] > most[i]) { std::printf("share %d of case %d\n", i, c); return 1; }
+      sum += g[i]; room += most[i];
+    }
+    if (sum != (room < 256 ? room : 256)) { std::printf("case %d: %lld workgroups\n", c, (long long)sum); return 1; }
+    for (int i = 0; i < n; ++i)
+      for (int j = 0; j < n; ++j)   // no workgroup of j would shorten the share of i without making j's the longer one
+        if (g[i] && g[j] > 1 && g[i] < most[i] && blocks[i] * (g[j] - 1) > blocks[j] * (g[i] + 1) + blocks[i] * g[i]) { std::printf("case %d uneven\n", c); return 1; }
+  }
+  std::puts("ok");
+  return 0;
+}
+"""
+
+
+def test_workgroups_shared_among_the_problems_of_a_launch(tmp_path):
+    """share_workgroups: never more workgroups than compute units (three equal shares are 86, 85, 85), none without work."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("needs g++")
+    src, exe = tmp_path / "shares.cpp", tmp_path / "shares"
+    src.write_text(SHARES)
+    csrc = os.path.join(os.path.dirname(fi.LIB_PATH), "csrc")
+    subprocess.run([gxx, "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=undefined", "-I" + csrc, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout
