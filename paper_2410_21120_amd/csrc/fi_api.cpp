@@ -542,6 +542,11 @@ static void take_pool_launches(fi_dag* g) {
     if (X.root >= 0 || X.out_dtype != FI_BF16 || X.Cop != 64) continue;
     const uint64_t ys = P.root >= 0 ? (uint64_t)g->nodes[(size_t)P.root].Cop : 64;
     if (B * A.H * A.W * 128 >= (1ull << 31) || B * P.Ho * P.Wo * ys * 2 >= (1ull << 31)) continue;   // the kernel's 32-bit offsets
+    // Low images leave most of a 16 x 16 block empty.  The two launches -> this one (us): 2 x 4000, batch 8 29 -> 42; 4 x 4000, batch 16 51 -> 72;
+    // 6 x 2000, batch 16 43 -> 43; 8 x 2000, batch 8 39 -> 28.  With two blocks per compute unit at most nothing is lost: 2 x 1000, batch 8 20 -> 20,
+    // 4 x 1000 22 -> 20.
+    const uint64_t cells = (uint64_t)((A.H + 15) / 16) * ((A.W + 15) / 16);
+    if (cells * 256 * 4 > 9ull * A.H * A.W && cells * B * g->members.size() > 512) continue;
     P.pre = P.input;
     P.kind = K_CONV_POOL;
     P.tile = 0;

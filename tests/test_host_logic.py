@@ -144,6 +144,21 @@ def test_patch_launches_count_the_convolutions_they_carry():
     assert "conv_patch 256x64" in with_pointwise and "conv_mfma_256x128" in with_pointwise
 
 
+@pytest.mark.parametrize("h, w, batch, taken", [(2, 4000, 8, False), (4, 4000, 16, False), (6, 2000, 16, False), (8, 2000, 8, True), (9, 2000, 16, True), (2, 1000, 8, True), (224, 224, 64, True)])
+def test_low_images_keep_convolution_and_pool_apart(h, w, batch, taken):
+    """Blocks of 16 x 16 pixels: on low images the launch that holds a 64-channel 3x3 convolution and its 2x2 pool would compute mostly padding."""
+    m = zoo.Model("c", "bf16", 3, h, w)
+    a = m.add(zoo.CONV, -1, cin=3, cout=64, k=3, stride=1, pad=1, act=zoo.RELU)
+    a = m.add(zoo.CONV, a, cin=64, cout=64, k=3, stride=1, pad=1, act=zoo.RELU)
+    a = m.add(zoo.MAXPOOL, a, k=2, stride=2, pad=0)
+    m.add(zoo.CONV, a, cin=64, cout=16, k=1, stride=1, pad=0, act=zoo.NONE)
+    m.shapes()
+    blob = gen.make_blob(m, 1)
+    spec, keep = fi.make_spec(m, blob.ctypes.data, blob.nbytes)
+    names = [L.name.decode() for L in fi.Dag([spec], batch, fi.HostAllocators(), keepalive=(keep, blob)).launches()]
+    assert ("conv_pool" in names) == taken and ("maxpool" in names) != taken
+
+
 def test_the_convolution_and_pool_launch_leaves_room_for_swaps():
     """A DAG of one architecture takes VGG's second layer and its pool in one launch, one of two lanes does not: replacing a member by a smaller
     one of another architecture must not need more memory than the first plan (a swap into the loaded allocation would be refused)."""
