@@ -206,7 +206,9 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   __syncthreads();
 
-  const bool has_res = d.r_off != kNone, stream_out = (int64_t)M * d.Cop * AE > (int64_t)STREAM_OUT_BYTES;
+  // (the tile kernel's line, which counts two bytes an element for fp32 rows as well: 52 MB of fp32 rows, 4 x 160 x 160 x 128, written past the
+  // cache made the mean behind them take 400 us where it takes 256)
+  const bool has_res = d.r_off != kNone, stream_out = (int64_t)M * d.Cop * 2 > (int64_t)STREAM_OUT_BYTES;
   const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(
       a.abase + (has_res ? d.r_off : 0), 0, has_res ? (int)((int64_t)M * d.Cop * AE) : 0, 0x00020000);
   const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(
