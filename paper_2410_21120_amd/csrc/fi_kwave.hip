@@ -225,8 +225,8 @@ __global__ void __launch_bounds__(NW * 64) conv_kwave_kernel(KArgs a) {
 template <int C>
 __global__ void __launch_bounds__(256) conv_rgb_kernel(KArgs a) {
   extern __shared__ __attribute__((aligned(16))) float lds[];   // weights [k * kw * C][32], patch [PH][PW * C]
-  int p, bid;
-  if (!find_problem_at(a, (int)blockIdx.x, p, bid)) return;
+  int p, bid;   // (neighbouring rows on one die, as in the kernel above: the layer behind reads an image from its own die's cache: 8 x 112 x 112 x 32, the mean behind it 108 -> 54 us)
+  if (!find_problem_at(a, xcd_contiguous((int)blockIdx.x, (int)gridDim.x), p, bid)) return;
   const Desc d = a.d[p];
   const int slabs = (d.Co + 31) / 32, bw = (d.Wo + 15) / 16, bh = (d.Ho + 15) / 16;
   const int n0 = bid % slabs * 32;
