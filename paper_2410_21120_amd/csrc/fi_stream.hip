@@ -39,6 +39,14 @@ __device__ __forceinline__ bf16x8 affine_relu(u32x4 x, const u32x4 (&scale)[2], 
   return __builtin_bit_cast(bf16x8, h);
 }
 
+// Whether the output is written past the cache: from the tile kernel's size on, which counts two bytes an element for fp32 rows as well (52 MB
+// of them, 4 x 160 x 160 x 128, made the mean behind them take 400 us where it takes 256), and only rows that are whole lines of 128 bytes. Of the others
+// every line leaves in pieces: 40 -> 120 channels, bf16, 16384 blocks of 32 rows 65 us past the cache, 35 through it (43 on the tile), 32768 blocks of
+// fp32 rows, 96 -> 40 179 and 127 (121), 24 -> 72 183 and 93 (123).
+__device__ __forceinline__ bool past_the_cache(const Desc& d, int M, int es) {
+  return (int64_t)M * d.Cop * 2 > (int64_t)STREAM_OUT_BYTES && (((uint64_t)d.Cop * es | (uint64_t)d.ys * es | d.y_off) & 127) == 0;
+}
+
 // A lane holds, for pixel (lane & 31) of 32, runs of four consecutive channels: bias, residual, activation, the one rounding.
 template <bool WIDE, int NB>
 __device__ __forceinline__ void finish_rows(const Desc& d, const f32x16 (&acc)[NB], int row0, int n0, int lane, const float* bias, uint8_t* patch, const Activation<false>& act,
@@ -206,9 +214,7 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   __syncthreads();
 
-  // (the tile kernel's line, which counts two bytes an element for fp32 rows as well: 52 MB of fp32 rows, 4 x 160 x 160 x 128, written past the
-  // cache made the mean behind them take 400 us where it takes 256)
-  const bool has_res = d.r_off != kNone, stream_out = (int64_t)M * d.Cop * 2 > (int64_t)STREAM_OUT_BYTES;
+  const bool has_res = d.r_off != kNone, stream_out = past_the_cache(d, M, AE);
   const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(
       a.abase + (has_res ? d.r_off : 0), 0, has_res ? (int)((int64_t)M * d.Cop * AE) : 0, 0x00020000);
   const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(
@@ -376,7 +382,7 @@ __global__ void __launch_bounds__(LW * 64, 2) conv_long_kernel(KArgs a) {
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (nothing lands in LDS any more)
-  const bool has_res = d.r_off != kNone, stream_out = (int64_t)M * d.Cop * 2 > (int64_t)STREAM_OUT_BYTES;
+  const bool has_res = d.r_off != kNone, stream_out = past_the_cache(d, M, 2);
   const __amdgpu_buffer_rsrc_t rres = __builtin_amdgcn_make_buffer_rsrc(
       a.abase + (has_res ? d.r_off : 0), 0, has_res ? (int)((int64_t)M * d.Cop * 2) : 0, 0x00020000);
   const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(
