@@ -161,7 +161,7 @@ def main():
     # divided by the time during which at least one of its launches was running (the union of its
     # intervals): never more than the chip delivered, and an underestimate whenever a different
     # kernel shared the chip during that time.
-    launches = dag.launches()
+    launches = dag.launches(B)   # (the kernels that this pass issues)
     prof_iters = max(3, min(10, a.steps))
     per_kernel = {}
     def kname(L):   # one name per kernel template: the chains of two and of three are one kernel (chain_mfma_kernel)

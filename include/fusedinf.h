@@ -178,8 +178,9 @@ typedef struct {
   int32_t separate_stem;     /* 0: a 7x7 stride-2, 3x3 stride-1 or 3x3 stride-2 convolution over the model input with 64 output channels
                               * (the first layer of the ResNet-style families, of VGG, of SqueezeNet 1.1) runs from an input patch held on
                               * chip, and a 3x3 stride-2 max-pool (padding 0 or 1) that alone reads a stride-2 one runs in the same launch
-                              * (the convolution's output is stored nowhere); 1: the
-                              * general convolution kernel and a pooling launch of its own.  The outputs are the same bits either way. */
+                              * (the convolution's output is stored nowhere); a 3x3 stride-1 convolution of 64 to 64 channels on images wider than
+                              * 91 pixels (VGG's second layer) and the 2x2 stride-2 max-pool that alone reads it are one launch in DAGs of one lane;
+                              * 1: the general convolution kernels and pooling launches of their own.  The outputs are the same bits either way. */
   int32_t reserved0;
 } fi_build_opts;
 
@@ -225,11 +226,11 @@ typedef struct {
 
 typedef struct {
   int32_t level, kind, n_problems, first_node; /* kind: internal kernel family id */
-  int32_t lane, tile;        /* launch lane (stream); tile: which of the family's kernels runs, 0 where it has one (internal id, as kind) */
+  int32_t lane, tile;        /* launch lane (stream); tile: which of the kernels of that name it is, 0 where there is one (internal id, as kind) */
   uint64_t macs_per_image;   /* dense work of the launch */
   uint64_t bytes_per_image;  /* compulsory activation bytes (in + out + residual), per image */
   uint64_t weight_bytes;     /* weight + bias bytes read once per launch */
-  char name[32];             /* kernel family name, e.g. "conv_mfma_128x128" */
+  char name[32];             /* name of the kernel, e.g. "conv_mfma_128x128" */
 } fi_launch_info;
 
 /* Section IV, "DNN model repository": the repository keeps every model ready to
@@ -252,7 +253,10 @@ fi_status fi_model_pack(const fi_model_spec* model, void* dst, uint64_t dst_byte
 fi_status fi_build_dag(const fi_model_spec* models, int32_t n, const fi_build_opts* opts, fi_dag** out);
 fi_status fi_query(const fi_dag* dag, fi_dag_info* info);
 fi_status fi_node(const fi_dag* dag, int32_t i, fi_node_info* info);     /* i in [0, n_nodes) */
-fi_status fi_launch(const fi_dag* dag, int32_t i, fi_launch_info* info); /* i in [0, n_launches) */
+/* i in [0, n_launches): the launch as planned.  Launches of many rows are issued to kernels of their own where the images that a pass brings
+ * are enough (the outputs are the same bits); fi_launch_at names the kernel that a pass of `batch` images per member issues, 1 <= batch <= max_batch. */
+fi_status fi_launch(const fi_dag* dag, int32_t i, fi_launch_info* info);
+fi_status fi_launch_at(const fi_dag* dag, int32_t i, int32_t batch, fi_launch_info* info);
 fi_status fi_member(const fi_dag* dag, int32_t m, fi_member_info* info); /* m in [0, n_models) */
 
 /* The footprint fi_build_dag would report for these members (Section IV: the

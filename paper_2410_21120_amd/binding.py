@@ -99,7 +99,7 @@ class fi_launch_info(C.Structure):
                 ("lane", C.c_int32), ("tile", C.c_int32), ("macs_per_image", C.c_uint64), ("bytes_per_image", C.c_uint64), ("weight_bytes", C.c_uint64),
                 ("name", C.c_char * 32)]
 
-    # Tiles of the families whose name does not say which one runs, by internal id: rows x columns of a workgroup; "diag": only
+    # Tiles of the kernels whose name does not say which one runs, by internal id: rows x columns of a workgroup; "diag": only
     # the 32 x 32 blocks on the diagonal of grouped weights; x waves that share the reduction; "scalar": element-wise fetch.
     TILES = {b"conv_mfma_128x128": {5: "deep"},   # three reduction tiles in flight
              b"conv_patch": {0: "256x32", 1: "256x64", 2: "256x64 diag", 3: "512x128", 4: "512x64 diag"},
@@ -107,13 +107,13 @@ class fi_launch_info(C.Structure):
 
     @property
     def kernel(self):
-        """The family's name and, where the family has several kernels that the name leaves open, the tile."""
+        """The kernel's name and, where the name leaves open which one it is, the tile."""
         tile = self.TILES.get(self.name, {}).get(self.tile)
         return self.name.decode() + (" " + tile if tile else "")
 
 
 LIB_PATH = _build.OUT
-EXPORTS = ["fi_model_packed_size", "fi_model_pack", "fi_build_dag", "fi_footprint", "fi_partition", "fi_round_robin", "fi_query", "fi_node", "fi_launch", "fi_member", "fi_load",
+EXPORTS = ["fi_model_packed_size", "fi_model_pack", "fi_build_dag", "fi_footprint", "fi_partition", "fi_round_robin", "fi_query", "fi_node", "fi_launch", "fi_launch_at", "fi_member", "fi_load",
            "fi_run", "fi_run_static", "fi_run_inputs", "fi_run_batches", "fi_run_lane", "fi_profile", "fi_timeline", "fi_swap_model", "fi_server_start", "fi_server_submit", "fi_server_wait", "fi_server_query", "fi_server_swap", "fi_server_stop",
            "fi_unload", "fi_destroy", "fi_last_error", "fi_version"]
 _lib = None
@@ -137,6 +137,7 @@ def lib():
         L.fi_query.argtypes = [vp, C.POINTER(fi_dag_info)]
         L.fi_node.argtypes = [vp, i32, C.POINTER(fi_node_info)]
         L.fi_launch.argtypes = [vp, i32, C.POINTER(fi_launch_info)]
+        L.fi_launch_at.argtypes = [vp, i32, i32, C.POINTER(fi_launch_info)]
         L.fi_load.argtypes = [vp, vp]
         L.fi_run.argtypes = [vp, vp, i32, C.POINTER(vp), vp]
         L.fi_run_static.argtypes = [vp, vp, i32, C.POINTER(vp), vp]
@@ -267,6 +268,12 @@ def fi_node(h, i) -> fi_node_info:
 def fi_launch(h, i) -> fi_launch_info:
     info = fi_launch_info()
     _check(lib().fi_launch(h, i, C.byref(info)), "fi_launch")
+    return info
+
+
+def fi_launch_at(h, i, batch) -> fi_launch_info:
+    info = fi_launch_info()
+    _check(lib().fi_launch_at(h, i, batch, C.byref(info)), "fi_launch_at")
     return info
 
 
@@ -489,8 +496,9 @@ class Dag:
     def nodes(self):
         return [fi_node(self.h, i) for i in range(self.query().n_nodes)]
 
-    def launches(self):
-        return [fi_launch(self.h, i) for i in range(self.query().n_launches)]
+    def launches(self, batch=None):
+        """The schedule as planned; with a batch, the kernels that a pass of so many images per member issues."""
+        return [fi_launch(self.h, i) if batch is None else fi_launch_at(self.h, i, batch) for i in range(self.query().n_launches)]
 
     def members(self):
         return [fi_member(self.h, m) for m in range(self.n_models)]

@@ -1450,11 +1450,26 @@ fi_status fi_launch(const fi_dag* g, int32_t i, fi_launch_info* o) {
   if (!g || !o || i < 0 || i >= (int32_t)g->launches.size()) { set_error("bad launch index"); return FI_EINVAL; }
   const Launch& L = g->launches[(size_t)i];
   std::memset(o, 0, sizeof(*o));
-  o->lane = L.lane; o->tile = L.kind == K_CONV_KWAVE ? L.tile & ~KW_RGB : L.tile;
+  const bool rgb = L.kind == K_CONV_KWAVE && (L.tile & KW_RGB);   // (a kernel of its own, which has no tile)
+  o->lane = L.lane; o->tile = rgb ? 0 : L.tile;
   o->level = L.level; o->kind = L.kind; o->n_problems = L.n;
   o->first_node = (L.nodes.empty() || L.kind == K_STAGE) ? -1 : L.nodes[0];
   o->macs_per_image = L.macs; o->bytes_per_image = L.act_bytes; o->weight_bytes = L.weight_bytes;
-  std::snprintf(o->name, sizeof(o->name), "%s", L.name.c_str());
+  std::snprintf(o->name, sizeof(o->name), "%s", rgb ? "conv_rgb" : L.name.c_str());
+  return FI_OK;
+}
+
+fi_status fi_launch_at(const fi_dag* g, int32_t i, int32_t batch, fi_launch_info* o) {
+  if (g && (batch < 1 || batch > g->opts.max_batch)) { set_error("batch %d outside [1, %d]", batch, g->opts.max_batch); return FI_EINVAL; }
+  const fi_status st = fi_launch(g, i, o);
+  if (st != FI_OK) return st;
+  const Launch& L = g->launches[(size_t)i];
+  int32_t batches[FI_MAX_GROUP];
+  std::fill(batches, batches + FI_MAX_GROUP, batch);
+  const int32_t route = choose_route(L, g->descs.data() + L.first_desc, batches).route;
+  if (route == R_FAMILY) return FI_OK;
+  o->tile = 0;
+  std::snprintf(o->name, sizeof(o->name), "%s", route == R_STREAM ? "conv_stream" : route == R_LONG ? "conv_long" : "dwconv_rows");
   return FI_OK;
 }
 

@@ -235,11 +235,21 @@ int launch_chain(const Launch& L, const KArgs& a, void* stream, const std::vecto
 // Implemented in fi_kwave.hip: a K_CONV_KWAVE launch.  Returns a hipError_t as int.
 int launch_kwave(const Launch& L, const KArgs& a, void* stream, const std::vector<Desc>& host_descs);
 
-// Implemented in fi_stream.hip: a K_CONV_MFMA launch of pointwise convolutions whose rows stream (descriptors and batches filled in).
-// stream_fits says whether a launch is one, and with which blocks of columns and pieces of a row launch_stream takes it.
-bool stream_fits(const Launch& L, const KArgs& a, int* nb, int* nch);
+// Kernels that a launch is issued to in place of its family's where the batches of the pass allow it.  They give the same bits, so the choice may look
+// at the launch and is made when the pass is issued.  Implemented in fi_plan.cpp (d, batch: the launch's problems and their images).
+enum Route : int32_t { R_FAMILY = 0, R_STREAM, R_LONG, R_DW_ROWS };
+struct Choice {
+  int32_t route;
+  int32_t nb, nch;   // R_STREAM: 32-column blocks of the output, 128-byte pieces of an input row
+};
+Choice choose_route(const Launch& L, const Desc* d, const int32_t* batch);
+inline int64_t dw_rows_blocks(const Desc& d, int batch) {   // workgroups of a problem on the R_DW_ROWS kernel: a thread has two rows of four outputs, eight channels
+  return ((int64_t)batch * ((d.Ho + 1) / 2) * ((d.Wo + 3) / 4) * (d.Cop / 8) + 255) / 256;
+}
+constexpr int32_t STREAM_WAVES = 8, LONG_WAVES = 4, LONG_K = 1792;   // waves of a workgroup (32 rows each); the longest row of the R_LONG kernel
+
+// Implemented in fi_stream.hip: a K_CONV_MFMA launch whose route is R_STREAM / R_LONG (descriptors and batches filled in).
 int launch_stream(const Launch& L, const KArgs& a, int nb, int nch, void* stream);
-bool long_fits(const Launch& L, const KArgs& a);   // ... or of rows of any length behind an affine stage
 int launch_long(const Launch& L, const KArgs& a, void* stream);
 
 // Implemented in fi_patch.hip: a K_CONV_PATCH launch.  Returns a hipError_t as int.

@@ -1391,8 +1391,7 @@ __global__ void __launch_bounds__(256) dwconv_strip_kernel(KArgs a) {
 
 // 3x3 stride 1, two rows of four outputs per thread: the four input rows are loaded once (three pixels per output instead of four and a
 // half).  Bound: the vector cache's loads.  fp32 rows, two members at batch 32, strip kernel -> this one: 112 x 112 x 16 39.5 -> 35.0 us, 56 x 56 x 72 40.5 ->
-// 37.8, 14 x 14 x 672 29.2 -> 25.9.  From 384 workgroups on (14 x 14 x 480, 420 workgroups 22.8 -> 20.0); below, half as many threads leave the
-// chip idle (14 x 14 x 200, 175 workgroups 15.3 -> 18.5).  Every output adds its taps in the strip kernel's order: the same bits.
+// 37.8, 14 x 14 x 672 29.2 -> 25.9.  Every output adds its taps in the strip kernel's order: the same bits.
 template <typename TA>
 __global__ void __launch_bounds__(256) dwconv_block_kernel(KArgs a) {
   constexpr int S = 4, NPIX = S + 2;
@@ -1801,6 +1800,7 @@ int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::v
                          ((L.kind == K_MAXPOOL || L.kind == K_AVGPOOL || L.kind == K_GATHER) && t.vec));
     if ((t.xs != t.Cp && !reads) || (t.ys != t.Cop && !writes)) return (int)hipErrorInvalidValue;
   }
+  const Choice choice = choose_route(L, a.d, a.batch);
   switch (L.kind) {
     case K_STAGE:
       if (wb && ab) return go(stage_kernel<bf16_t, bf16_t>, nb, 256, a, s);
@@ -1810,11 +1810,8 @@ int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::v
       return wb ? (int)hipErrorInvalidValue : go(conv_direct_kernel, nb, 256, a, s);
     case K_CONV_MFMA:
       if (!wb) return (int)hipErrorInvalidValue;
-      {   // many rows and a short reduction: they stream (the same bits, so the choice is made for the batches of this pass)
-        int cols = 0, pieces = 0;
-        if (stream_fits(L, a, &cols, &pieces)) return launch_stream(L, a, cols, pieces, stream);
-        if (long_fits(L, a)) return launch_long(L, a, stream);
-      }
+      if (choice.route == R_STREAM) return launch_stream(L, a, choice.nb, choice.nch, stream);
+      if (choice.route == R_LONG) return launch_long(L, a, stream);
       if (hd[(size_t)L.first_desc].Cp == 4) {  // 4-channel model input
         if (!ab) {
           if (L.tile == T_128x128) return go(conv_mfma_kernel<T_128x128, 128, 128, 2, 2, true, true>, nb, 256, a, s);
@@ -1888,18 +1885,13 @@ int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::v
       const bool vec = hd[(size_t)L.first_desc].vec != 0;
       if (vec && hd[(size_t)L.first_desc].tiles_n > 1) {   // the planner found one filter size and stride for the whole launch
         const int ks = hd[(size_t)L.first_desc].k, st = hd[(size_t)L.first_desc].stride;
-        if (ks == 3 && st == 1) {
-          bool plain = true;
-          int64_t blocks2 = 0;
-          KArgs a2 = a;
+        if (choice.route == R_DW_ROWS) {
+          int64_t rows = 0;
           for (int i = 0; i <= FI_MAX_GROUP; ++i) {
-            a2.first_block[i] = (int32_t)blocks2;
-            if (i >= L.n) continue;
-            const Desc& t = a.d[i];
-            plain = plain && t.r_off == kNone && !t.ext && t.Co == t.Cop;
-            blocks2 += ((int64_t)a.batch[i] * ((t.Ho + 1) / 2) * ((t.Wo + 3) / 4) * (t.Cop / 8) + 255) / 256;
+            a.first_block[i] = (int32_t)rows;
+            if (i < L.n) rows += dw_rows_blocks(a.d[i], a.batch[i]);
           }
-          if (plain && blocks2 >= 384) return ab ? go(dwconv_block_kernel<bf16_t>, (int)blocks2, 256, a2, s) : go(dwconv_block_kernel<float>, (int)blocks2, 256, a2, s);
+          return ab ? go(dwconv_block_kernel<bf16_t>, (int)rows, 256, a, s) : go(dwconv_block_kernel<float>, (int)rows, 256, a, s);
         }
 #define FI_DW_STRIP(K, T) if (ks == K && st == T) return ab ? go(dwconv_strip_kernel<bf16_t, K, T>, nb, 256, a, s) : go(dwconv_strip_kernel<float, K, T>, nb, 256, a, s);
         FI_DW_STRIP(3, 1) FI_DW_STRIP(3, 2) FI_DW_STRIP(5, 1) FI_DW_STRIP(5, 2) FI_DW_STRIP(7, 1) FI_DW_STRIP(7, 2)

@@ -295,4 +295,80 @@ void pack_model(const fi_model_spec& m, const ModelPlan& p, uint8_t* dst) {
   else pack_typed<uint32_t>(m, p, dst);
 }
 
+// ---------------------------------------------------------------------------------
+// Choices of a pass: kernels that take a launch from its family's, by the batches that the members bring
+// ---------------------------------------------------------------------------------
+
+// What the streaming kernels compute and address; `past`: rows past the last whose offsets they form.
+static bool streams(const Desc& t, int batch, bool wide, int past) {
+  const int es = wide ? 4 : 2;
+  const int64_t m = (int64_t)batch * t.Ho * t.Wo, ys = t.ys > t.Cop ? t.ys : t.Cop;
+  if (t.Cp == 4)   // 3x3 over the four-channel staged input
+    return batch >= 0 && t.k == 3 && t.kw == 3 && t.stride >= 1 && t.gin == 0 && t.pre_kind == 0 && t.splits == 1 && !t.ext && !t.out_f32 && t.xs == 4 && t.Kp == 64 && t.Co == t.Cop &&
+           t.Cop % 8 == 0 && t.ys % (16 / es) == 0 && (t.act <= FI_ACT_RELU6 || t.act == FI_ACT_HARDSWISH) && m < (1 << 24) - 1024 &&
+           (int64_t)batch * t.H * t.W * 4 * es < (1ll << 31) && (m + past) * ys * es < (1ll << 31);
+  if (batch < 0 || t.k != 1 || t.kw != 1 || t.stride != 1 || t.pad != 0 || t.pad_w != 0 || t.gin > 0 || t.splits != 1 || t.ext || t.out_f32) return false;
+  if (t.pre_kind > 1 || (t.pre_kind == 1 && (wide || t.pre_act != FI_ACT_RELU)) || (t.pre_kind == 0 && t.xs != t.Cp)) return false;
+  if (t.act > FI_ACT_RELU6 && t.act != FI_ACT_HARDSWISH) return false;
+  if (t.Cp % 8 || t.Co != t.Cop || t.Cop % 8 || t.ys % (16 / es) || t.xs % (16 / es) || t.Kp < t.Cp || t.Kp % 8) return false;
+  return m < (1 << 24) && (m + past) * t.xs * es < (1ll << 31) && (m + past) * ys * es < (1ll << 31) && ((int64_t)t.Co + 128) * t.Kp * 2 < (1ll << 31);
+}
+
+// Whether a launch of pointwise convolutions streams, and with which blocks of columns and pieces of a row.  Rows enough to pay for the weights
+// that every workgroup loads first: 512 blocks of 32 rows, from three pieces on
+// 256 per piece.  4x MobileNetV3-Large at batch 32 1912 us without this kernel, 1824 / 1815 / 1807 from 2048 / 1024 / 512 blocks on (28 x 28
+// layers of one to four pieces); 4x DenseNet-121 2972, 2855 / 2851 / 2873 (the 14 x 14 layers of four to six pieces lose).
+static bool stream_fits(const Launch& L, const Desc* d, const int32_t* batch, Choice* c) {
+  const bool wide = L.adtype != FI_BF16;
+  const int ce = wide ? 32 : 64;   // elements of a 128-byte piece
+  int64_t tiles = 0;
+  int cop = 0, pieces = 0;
+  auto form = [](const Desc& t) { return t.Cp == 4 ? 2 : t.pre_kind; };   // (the kernel's PRE)
+  for (int i = 0; i < L.n; ++i) {
+    const Desc& t = d[i];
+    const int64_t m = (int64_t)batch[i] * t.Ho * t.Wo;
+    if (!streams(t, batch[i], wide, 2 * STREAM_WAVES * 32) || form(t) != form(d[0])) return false;
+    tiles += (m + 31) / 32;
+    cop = std::max(cop, t.Cop);
+    pieces = std::max(pieces, ((t.Cp == 4 ? 36 : t.Cp) + ce - 1) / ce);
+  }
+  if (tiles < 512 || tiles < 256 * pieces || pieces > 6 || cop > 128) return false;
+  c->nb = form(d[0]) == 1 || cop > 64 ? 4 : cop > 32 ? 2 : 1;
+  c->nch = pieces <= 4 ? pieces : 6;
+  return true;
+}
+
+// Whether a launch is one of affine stages and rows of any length.  From 128
+// workgroups on: fewer leave the chip idle (7 x 7, 640 channels, four members, 52 workgroups 17.0 us on the tile, 19.7 here).
+static bool long_fits(const Launch& L, const Desc* d, const int32_t* batch) {
+  constexpr int rows = LONG_WAVES * 32;
+  int64_t blocks = 0;
+  for (int i = 0; i < L.n; ++i) {
+    const Desc& t = d[i];
+    if (!streams(t, batch[i], L.adtype != FI_BF16, rows) || t.pre_kind != 1 || t.Cp > LONG_K) return false;
+    blocks += ((int64_t)batch[i] * t.Ho * t.Wo + rows - 1) / rows * ((t.Cop + 127) / 128);
+  }
+  return blocks >= 128;
+}
+
+// Whether a depthwise launch computes two rows of four outputs per thread (3x3, stride 1): from 384 workgroups on (14 x 14 x 480, 420 workgroups
+// 22.8 -> 20.0 us); below, half as many threads leave the chip idle (14 x 14 x 200, 175 workgroups 15.3 -> 18.5).
+static bool two_rows_fit(const Launch& L, const Desc* d, const int32_t* batch) {
+  int64_t blocks = 0;
+  for (int i = 0; i < L.n; ++i) {
+    const Desc& t = d[i];
+    if (!t.vec || t.tiles_n != 4 || t.k != 3 || t.stride != 1 || t.r_off != kNone || t.ext || t.Co != t.Cop) return false;
+    blocks += dw_rows_blocks(t, batch[i]);
+  }
+  return blocks >= 384;
+}
+
+Choice choose_route(const Launch& L, const Desc* d, const int32_t* batch) {
+  Choice c{R_FAMILY, 0, 0};
+  if (L.wdtype != FI_BF16 || L.n < 1) return c;
+  if (L.kind == K_CONV_MFMA) c.route = stream_fits(L, d, batch, &c) ? R_STREAM : long_fits(L, d, batch) ? R_LONG : R_FAMILY;
+  else if (L.kind == K_DWCONV && two_rows_fit(L, d, batch)) c.route = R_DW_ROWS;
+  return c;
+}
+
 }  // namespace fi

@@ -24,7 +24,7 @@
 namespace fi {
 namespace {
 
-constexpr int SW = 8;   // waves of a workgroup
+constexpr int SW = STREAM_WAVES;
 
 // max(x * scale + shift, 0) of eight channels: product and sum rounded separately, one rounding to bf16 (the depthwise kernel's operations).
 __device__ __forceinline__ bf16x8 affine_relu(u32x4 x, const u32x4 (&scale)[2], const u32x4 (&shift)[2]) {
@@ -282,7 +282,7 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
 // 64 channels), the rows four pieces ahead in registers, scale and shift as tables in LDS, read before the barrier.  Bound: what a compute unit takes
 // from L2 (32 KB per piece in 0.9 us).  DenseNet-121, four members at batch 32, 14 x 14, 288 / 480 / 672 / 960 -> 128 channels: 17.2 / 22.0 / 26.0 / 32.0 us on the
 // 128x64 tile, 15.2 / 18.2 / 21.3 / 25.0 here.
-constexpr int LW = 4, LK = 1792;   // waves of a workgroup, the longest reduction (its tables leave room for two workgroups per compute unit)
+constexpr int LW = LONG_WAVES, LK = LONG_K;   // (the tables of the longest row leave room for two workgroups per compute unit)
 
 __global__ void __launch_bounds__(LW * 64, 2) conv_long_kernel(KArgs a) {
   constexpr int NB = 4, BN = 128, NS = 3, STAGE = BN * 128, D = 4;   // columns; stages of the weights' ring; pieces of a row in registers
@@ -399,36 +399,6 @@ int go_stream(int blocks, const KArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// What both kernels compute and address; `past`: rows past the last whose offsets they form.
-static bool streams(const Desc& t, int batch, bool wide, int past) {
-  const int es = wide ? 4 : 2;
-  const int64_t m = (int64_t)batch * t.Ho * t.Wo, ys = t.ys > t.Cop ? t.ys : t.Cop;
-  if (t.Cp == 4)   // 3x3 over the four-channel staged input
-    return batch >= 0 && t.k == 3 && t.kw == 3 && t.stride >= 1 && t.gin == 0 && t.pre_kind == 0 && t.splits == 1 && !t.ext && !t.out_f32 && t.xs == 4 && t.Kp == 64 && t.Co == t.Cop &&
-           t.Cop % 8 == 0 && t.ys % (16 / es) == 0 && (t.act <= FI_ACT_RELU6 || t.act == FI_ACT_HARDSWISH) && m < (1 << 24) - 1024 &&
-           (int64_t)batch * t.H * t.W * 4 * es < (1ll << 31) && (m + past) * ys * es < (1ll << 31);
-  if (batch < 0 || t.k != 1 || t.kw != 1 || t.stride != 1 || t.pad != 0 || t.pad_w != 0 || t.gin > 0 || t.splits != 1 || t.ext || t.out_f32) return false;
-  if (t.pre_kind > 1 || (t.pre_kind == 1 && (wide || t.pre_act != FI_ACT_RELU)) || (t.pre_kind == 0 && t.xs != t.Cp)) return false;
-  if (t.act > FI_ACT_RELU6 && t.act != FI_ACT_HARDSWISH) return false;
-  if (t.Cp % 8 || t.Co != t.Cop || t.Cop % 8 || t.ys % (16 / es) || t.xs % (16 / es) || t.Kp < t.Cp || t.Kp % 8) return false;
-  return m < (1 << 24) && (m + past) * t.xs * es < (1ll << 31) && (m + past) * ys * es < (1ll << 31) && ((int64_t)t.Co + 128) * t.Kp * 2 < (1ll << 31);
-}
-
-static int stream_pre(const Desc& t) { return t.Cp == 4 ? 2 : t.pre_kind; }   // (the kernel's PRE)
-
-// Whether a launch is one of affine stages and rows of any length.  (The bits are the tile kernel's: the rule may look at the launch.)  From 128
-// workgroups on: fewer leave the chip idle (7 x 7, 640 channels, four members, 52 workgroups 17.0 us on the tile, 19.7 here).
-bool long_fits(const Launch& L, const KArgs& a) {
-  int64_t blocks = 0;
-  for (int i = 0; i < L.n; ++i) {
-    const Desc& t = a.d[i];
-    const int64_t m = (int64_t)a.batch[i] * t.Ho * t.Wo;
-    if (!streams(t, a.batch[i], L.adtype != FI_BF16, LW * 32) || t.pre_kind != 1 || t.Cp > LK) return false;
-    blocks += (m + LW * 32 - 1) / (LW * 32) * ((t.Cop + 127) / 128);
-  }
-  return blocks >= 128;
-}
-
 int launch_long(const Launch& L, const KArgs& args, void* stream) {
   KArgs a = args;
   int64_t blocks = 0;
@@ -440,31 +410,6 @@ int launch_long(const Launch& L, const KArgs& args, void* stream) {
   if (blocks <= 0) return (int)hipSuccess;
   hipLaunchKernelGGL(conv_long_kernel, dim3((unsigned)blocks), dim3(LW * 64), 0, static_cast<hipStream_t>(stream), a);
   return (int)hipGetLastError();
-}
-
-// Whether a launch of pointwise convolutions streams, and with which blocks of columns and pieces of a row.  (The rule may look at the
-// launch: the bits are the tile kernel's.)  Rows enough to pay for the weights that every workgroup loads first: 512 blocks of 32 rows, from three pieces on
-// 256 per piece.  4x MobileNetV3-Large at batch 32 1912 us without this kernel, 1824 / 1815 / 1807 from 2048 / 1024 / 512 blocks on (28 x 28
-// layers of one to four pieces); 4x DenseNet-121 2972, 2855 / 2851 / 2873 (the 14 x 14 layers of four to six pieces lose).
-bool stream_fits(const Launch& L, const KArgs& a, int* nb, int* nch) {
-  const bool wide = L.adtype != FI_BF16;
-  const int es = wide ? 4 : 2, ce = 128 / es;
-  int64_t tiles = 0;
-  int cop = 0, pieces = 0;
-  const int pre = stream_pre(a.d[0]);
-  for (int i = 0; i < L.n; ++i) {
-    const Desc& t = a.d[i];
-    const int64_t m = (int64_t)a.batch[i] * t.Ho * t.Wo;
-    if (!streams(t, a.batch[i], wide, 2 * SW * 32) || stream_pre(t) != pre) return false;
-    tiles += (m + 31) / 32;
-    cop = cop > t.Cop ? cop : t.Cop;
-    const int k = t.Cp == 4 ? 36 : t.Cp;
-    pieces = pieces > (k + ce - 1) / ce ? pieces : (k + ce - 1) / ce;
-  }
-  if (tiles < 512 || tiles < 256 * pieces || pieces > 6 || cop > 128) return false;
-  *nb = pre == 1 || cop > 64 ? 4 : cop > 32 ? 2 : 1;
-  *nch = pieces <= 4 ? pieces : 6;
-  return true;
 }
 
 int launch_stream(const Launch& L, const KArgs& args, int nb, int nch, void* stream) {
@@ -483,7 +428,7 @@ int launch_stream(const Launch& L, const KArgs& args, int nb, int nch, void* str
   for (int i = L.n; i <= FI_MAX_GROUP; ++i) a.first_block[i] = (int32_t)blocks;
   const int n = (int)blocks;
   const bool wide = L.adtype != FI_BF16;
-  const int pre = stream_pre(a.d[0]);
+  const int pre = a.d[0].Cp == 4 ? 2 : a.d[0].pre_kind;
   if (pre == 2) {
 #define FI_GATHER(NB) if (nb == (NB)) return wide ? go_stream<true, 2, NB, 2>(n, a, s) : go_stream<false, 2, NB, 1>(n, a, s);
     FI_GATHER(1) FI_GATHER(2) FI_GATHER(4)

@@ -273,6 +273,11 @@ bool exercise(std::vector<Model>& members, Rng& r, uint64_t seed, bool must_comp
       const fi_status st = fi_launch(dag, i, &li);
       check((st == FI_OK) == (i >= 0 && i < info.n_launches), "fi_launch range check", seed);
       if (st == FI_OK) check(li.n_problems >= 1 && li.n_problems <= FI_MAX_GROUP && li.lane >= 0 && li.lane < info.n_lanes, "launch fields out of range", seed);
+      for (int32_t b : {0, 1, opts.max_batch, opts.max_batch + 1}) {
+        fi_launch_info at{};
+        check((fi_launch_at(dag, i, b, &at) == FI_OK) == (st == FI_OK && b >= 1 && b <= opts.max_batch), "fi_launch_at range check", seed);
+        if (st == FI_OK && b == 1) check(at.kind == li.kind && at.n_problems == li.n_problems && at.macs_per_image == li.macs_per_image, "fi_launch_at is another launch", seed);
+      }
     }
     for (int32_t i = -1; i <= info.n_models; ++i) {
       fi_member_info mi{};

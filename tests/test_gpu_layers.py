@@ -96,7 +96,7 @@ def test_conv_f32_patch_of_few_channels(case):
     m = zoo.Model("c", "f32", cin, h, w)
     a = m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.NONE)
     m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, stride=s, pad=p, act=zoo.HARDSWISH, residual=a)
-    _run_case(m, 940 + cin + cout, b, tol=2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23)
+    _run_case(m, 940 + cin + cout, b, tol=2.0 * (cin * k * k) ** 0.5 * 2.0 ** -23, kernels=[("conv_rgb", 2)])
 
 
 def test_conv_f32_few_channel_siblings():
@@ -107,10 +107,10 @@ def test_conv_f32_few_channel_siblings():
     t = wide[0]
     for w in wide[1:]:
         t = m.add(zoo.CONCAT, t, residual=w)
-    _run_case(m, 950, 4, tol=2.0 * ((9 * 3) ** 0.5 + 3 ** 0.5) * 2.0 ** -23)   # (the roundings of both layers)
+    _run_case(m, 950, 4, tol=2.0 * ((9 * 3) ** 0.5 + 3 ** 0.5) * 2.0 ** -23, kernels=[("conv_rgb", 4)])   # (the roundings of both layers)
 
 
-@pytest.mark.parametrize("case", [(64, 40, 3, 1, 1, 61, 57, 4, "64x64x4"), (3, 64, 7, 2, 3, 161, 157, 4, "64x64x4 scalar"),
+@pytest.mark.parametrize("case", [(64, 40, 3, 1, 1, 61, 57, 4, "64x64x4"), (3, 64, 7, 2, 3, 161, 157, 4, "rgb"), (5, 64, 7, 2, 3, 161, 157, 4, "64x64x4 scalar"),
                                   (5, 33, 3, 1, 1, 9, 11, 1, "32x32x8 scalar"), (36, 31, 5, 2, 2, 9, 11, 1, "32x32x8")])
 def test_conv_f32_weights_that_are_not_finite(case):
     """Infinite and NaN weights reach the outputs whose window holds their tap, and no output at the border where the tap
@@ -128,7 +128,7 @@ def test_conv_f32_weights_that_are_not_finite(case):
     x = gen.make_input(72, b, cin, h, w, "normal", "f32")
     g = harness.GpuDag([(m, blob, None)], b)
     try:
-        assert "conv_kwave " + tile in [L.kernel for L in g.dag.launches()]
+        assert ("conv_rgb" if tile == "rgb" else "conv_kwave " + tile) in [L.kernel for L in g.dag.launches()]
         y = g.run(x)[0]
     finally:
         g.close()

@@ -91,7 +91,7 @@ def test_grouping_reduces_launches_only():
 @pytest.mark.parametrize("layer, kernel", [
     ((1, 1, 3, 1, 1024, 1), "conv_direct"), ((1, 8, 3, 1, 512, 1), "conv_direct"), ((3, 3, 1, 0, 512, 1), "conv_direct"), ((2, 2, 1, 0, 256, 2), "conv_direct"),
     ((4, 4, 1, 0, 256, 4), "conv_direct"), ((8, 8, 1, 0, 256, 4), "conv_direct"),
-    ((3, 64, 7, 3, 224, 1), "conv_kwave 64x64x4 scalar"), ((16, 16, 3, 1, 128, 4), "conv_kwave 64x64x4"), ((16, 96, 1, 0, 112, 8), "conv_kwave 64x64x4"),
+    ((3, 64, 7, 3, 224, 1), "conv_rgb"), ((5, 64, 7, 3, 224, 1), "conv_kwave 64x64x4 scalar"), ((16, 16, 3, 1, 128, 4), "conv_kwave 64x64x4"), ((16, 96, 1, 0, 112, 8), "conv_kwave 64x64x4"),
     ((32, 1, 5, 2, 256, 1), "conv_kwave 64x64x4"), ((3, 16, 3, 1, 32, 1), "conv_kwave 32x32x8 scalar"), ((256, 2, 1, 0, 64, 4), "conv_kwave 64x64x4"),
     ((16, 8, 5, 2, 4096, 1), "conv_direct")])   # (2^24 rows: more than the matrix kernel decodes)
 def test_fp32_layers_of_few_products_keep_the_element_kernel(layer, kernel):
