@@ -262,14 +262,18 @@ def test_conv_patch_has_the_bits_of_the_tile_kernel(case):
     assert np.isfinite(_same_bits(m, few, many, small, "conv_patch " + tile)[2]).all()
 
 
-def _bits_and_parity(m, act_dtype, few, many, seed=71):
-    """The first images of a batch of `many` have the bits that a batch of `few` gives them, and meet the oracle."""
+def _bits_and_parity(m, act_dtype, few, many, seed=71, kernel=None, n=1):
+    """The first images of a batch of `many`, n of whose launches are issued to `kernel`, have the bits that a batch of `few`, none of whose are,
+    gives them, and meet the oracle."""
     from tests import harness
     m.shapes()
     blob = gen.make_blob(m, seed, bias_std=0.1)
     x = gen.make_input(seed + 1, many, m.in_c, m.in_h, m.in_w, "normal", m.dtype)
     g = harness.GpuDag([(m, blob, act_dtype)], many)
     try:
+        if kernel:
+            names = {b: [L.name.decode() for L in g.dag.launches(b)] for b in (few, many)}
+            assert names[many].count(kernel) == n and kernel not in names[few], names
         large, small = g.run(x)[0], g.run(x[:few])[0]
     finally:
         g.close()
@@ -304,14 +308,14 @@ def test_first_layers_that_stream(cout, stride, pad, act_dtype):
     _bits_and_parity(m, act_dtype, 1, 6)
 
 
-@pytest.mark.parametrize("h, w, c, pad, act_dtype, many", [(61, 53, 160, 1, None, 12), (60, 50, 136, 0, "f32", 18), (33, 30, 248, 1, "f32", 24)])
+@pytest.mark.parametrize("h, w, c, pad, act_dtype, many", [(61, 53, 160, 1, None, 12), (61, 53, 160, 1, "f32", 12), (60, 50, 136, 0, "f32", 18), (33, 30, 248, 1, "f32", 24)])
 def test_depthwise_two_rows_per_thread(h, w, c, pad, act_dtype, many):
-    """3x3 stride-1 depthwise layers of 384 workgroups or more compute two rows per thread; one image keeps one row: the same bits."""
+    """3x3 stride-1 depthwise layers of 384 workgroups or more, fp32 rows, compute two rows per thread; one image and bf16 rows keep one: the same bits."""
     m = zoo.Model("c", "bf16", 8, h, w)
     a = m.add(zoo.CONV, -1, cin=8, cout=c, k=1, stride=1, pad=0, act=zoo.RELU)
     a = m.add(zoo.DWCONV, a, cin=c, cout=c, k=3, stride=1, pad=pad, act=zoo.HARDSWISH if c == 160 else zoo.RELU6)
     m.add(zoo.MAXPOOL, a, k=1, stride=1, pad=0)
-    _bits_and_parity(m, act_dtype, 1, many)
+    _bits_and_parity(m, act_dtype, 1, many, kernel="dwconv_rows", n=1 if act_dtype else 0)
 
 
 # 16 images: 1617 blocks of 32 rows; 6 images: 607, too few for resident weights from three pieces of 64 channels on; 440 channels are seven pieces
