@@ -243,6 +243,17 @@ struct Choice {
   int32_t nb, nch;   // R_STREAM: 32-column blocks of the output, 128-byte pieces of an input row
 };
 Choice choose_route(const Launch& L, const Desc* d, const int32_t* batch);
+// The streaming kernels that are built: fp32 rows, form (0 plain, 1 an affine stage, 2 3x3 over the four-channel input), nb, nch.
+#define FI_STREAM_FORMS(X)                                                                           \
+  X(false, 0, 1, 1) X(false, 0, 1, 2) X(false, 0, 1, 3) X(false, 0, 1, 4) X(false, 0, 1, 6)          \
+  X(false, 0, 2, 1) X(false, 0, 2, 2) X(false, 0, 2, 3)                                              \
+  X(false, 0, 4, 1) X(false, 0, 4, 2) X(false, 0, 4, 3) X(false, 0, 4, 4)                            \
+  X(false, 1, 4, 1) X(false, 1, 4, 2) X(false, 1, 4, 3) X(false, 1, 4, 4) X(false, 1, 4, 6)          \
+  X(false, 2, 1, 1) X(false, 2, 2, 1) X(false, 2, 4, 1)                                              \
+  X(true, 0, 1, 1) X(true, 0, 1, 2) X(true, 0, 1, 3) X(true, 0, 1, 4) X(true, 0, 1, 6)               \
+  X(true, 0, 2, 1) X(true, 0, 2, 2)                                                                  \
+  X(true, 0, 4, 1) X(true, 0, 4, 2) X(true, 0, 4, 3) X(true, 0, 4, 4) X(true, 0, 4, 6)               \
+  X(true, 2, 1, 2) X(true, 2, 2, 2) X(true, 2, 4, 2)
 inline int64_t dw_rows_blocks(const Desc& d, int batch) {   // workgroups of a problem on the R_DW_ROWS kernel: a thread has two rows of four outputs, eight channels
   return ((int64_t)batch * ((d.Ho + 1) / 2) * ((d.Wo + 3) / 4) * (d.Cop / 8) + 255) / 256;
 }

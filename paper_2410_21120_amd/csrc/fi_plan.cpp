@@ -314,15 +314,39 @@ static bool streams(const Desc& t, int batch, bool wide, int past) {
   return m < (1 << 24) && (m + past) * t.xs * es < (1ll << 31) && (m + past) * ys * es < (1ll << 31) && ((int64_t)t.Co + 128) * t.Kp * 2 < (1ll << 31);
 }
 
-// Whether a launch of pointwise convolutions streams, and with which blocks of columns and pieces of a row.  Rows enough to pay for the weights
-// that every workgroup loads first: 512 blocks of 32 rows, from three pieces on
-// 256 per piece.  4x MobileNetV3-Large at batch 32 1912 us without this kernel, 1824 / 1815 / 1807 from 2048 / 1024 / 512 blocks on (28 x 28
-// layers of one to four pieces); 4x DenseNet-121 2972, 2855 / 2851 / 2873 (the 14 x 14 layers of four to six pieces lose).
+// The blocks of 32 rows from which on a launch of this form streams, -1 for never.  What a launch has to pay for are the weights that every workgroup
+// loads before its first row; what it gains over the tile kernel shrinks with a wide row (the tile kernel's weights are then read by many rows,
+// too) and with a residual, which is read between two blocks.  Tile kernel -> this one at the lines (us; single layers, one member):
+//   bf16, up to 32 columns   64 -> 32, 512 blocks 7.7 -> 7.8, 1024 8.8 -> 8.0; 128 -> 32, 1024 9.5 -> 9.0; 256 -> 32, 2048 12.7 -> 12.3
+//   bf16, more               64 -> 128, 512 9.0 -> 9.8, 1024 11.1 -> 10.5; 128 -> 64, 1024 9.8 -> 10.1, 2048 11.2 -> 11.0; 192 -> 128, 1024 12.6 -> 13.6, 3008 19.2 -> 19.1;
+//                            256 -> 64, 2048 13.5 -> 14.4, 4096 22.0 -> 23.4 (never); 256 -> 128, 3008 21.5 -> 21.2, 4096 31 -> 27; 384 -> 128, 2048 19.9 -> 22.5,
+//                            8192 64 -> 63, 320 -> 96, 16384 95 -> 108 (never)
+//   fp32, up to 32 columns   16 -> 16, 512 7.9 -> 7.8; 64 -> 32, 784 8.4 -> 9.9, 1312 10.5 -> 10.3; 96 -> 24, 16384 61 -> 57, 65536 209 -> 222
+//   fp32, 33 to 64           16 -> 64, 512 8.7 -> 9.1, 1024 11.1 -> 9.6; 64 -> 64, 1312 12.0 -> 12.0, 2048 14.2 -> 13.4; 120 -> 40, 1568 13.0 -> 13.9, 32768 142 -> 151 (never)
+//   fp32, 65 to 128          32 -> 128, 512 10.8 -> 11.8, 1024 14.6 -> 13.3; 128 -> 128, 1024 15.9 -> 18.4, 1312 19.1 -> 18.9; 184 -> 128, 1568 22.9 -> 21.8
+//   a residual               bf16 24 -> 24, 1024 8.8 -> 7.4; 40 -> 40, 1024 8.9 -> 8.3; 64 -> 64, 1024 9.0 -> 10.1, 65536 145 -> 149 (never); fp32 64 -> 32, 1024 9.6 -> 10.3,
+//                            4096 18.6 -> 16.9, 65536 193 -> 201; 40 -> 40, 16384 44 -> 50 (never)
+//   an affine stage          (against the R_LONG kernel) 64 channels, 1024 10.4 -> 11.3, 2048 13.2 -> 12.8; 256, 2048 19.8 -> 19.9, 3008 27.4 -> 23.6; 384, 2048 23.1 -> 25.0,
+//                            3008 33.8 -> 31.8
+//   the four-channel input   8 columns, 512 9.0 -> 8.0; 128, fp32, 512 13.0 -> 11.9
+static int64_t stream_line(int form, bool wide, bool residual, int cop, int pieces) {
+  if (cop > 128 || pieces > 6) return -1;
+  if (form == 1) return std::max(2048, 512 * pieces);
+  if (form == 2) return residual ? -1 : 512;
+  if (residual) return cop <= (wide ? 32 : 40) ? 1024 * pieces : -1;
+  if (cop <= 32) return 512 * pieces;
+  if (!wide) return pieces <= (cop <= 64 ? 3 : 4) ? 1024 * pieces : -1;
+  if (cop <= 64) return pieces <= 2 ? 1024 * pieces : -1;
+  return 768 + 128 * pieces;
+}
+
+// Whether a launch of pointwise convolutions (or of 3x3 ones over the four-channel input) streams, and with which blocks of columns and pieces of a row.
 static bool stream_fits(const Launch& L, const Desc* d, const int32_t* batch, Choice* c) {
   const bool wide = L.adtype != FI_BF16;
   const int ce = wide ? 32 : 64;   // elements of a 128-byte piece
   int64_t tiles = 0;
   int cop = 0, pieces = 0;
+  bool residual = false;
   auto form = [](const Desc& t) { return t.Cp == 4 ? 2 : t.pre_kind; };   // (the kernel's PRE)
   for (int i = 0; i < L.n; ++i) {
     const Desc& t = d[i];
@@ -331,11 +355,17 @@ static bool stream_fits(const Launch& L, const Desc* d, const int32_t* batch, Ch
     tiles += (m + 31) / 32;
     cop = std::max(cop, t.Cop);
     pieces = std::max(pieces, ((t.Cp == 4 ? 36 : t.Cp) + ce - 1) / ce);
+    residual = residual || t.r_off != kNone;
   }
-  if (tiles < 512 || tiles < 256 * pieces || pieces > 6 || cop > 128) return false;
+  const int64_t line = stream_line(form(d[0]), wide, residual, cop, pieces);
+  if (line < 0 || tiles < line) return false;
+  if (wide && cop <= 32 && pieces + residual > 2 && tiles > 16384) return false;   // (long fp32 rows, narrow outputs: 96 -> 24 above)
   c->nb = form(d[0]) == 1 || cop > 64 ? 4 : cop > 32 ? 2 : 1;
   c->nch = pieces <= 4 ? pieces : 6;
-  return true;
+#define FI_BUILT(WIDE, PRE, NB, NCH) if (wide == (WIDE) && form(d[0]) == (PRE) && c->nb == (NB) && c->nch == (NCH)) return true;
+  FI_STREAM_FORMS(FI_BUILT)
+#undef FI_BUILT
+  return false;   // (a residual on 33 to 40 columns and rows of more than three pieces)
 }
 
 // Whether a launch is one of affine stages and rows of any length.  From 128

@@ -429,24 +429,9 @@ int launch_stream(const Launch& L, const KArgs& args, int nb, int nch, void* str
   const int n = (int)blocks;
   const bool wide = L.adtype != FI_BF16;
   const int pre = a.d[0].Cp == 4 ? 2 : a.d[0].pre_kind;
-  if (pre == 2) {
-#define FI_GATHER(NB) if (nb == (NB)) return wide ? go_stream<true, 2, NB, 2>(n, a, s) : go_stream<false, 2, NB, 1>(n, a, s);
-    FI_GATHER(1) FI_GATHER(2) FI_GATHER(4)
-#undef FI_GATHER
-    return (int)hipErrorInvalidValue;
-  }
-#define FI_NCH(WIDE, PRE, NB)                                                                      \
-  if (wide == (WIDE) && pre == (PRE) && nb == (NB)) {                                              \
-    if (nch == 1) return go_stream<WIDE, PRE, NB, 1>(n, a, s);                                     \
-    if (nch == 2) return go_stream<WIDE, PRE, NB, 2>(n, a, s);                                     \
-    if (nch == 3) return go_stream<WIDE, PRE, NB, 3>(n, a, s);                                     \
-    if (nch == 4) return go_stream<WIDE, PRE, NB, 4>(n, a, s);                                     \
-    if (nch == 6) return go_stream<WIDE, PRE, NB, 6>(n, a, s);                                     \
-  }
-  FI_NCH(false, 0, 1) FI_NCH(false, 0, 2) FI_NCH(false, 0, 4)
-  FI_NCH(false, 1, 4)
-  FI_NCH(true, 0, 1) FI_NCH(true, 0, 2) FI_NCH(true, 0, 4)
-#undef FI_NCH
+#define FI_TAKE(WIDE, PRE, NB, NCH) if (wide == (WIDE) && pre == (PRE) && nb == (NB) && nch == (NCH)) return go_stream<WIDE, PRE, NB, NCH>(n, a, s);
+  FI_STREAM_FORMS(FI_TAKE)
+#undef FI_TAKE
   return (int)hipErrorInvalidValue;
 }
 

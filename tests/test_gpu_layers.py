@@ -285,27 +285,29 @@ def _bits_and_parity(m, act_dtype, few, many, seed=71, kernel=None, n=1):
     assert harness.elem_excess(large[-1:], ref, harness.ELEM_C_F32 if wide else harness.ELEM_C_BF16) <= 1.0
 
 
-# rows of 61 x 53 pixels: 6 images are 607 blocks of 32 (the last of 6 rows), above the line of one or two pieces of 128 bytes; 16 images are 1617
-@pytest.mark.parametrize("cin, cout, act_dtype, many", [(8, 8, None, 6), (72, 24, None, 6), (64, 128, None, 6), (128, 40, None, 6), (328, 104, None, 16),
-                                                        (16, 64, "f32", 6), (24, 72, "f32", 6), (40, 8, "f32", 6), (184, 96, "f32", 16)])
-def test_pointwise_rows_that_stream(cin, cout, act_dtype, many):
-    """Many rows and a short reduction stream through waves of their own; one image (102 blocks) keeps the tile kernel: the same bits.
+# Rows of 61 x 53 pixels: 6 images are 607 blocks of 32 (the last of 6 rows), 12 are 1213, 16 1617, 21 2122, 31 3133, 41 4143; one image is 102, too
+# few for any form.  `streams`: of the three layers (8 -> cin, cin -> cout, cout -> cin with the first as residual) so many do.
+@pytest.mark.parametrize("cin, cout, act_dtype, many, streams", [(8, 8, None, 12, 3), (40, 40, None, 12, 3), (72, 24, None, 12, 2), (64, 128, None, 12, 2), (128, 40, None, 21, 2),
+                                                                 (200, 104, None, 41, 2), (328, 24, None, 31, 2), (16, 64, "f32", 21, 3), (24, 72, "f32", 12, 2), (40, 8, "f32", 12, 2),
+                                                                 (104, 32, "f32", 21, 2), (184, 96, "f32", 16, 2)])
+def test_pointwise_rows_that_stream(cin, cout, act_dtype, many, streams):
+    """Many rows and a short reduction stream through waves of their own; one image keeps the tile kernel: the same bits.
     Partial pieces and blocks of columns, a residual, every activation the kernel has."""
     m = zoo.Model("c", "bf16", 8, 61, 53)
     e = m.add(zoo.CONV, -1, cin=8, cout=cin, k=1, stride=1, pad=0, act=zoo.RELU6)
     a = m.add(zoo.CONV, e, cin=cin, cout=cout, k=1, stride=1, pad=0, act=zoo.HARDSWISH)
     a = m.add(zoo.CONV, a, cin=cout, cout=cin if cin <= 128 else 16, k=1, stride=1, pad=0, act=zoo.RELU, residual=e if cin <= 128 else zoo.NO_RESIDUAL)
     m.add(zoo.MAXPOOL, a, k=1, stride=1, pad=0)
-    _bits_and_parity(m, act_dtype, 1, many)
+    _bits_and_parity(m, act_dtype, 1, many, kernel="conv_stream", n=streams)
 
 
-@pytest.mark.parametrize("cout, stride, pad, act_dtype", [(16, 2, 1, "f32"), (40, 1, 0, "f32"), (104, 2, 0, "f32"), (24, 2, 1, None), (64, 1, 1, "f32"), (136, 2, 1, None), (40, 1, 1, None)])
+@pytest.mark.parametrize("cout, stride, pad, act_dtype", [(16, 2, 1, "f32"), (40, 1, 0, "f32"), (104, 2, 0, "f32"), (24, 2, 1, None), (64, 1, 1, "f32"), (128, 2, 1, None), (40, 1, 1, None)])
 def test_first_layers_that_stream(cout, stride, pad, act_dtype):
     """3x3 convolutions over the model input gather their rows tap by tap: ragged blocks of rows and columns, windows over every border."""
     m = zoo.Model("c", "bf16", 3, 123 if stride == 2 else 61, 107 if stride == 2 else 53)
     a = m.add(zoo.CONV, -1, cin=3, cout=cout, k=3, stride=stride, pad=pad, act=zoo.HARDSWISH if cout == 16 else zoo.RELU6)
     m.add(zoo.MAXPOOL, a, k=1, stride=1, pad=0)
-    _bits_and_parity(m, act_dtype, 1, 6)
+    _bits_and_parity(m, act_dtype, 1, 6, kernel="conv_stream")
 
 
 @pytest.mark.parametrize("h, w, c, pad, act_dtype, many", [(61, 53, 160, 1, None, 12), (61, 53, 160, 1, "f32", 12), (60, 50, 136, 0, "f32", 18), (33, 30, 248, 1, "f32", 24)])
@@ -318,10 +320,12 @@ def test_depthwise_two_rows_per_thread(h, w, c, pad, act_dtype, many):
     _bits_and_parity(m, act_dtype, 1, many, kernel="dwconv_rows", n=1 if act_dtype else 0)
 
 
-# 16 images: 1617 blocks of 32 rows; 6 images: 607, too few for resident weights from three pieces of 64 channels on; 440 channels are seven pieces
-@pytest.mark.parametrize("first, grow, act, many", [(64, 32, zoo.RELU, 16), (40, 24, zoo.RELU6, 16), (128, 72, zoo.NONE, 16), (64, 32, zoo.RELU, 6), (136, 40, zoo.RELU, 6),
-                                                    (200, 56, zoo.RELU, 6), (440, 72, zoo.RELU, 6)])
-def test_dense_layers_that_stream(first, grow, act, many):
+# 21 images: 2122 blocks of 32 rows, resident weights; 6 images: 607, 152 workgroups with the weights in a ring (440 channels are seven pieces); other
+# activations than ReLU keep the tile, and `n` counts the plain layers that stream
+@pytest.mark.parametrize("first, grow, act, many, kernel, n", [(64, 32, zoo.RELU, 21, "conv_stream", 5), (40, 24, zoo.RELU6, 16, "conv_stream", 3), (128, 72, zoo.NONE, 16, "conv_stream", 1),
+                                                               (64, 32, zoo.RELU, 6, "conv_long", 2), (136, 40, zoo.RELU, 6, "conv_long", 2), (200, 56, zoo.RELU, 6, "conv_long", 2),
+                                                               (440, 72, zoo.RELU, 6, "conv_long", 2)])
+def test_dense_layers_that_stream(first, grow, act, many, kernel, n):
     """Dense layers whose rows stream: an affine stage on the way in, the input a prefix of a concatenation's tensor."""
     m = zoo.Model("c", "bf16", 8, 61, 53)
     t = m.add(zoo.CONV, -1, cin=8, cout=first, k=1, stride=1, pad=0, act=zoo.RELU)
@@ -333,7 +337,81 @@ def test_dense_layers_that_stream(first, grow, act, many):
         t = m.add(zoo.CONCAT, t, residual=a)
         c += grow
     m.add(zoo.MAXPOOL, t, k=1, stride=1, pad=0)
-    _bits_and_parity(m, None, 1, many)
+    _bits_and_parity(m, None, 1, many, kernel=kernel, n=n)
+
+
+def _streaming_model(kind, side=61):
+    m = zoo.Model("c", "bf16", 3 if kind == "first" else 8, side, 53)
+    if kind == "first":
+        a = m.add(zoo.CONV, -1, cin=3, cout=24, k=3, stride=1, pad=1, act=zoo.HARDSWISH)
+    else:
+        a = m.add(zoo.CONV, -1, cin=8, cout=72, k=1, stride=1, pad=0, act=zoo.SILU)
+        if kind == "affine":
+            a = m.add(zoo.DWCONV, a, cin=72, cout=72, k=1, stride=1, pad=0, act=zoo.RELU)
+        a = m.add(zoo.CONV, a, cin=72, cout=128 if kind == "affine" else 24, k=1, stride=1, pad=0, act=zoo.NONE)
+    m.add(zoo.AVGPOOL, a, k=1, stride=1, pad=0)   # (a maximum would drop NaN)
+    return m.shapes()
+
+
+@pytest.mark.parametrize("kind, act_dtype, batch, kernel", [("plain", None, 12, "conv_stream"), ("plain", "f32", 16, "conv_stream"), ("affine", None, 6, "conv_long"), ("affine", None, 21, "conv_stream"),
+                                                            ("first", None, 6, "conv_stream"), ("first", "f32", 6, "conv_stream")])
+def test_streaming_keeps_what_is_not_finite(kind, act_dtype, batch, kernel):
+    """Infinite and NaN inputs, weights and biases: every image has the bits (NaN where it is NaN) of a pass of one, which keeps the tile kernel."""
+    from tests import harness
+    m = _streaming_model(kind)
+    blob = gen.make_blob(m, 83, bias_std=0.1)
+    last = m.layers[-2]
+    k = last.k * last.k * last.cin
+    w = blob[last.w_off:last.w_off + 2 * last.cout * k].view(np.uint16).reshape(last.cout, k)
+    w[1, 0], w[2, k - 1], w[3, k // 2] = 0x7F80, 0xFF80, 0x7FC0   # inf, -inf, NaN
+    blob[last.b_off:last.b_off + 4 * last.cout].view(np.float32)[4:7] = np.inf, -np.inf, np.nan
+    x = gen.make_input(84, batch, m.in_c, 61, 53, "normal", "bf16")
+    x[0, 0, 0, 0], x[1, 1, 60, 52], x[-1, 2, 60, 0], x[-1, 0, 30, 26] = np.inf, np.nan, -np.inf, np.inf
+    g = harness.GpuDag([(m, blob, act_dtype)], batch)
+    try:
+        assert kernel in [L.name.decode() for L in g.dag.launches(batch)] and kernel not in [L.name.decode() for L in g.dag.launches(1)]
+        large = g.run(x)[0]
+        ones = np.concatenate([g.run(x[i:i + 1])[0] for i in (0, 1, 2, batch - 1)])
+    finally:
+        g.close()
+    assert np.isnan(large).any() and np.isinf(large).any() and np.isfinite(large).any()
+    assert np.array_equal(large[[0, 1, 2, batch - 1]], ones, equal_nan=True)
+
+
+@pytest.mark.parametrize("kind, act_dtype, kernel", [("plain", None, "conv_stream"), ("plain", "f32", "conv_stream"), ("affine", None, "conv_stream"), ("first", None, "conv_stream"), ("long", None, "conv_long")])
+def test_streaming_launches_of_ragged_members(kind, act_dtype, kernel):
+    """Five members share a streaming launch with batches of their own, one of them none: every member has the bits of a DAG of its own, one image at a time."""
+    import torch
+    import paper_2410_21120_amd as fi
+    from tests import harness
+    m = _streaming_model("affine" if kind == "long" else kind)
+    batches = {"plain": [9, 0, 1, 5, 14], "affine": [17, 0, 1, 6, 9], "first": [3, 0, 1, 1, 2], "long": [3, 0, 1, 1, 2]}[kind]
+    B, blobs = max(batches), [gen.make_blob(m, 90 + i, bias_std=0.1) for i in range(len(batches))]
+    xs = [gen.make_input(95 + i, B, m.in_c, 61, 53, "normal", "bf16") for i in range(len(batches))]
+    made = [fi.make_spec(m, b.ctypes.data, b.nbytes, act_dtype=act_dtype) for b in blobs]
+    dag = fi.Dag([s for s, _ in made], B, fi.TorchAllocators("cuda:0"), keepalive=(blobs, [k for _, k in made]), per_member_inputs=True, serial_lanes=True)
+    stream = torch.cuda.current_stream().cuda_stream
+    dag.load(stream)
+    try:
+        assert kernel in [L.name.decode() for L in dag.launches(-(-sum(batches) // len(batches)))]   # (as many blocks in all)
+        n = m.layers[-1].cout * 61 * 53
+        ins = [torch.from_numpy(gen.to_nhwc_storage(x, "bf16").view(np.int16)).cuda() for x in xs]
+        outs = [torch.full((B, n), -7.0, dtype=torch.float32, device="cuda:0") for _ in batches]
+        for _ in range(2):
+            dag.run_batches([t.data_ptr() for t in ins], batches, [o.data_ptr() for o in outs], stream)
+        torch.cuda.synchronize()
+        got = [o.cpu().numpy() for o in outs]
+    finally:
+        dag.unload()
+        dag.destroy()
+    for i, b in enumerate(batches):
+        assert np.all(got[i][b:] == -7.0), i
+        g = harness.GpuDag([(m, blobs[i], act_dtype)], 1)
+        try:
+            for j in sorted({0, b // 2, b - 1}) if b else ():
+                assert np.array_equal(got[i][j], g.run(xs[i][j:j + 1])[0][0]), (i, j)
+        finally:
+            g.close()
 
 
 @pytest.mark.parametrize("features, batch", [(1000, 4), (1001, 33), (7, 1)])

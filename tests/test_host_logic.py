@@ -122,6 +122,52 @@ def test_few_channel_launches_hold_one_channel_count():
     assert launch[1] == launch[3] and len(set(launch)) == 3   # (the two of three channels share one)
 
 
+@pytest.mark.parametrize("cin, cout, act_dtype, residual, lines", [
+    # images of 64 x 64 are 128 blocks of 32 rows; from the first batch of `lines` on the layer streams, from the second on no more
+    (64, 32, None, False, (4, None)), (64, 128, None, False, (8, None)), (128, 64, None, False, (16, None)), (192, 64, None, False, (24, None)), (256, 64, None, False, None),
+    (256, 128, None, False, (32, None)), (320, 96, None, False, None), (328, 24, None, False, (24, None)), (136, 136, None, False, None),
+    (16, 64, "f32", False, (8, None)), (64, 64, "f32", False, (16, None)), (120, 40, "f32", False, None), (128, 128, "f32", False, (10, None)), (96, 24, "f32", False, (12, 129)),
+    (24, 24, None, True, (8, None)), (40, 40, None, True, (8, None)), (200, 40, None, True, None), (64, 64, None, True, None), (40, 40, "f32", True, None), (64, 32, "f32", True, (16, 129)),
+    (32, 16, "f32", True, (8, None))])
+def test_lines_from_which_pointwise_rows_stream(cin, cout, act_dtype, residual, lines):
+    """Which 1x1 layers a pass issues to the streaming kernel, by its images: one image below and at every line."""
+    m = zoo.Model("c", "bf16", 8, 64, 64)
+    r = m.add(zoo.CONV, -1, cin=8, cout=cout, k=1, stride=1, pad=0, act=zoo.SILU) if residual else zoo.NO_RESIDUAL   # (an activation that the kernel does not have)
+    a = m.add(zoo.CONV, -1, cin=8, cout=cin, k=1, stride=1, pad=0, act=zoo.SILU)
+    a = m.add(zoo.CONV, a, cin=cin, cout=cout, k=1, stride=1, pad=0, act=zoo.RELU, residual=r)
+    m.add(zoo.CONV, a, cin=cout, cout=8, k=1, stride=1, pad=0, act=zoo.SILU)
+    m.shapes()
+    blob = gen.make_blob(m, 1)
+    spec, keep = fi.make_spec(m, blob.ctypes.data, blob.nbytes, act_dtype=act_dtype)
+    d = fi.Dag([spec], 160, fi.HostAllocators(), keepalive=(keep, blob))
+    first, last = lines or (161, None)
+    for b in sorted({1, 3, first - 1, min(first, 160), (last or 161) - 1, last or 160, 160}):
+        names = [L.name.decode() for L in d.launches(b)]
+        assert names.count("conv_stream") == int(first <= b and (last is None or b < last)), (b, names)
+
+
+def test_lines_from_which_affine_and_first_layers_stream():
+    def names(m, batches, **kw):
+        m.shapes()
+        blob = gen.make_blob(m, 1)
+        spec, keep = fi.make_spec(m, blob.ctypes.data, blob.nbytes, **kw)
+        d = fi.Dag([spec], max(batches), fi.HostAllocators(), keepalive=(keep, blob))
+        return [[n for n in (L.name.decode() for L in d.launches(b)) if n in ("conv_stream", "conv_long")] for b in batches]
+    for cin, act, want in ((64, zoo.RELU, [[], ["conv_long"], ["conv_long"], ["conv_stream"], ["conv_stream"]]), (384, zoo.RELU, [[], ["conv_long"], ["conv_long"], ["conv_long"], ["conv_stream"]]),
+                           (1792, zoo.RELU, [[]] + [["conv_long"]] * 4), (1800, zoo.RELU, [[]] * 5), (64, zoo.RELU6, [[]] * 5)):
+        m = zoo.Model("c", "bf16", 8, 64, 64)
+        a = m.add(zoo.CONV, -1, cin=8, cout=cin, k=1, stride=1, pad=0, act=zoo.SILU)
+        a = m.add(zoo.DWCONV, a, cin=cin, cout=cin, k=1, stride=1, pad=0, act=act)
+        a = m.add(zoo.CONV, a, cin=cin, cout=128, k=1, stride=1, pad=0, act=zoo.RELU)
+        m.add(zoo.CONV, a, cin=128, cout=8, k=1, stride=1, pad=0, act=zoo.SILU)
+        assert names(m, (3, 4, 15, 16, 24)) == want, (cin, act)
+    for cout, kw, want in ((16, {}, [[], ["conv_stream"]]), (128, {"act_dtype": "f32"}, [[], ["conv_stream"]]), (136, {}, [[], []])):
+        m = zoo.Model("c", "bf16", 3, 128, 128)
+        a = m.add(zoo.CONV, -1, cin=3, cout=cout, k=3, stride=2, pad=1, act=zoo.HARDSWISH)
+        m.add(zoo.CONV, a, cin=cout, cout=8, k=1, stride=1, pad=0, act=zoo.SILU)
+        assert names(m, (3, 4), **kw) == want, cout
+
+
 def test_patch_launches_count_the_convolutions_they_carry():
     """The patch kernel's lines are in workgroups of one launch.  A 1x1 convolution beside a 3x3 of the same size, output channels and
     tile stays on the tile kernel and must not count: 42 images of 28 x 28 x 256 are 130 tiles of 512x128, below the line of 256 (two
