@@ -828,7 +828,10 @@ static bool direct_is_shorter(const F32Cost& c, int64_t K) { return K <= 256 && 
 // fit on 72 layers (3 channels to 16, 32 and 64, 3x3 and 7x7, stride 1 and 2, sides 32 to 224, batch 1 and 4).  At the ends, other
 // kernel -> this one (us): 3 -> 64, 7x7 stride 2, 224 x 224, batch 4 67 -> 40, 160 x 160 37.5 -> 34.3, 128 x 128 23 -> 32; 3x3 stride 2,
 // 224 x 224, batch 4 53 -> 24, 128 x 128 18.2 -> 17.2, 128 x 128, batch 1 10.7 -> 14.5.
-static bool takes_rgb(const Node& nd, int64_t batch, int64_t K, const F32Cost& c) {
+// A filter row's products are one serial sum, and no longer than the other kernel's of a wave (distance from 64 bits, 3x15, 3 channels: 1.16e-7
+// shared, 1.29e-7 here).
+static bool takes_rgb(const Node& nd, int64_t batch, int64_t K, const F32Cost& c, int tile) {
+  if ((int64_t)nd.kw * nd.Cp > std::max<int64_t>(32, K / (tile == KW_32x8 ? 8 : 4))) return false;
   if (nd.op != FI_CONV2D || nd.Cp > 3 || nd.C != nd.Cp || rgb_lds(nd.k, nd.kw, nd.stride, nd.Cp) > KW_RGB_LDS) return false;
   const double groups = (double)batch * (double)((nd.Ho + 15) / 16) * (double)((nd.Wo + 15) / 16) * (double)((nd.Co + 31) / 32);
   const double us = 3.5 + 0.4 * (double)(nd.k * nd.kw) + 0.027 * groups;
@@ -904,7 +907,7 @@ static fi_status choose_kernels(fi_dag* g) {
             const int tile = ((M + 63) / 64) * ((nd.Co + 63) / 64) >= 192 ? KW_64x4 : KW_32x8;
             const int64_t K = nd.op == FI_FC ? (int64_t)nd.H * nd.W * nd.C : (int64_t)nd.k * nd.kw * nd.C;
             const F32Cost cost = f32_cost(M, nd.Co, K, cp % 4 != 0, tile);
-            const bool rgb = takes_rgb(nd, B, K, cost);
+            const bool rgb = takes_rgb(nd, B, K, cost, tile);
             if (rgb || !direct_is_shorter(cost, K)) {
               nd.kind = K_CONV_KWAVE;
               nd.tile = tile | (cp % 4 ? KW_SCALAR : 0) | (rgb ? KW_RGB : 0);

@@ -220,8 +220,9 @@ __global__ void __launch_bounds__(NW * 64) conv_kwave_kernel(KArgs a) {
 // loads of 4 bytes per lane and step: 112 x 112 x 64, 7x7 stride 2, batch 4 67 us at 14 TFLOP/s.  Here a workgroup owns 16 x 16 pixels x 32
 // channels, with the input patch under them and the weights, [tap][channel][output], in LDS: one round of loads, then a
 // wave reads an input value for 8 products and the eight weights as two broadcasts for 32: 37 us for that layer.  Bound: the LDS reads and
-// their latency, 0.4 us per tap.  (Without the patch, a tap's pixels requested one tap ahead, every tap waits for memory: 57 us.)  A filter row's products are
-// summed first, then the rows: short serial sums, as close to the exact value as the sums shared among waves above.
+// their latency, 0.4 us per tap.  (Without the patch, a tap's pixels requested one tap ahead, every tap waits for memory: 57 us.)  A filter row's products (three at
+// least) are summed first, then the rows: short serial sums, as close to the exact value as the sums shared among waves above or the element kernel's.  (One
+// product a row would be rounded twice: distance from 64 bits 5.5e-8 -> 6.2e-8 of 7x1, one channel; rows that are too long for this stay with the kernel above.)
 template <int C>
 __global__ void __launch_bounds__(256) conv_rgb_kernel(KArgs a) {
   extern __shared__ __attribute__((aligned(16))) float lds[];   // weights [k * kw * C][32], patch [PH][PW * C]
@@ -280,11 +281,13 @@ __global__ void __launch_bounds__(256) conv_rgb_kernel(KArgs a) {
 #pragma unroll
     for (int o = 0; o < 8; ++o) acc[i][o] = 0.0f;
   const float* wt = lds + g0;
+  int held = 0;   // products in `row` (of three channels a filter row has enough by itself)
   for (int r = 0; r < d.k; ++r) {
+    if (C > 2 || held == 0)
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int o = 0; o < 8; ++o) row[i][o] = 0.0f;
+        for (int o = 0; o < 8; ++o) row[i][o] = 0.0f;
 #pragma unroll 3
     for (int s = 0; s < d.kw * C; s += C) {
 #pragma unroll
@@ -301,11 +304,16 @@ __global__ void __launch_bounds__(256) conv_rgb_kernel(KArgs a) {
       wt += C * 32;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      xp[i] += pitch;
+    for (int i = 0; i < 4; ++i) xp[i] += pitch;
+    if constexpr (C <= 2) {
+      held += d.kw * C;
+      if (held < 3 && r + 1 < d.k) continue;
+      held = 0;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int o = 0; o < 8; ++o) acc[i][o] += row[i][o];
-    }
   }
   const int q = q0 + (lane & 15), o = n0 + g0;
   // The common case is finished from registers; an element in doubt (NaN beside padding), a residual, the caller's buffer or rows of any

@@ -110,6 +110,37 @@ def test_conv_f32_few_channel_siblings():
     _run_case(m, 950, 4, tol=2.0 * ((9 * 3) ** 0.5 + 3 ** 0.5) * 2.0 ** -23, kernels=[("conv_rgb", 4)])   # (the roundings of both layers)
 
 
+@pytest.mark.parametrize("cin, k, kw", [(1, 2, 0), (1, 7, 1), (2, 2, 1), (1, 3, 0), (3, 3, 0), (3, 1, 7)])
+def test_conv_f32_few_channels_loses_nothing_to_a_serial_sum(cin, k, kw):
+    """The distance from 64 bits is no larger than that of one fused multiply-add after another, the longest order any kernel has (both of
+    2 x 64 x 80 x 80 elements: the two distances' own scatter is below 0.5 %)."""
+    m = zoo.Model("c", "f32", cin, 80 + k - 1, 80 + (kw or k) - 1)
+    m.add(zoo.CONV, -1, cin=cin, cout=64, k=k, kw=kw, stride=1, pad=0, act=zoo.NONE)
+    m.add(zoo.MAXPOOL, 0, k=1, stride=1, pad=0)
+    m.shapes()
+    blob = gen.make_blob(m, 61, bias_std=0.1)
+    x = gen.make_input(62, 16, cin, m.in_h, m.in_w, "normal", "f32")
+    from tests import harness
+    g = harness.GpuDag([(m, blob, None)], 16)
+    try:
+        assert "conv_rgb" in [L.kernel for L in g.dag.launches()]
+        y = g.run(x)[0][:2].reshape(2, 80, 80, 64)
+    finally:
+        g.close()
+    L = m.layers[0]
+    w = blob[L.w_off:L.w_off + 4 * 64 * cin * k * (kw or k)].view(np.float32).reshape(64, cin, k, kw or k).astype(np.float64)
+    b = blob[L.b_off:L.b_off + 256].view(np.float32).astype(np.float64)
+    exact, serial = np.zeros((2, 80, 80, 64)), np.zeros((2, 80, 80, 64), np.float32)
+    for r in range(k):
+        for s in range(kw or k):
+            for c in range(cin):
+                p = x[:2, c, r:r + 80, s:s + 80, None].astype(np.float64) * w[:, c, r, s]   # (exact: two 24-bit factors)
+                exact += p
+                serial = (serial + p).astype(np.float32)
+    exact, serial = exact + b, (serial + b).astype(np.float32)
+    assert np.linalg.norm(y - exact) <= 1.005 * np.linalg.norm(serial - exact)
+
+
 @pytest.mark.parametrize("case", [(64, 40, 3, 1, 1, 61, 57, 4, "64x64x4"), (3, 64, 7, 2, 3, 161, 157, 4, "rgb"), (5, 64, 7, 2, 3, 161, 157, 4, "64x64x4 scalar"),
                                   (5, 33, 3, 1, 1, 9, 11, 1, "32x32x8 scalar"), (36, 31, 5, 2, 2, 9, 11, 1, "32x32x8")])
 def test_conv_f32_weights_that_are_not_finite(case):

@@ -106,6 +106,19 @@ def test_fp32_layers_of_few_products_keep_the_element_kernel(layer, kernel):
     assert [L.kernel for L in d.launches()][1:] == [kernel]
 
 
+@pytest.mark.parametrize("cin, cout, k, kw, stride, hw, batch, taken", [
+    (3, 96, 3, 15, 1, 128, 8, False), (3, 64, 1, 15, 1, 224, 4, False), (3, 64, 1, 11, 1, 224, 4, False), (3, 64, 1, 10, 1, 224, 4, True), (3, 64, 11, 11, 1, 128, 4, True), (3, 64, 7, 7, 2, 224, 4, True)])
+def test_few_channel_kernel_and_the_filters_that_it_leaves(cin, cout, k, kw, stride, hw, batch, taken):
+    """fp32 layers of one to three channels whose filter rows are longer sums than the shared reduction's keep that kernel."""
+    m = zoo.Model("c", "f32", cin, hw, hw)
+    m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, kw=kw if kw != k else 0, stride=stride, pad=1 if k > 1 else 0, act=zoo.NONE)
+    m.shapes()
+    blob = gen.make_blob(m, 1)
+    spec, keep = fi.make_spec(m, blob.ctypes.data, blob.nbytes)
+    d = fi.Dag([spec], batch, fi.HostAllocators(), keepalive=(keep, blob))
+    assert (d.launches()[1].kernel == "conv_rgb") == taken, d.launches()[1].kernel
+
+
 def test_few_channel_launches_hold_one_channel_count():
     """The kernel of fp32 layers of one to three channels is built for a channel count: sibling layers of other counts are launches of their own."""
     m = zoo.Model("c", "f32", 3, 224, 224)
