@@ -829,10 +829,13 @@ static bool direct_is_shorter(const F32Cost& c, int64_t K) { return K <= 256 && 
 // kernel -> this one (us): 3 -> 64, 7x7 stride 2, 224 x 224, batch 4 67 -> 40, 160 x 160 37.5 -> 34.3, 128 x 128 23 -> 32; 3x3 stride 2,
 // 224 x 224, batch 4 53 -> 24, 128 x 128 18.2 -> 17.2, 128 x 128, batch 1 10.7 -> 14.5.
 // A filter row's products are one serial sum, and no longer than the other kernel's of a wave (distance from 64 bits, 3x15, 3 channels: 1.16e-7
-// shared, 1.29e-7 here).
+// shared, 1.29e-7 here).  A patch of more than 32 KB of which a stride skips more than half is not worth its loads (2x2 stride 4, 3 -> 192, 4 x 375 x 54
+// 42 -> 52 us; 3 -> 32, 32 x 187 x 65 28.8 -> 32.1; 3x3 stride 4, 9/16 of the patch read, 48.2 -> 44.9).
 static bool takes_rgb(const Node& nd, int64_t batch, int64_t K, const F32Cost& c, int tile) {
-  if ((int64_t)nd.kw * nd.Cp > std::max<int64_t>(32, K / (tile == KW_32x8 ? 8 : 4))) return false;
   if (nd.op != FI_CONV2D || nd.Cp > 3 || nd.C != nd.Cp || rgb_lds(nd.k, nd.kw, nd.stride, nd.Cp) > KW_RGB_LDS) return false;
+  if ((int64_t)nd.kw * nd.Cp > std::max<int64_t>(32, K / (tile == KW_32x8 ? 8 : 4))) return false;
+  const int64_t patch = ((int64_t)15 * nd.stride + nd.k) * (15 * nd.stride + nd.kw) * nd.Cp;
+  if (patch > 8192 && 2 * nd.k * nd.kw < nd.stride * nd.stride) return false;
   const double groups = (double)batch * (double)((nd.Ho + 15) / 16) * (double)((nd.Wo + 15) / 16) * (double)((nd.Co + 31) / 32);
   const double us = 3.5 + 0.4 * (double)(nd.k * nd.kw) + 0.027 * groups;
   return us < 0.75 * c.shared && (K > 256 || us < 0.75 * c.direct);

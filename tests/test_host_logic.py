@@ -107,9 +107,11 @@ def test_fp32_layers_of_few_products_keep_the_element_kernel(layer, kernel):
 
 
 @pytest.mark.parametrize("cin, cout, k, kw, stride, hw, batch, taken", [
-    (3, 96, 3, 15, 1, 128, 8, False), (3, 64, 1, 15, 1, 224, 4, False), (3, 64, 1, 11, 1, 224, 4, False), (3, 64, 1, 10, 1, 224, 4, True), (3, 64, 11, 11, 1, 128, 4, True), (3, 64, 7, 7, 2, 224, 4, True)])
+    (3, 96, 3, 15, 1, 128, 8, False), (3, 64, 1, 15, 1, 224, 4, False), (3, 64, 1, 11, 1, 224, 4, False), (3, 64, 1, 10, 1, 224, 4, True), (3, 64, 11, 11, 1, 128, 4, True), (3, 64, 7, 7, 2, 224, 4, True),
+    (3, 192, 2, 2, 4, 192, 4, False), (3, 128, 3, 3, 4, 192, 32, True), (1, 128, 2, 2, 4, 256, 16, True)])
 def test_few_channel_kernel_and_the_filters_that_it_leaves(cin, cout, k, kw, stride, hw, batch, taken):
-    """fp32 layers of one to three channels whose filter rows are longer sums than the shared reduction's keep that kernel."""
+    """fp32 layers of one to three channels whose filter rows are longer sums than the shared reduction's keep that kernel, and so do
+    those whose patch is large and mostly skipped by the stride."""
     m = zoo.Model("c", "f32", cin, hw, hw)
     m.add(zoo.CONV, -1, cin=cin, cout=cout, k=k, kw=kw if kw != k else 0, stride=stride, pad=1 if k > 1 else 0, act=zoo.NONE)
     m.shapes()
