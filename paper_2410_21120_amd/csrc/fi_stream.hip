@@ -5,13 +5,15 @@
 // six reduction tiles with two barriers each and one tile of loads in flight, and an epilogue: 2.0 to 3.4 TB/s.  Here eight waves share
 // the weights in LDS (one workgroup per compute unit, loaded once) and each takes blocks of 32 rows on its own: a lane loads
 // the 16-byte pieces that the matrix instruction wants of it straight into registers, the whole next block requested piece by piece
-// while this one is multiplied (up to 128 KB in flight per compute unit), no barrier after the start.  Outputs turn through a 4 KB patch of the wave's own, so
+// while this one is multiplied (up to 128 KB in flight per compute unit), no barrier after the start.  The end of a block breaks into that: loads return
+// in order, so the loads of a residual (fp32 rows make them without one too, out of range) wait for the next block's rows, one after the other; and
+// as a store is one of two kinds by a branch, the first multiply of a block waits for its rows as if no store had been issued behind them.  Outputs turn through a 4 KB patch of the wave's own, so
 // that whole cache lines leave: 16-byte pieces straight from the accumulators' layout, 32 bytes of a row at a time, written past the
 // cache cost 166 us where the tile took 69 (112 x 112, fp32 rows, 16 -> 64 channels).
 //
 // Measured alone, tile kernel -> this one (us): DenseNet-121, four members at batch 32, 56 x 56, affine and ReLU on the way in, 64 / 128 /
-// 192 / 256 -> 128 channels 54.1 / 61.4 / 74.6 / 90.3 -> 40.5 / 40.8 / 59.7 / 65.1 (3.8 to 5.0 TB/s; a copy reaches 5.2); MobileNetV3-Large, fp32 rows,
-// two members at batch 32, 112 x 112, 16 -> 16 60.6 -> 37.6, 16 -> 64 69.3 -> 52.9, 56 x 56, 24 -> 72 35.4 -> 26.5.
+// 192 / 256 -> 128 channels 54 / 67 / 79 / 103 -> 32 / 42 / 53 / 79 (3.9 to 4.9 TB/s; a copy reaches 5.2); MobileNetV3-Large, fp32 rows,
+// two members at batch 32, 112 x 112, 16 -> 16 60 -> 29, 16 -> 64 64 -> 46, 56 x 56, 24 -> 72 36 -> 27.
 // Wider outputs would read every row once per 128 columns, at different times: 256 -> 256 channels, 56 x 56, 69.6 -> 124.6 us, so they keep the tile.
 //
 // The order of the sums (ascending channels, 16 per instruction, from zero; for fp32 rows the small halves first) and the epilogue's operations are the
@@ -47,7 +49,8 @@ __device__ __forceinline__ bool past_the_cache(const Desc& d, int M, int es) {
   return (int64_t)M * d.Cop * 2 > (int64_t)STREAM_OUT_BYTES && (((uint64_t)d.Cop * es | (uint64_t)d.ys * es | d.y_off) & 127) == 0;
 }
 
-// A lane holds, for pixel (lane & 31) of 32, runs of four consecutive channels: bias, residual, activation, the one rounding.
+// A lane holds, for pixel (lane & 31) of 32, runs of four consecutive channels: bias, residual, activation, the one rounding.  A bf16 line of the patch
+// is two blocks of columns: with an odd NB the half of the last one that nothing wrote is not stored, as there Cop <= n0 + NB * 32.
 template <bool WIDE, int NB>
 __device__ __forceinline__ void finish_rows(const Desc& d, const f32x16 (&acc)[NB], int row0, int n0, int lane, const float* bias, uint8_t* patch, const Activation<false>& act,
                                             const __amdgpu_buffer_rsrc_t rres, bool has_res, const __amdgpu_buffer_rsrc_t yres, bool stream_out) {
@@ -120,7 +123,7 @@ __device__ __forceinline__ void finish_rows(const Desc& d, const f32x16 (&acc)[N
 // WIDE: fp32-stored activations, multiplied as hi + lo bf16 halves.  PRE: 1 = per-channel affine and ReLU on the way in.
 // PRE 2 (not a pointwise convolution): 3x3 over the four-channel staged input, the first layer of the mobile families.  A row's 36 elements
 // are gathered tap by tap (8 or 16 bytes) from the pixels around it, which neighbouring rows share in the vector cache.  MobileNetV3-Large, fp32
-// rows, 112 x 112 x 16, two members at batch 32: 74.9 us on the tile kernel, 38 here.
+// rows, 112 x 112 x 16, two members at batch 32: 80 us on the tile kernel, 37 here.
 // NB: 32-column blocks of a workgroup's weights.  NCH: 128-byte pieces of a row (64 bf16 or 32 fp32 elements).
 template <bool WIDE, int PRE, int NB, int NCH>
 __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
@@ -141,9 +144,8 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
   const Desc d = a.d[p];
   const int batch = a.batch[p];
   const int M = batch * d.Ho * d.Wo, T = (M + 31) >> 5;
-  const int slabs = (d.Cop + BN - 1) / BN, groups = (a.first_block[p + 1] - a.first_block[p]) / slabs;
-  const int n0 = bid % slabs * BN, grp = bid / slabs;
-  const int t0 = (int)((int64_t)T * grp / groups), t1 = (int)((int64_t)T * (grp + 1) / groups);   // this workgroup's blocks of 32 rows
+  const int groups = a.first_block[p + 1] - a.first_block[p];
+  const int t0 = (int)((int64_t)T * bid / groups), t1 = (int)((int64_t)T * (bid + 1) / groups);   // this workgroup's blocks of 32 rows
   const int tid = threadIdx.x, lane = tid & 63, r31 = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
@@ -198,9 +200,9 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
   for (int i = wave; i < KW * (BN / 8); i += SW) {
     const int kc = i / (BN / 8), r = i % (BN / 8) * 8 + lrow;
     const int k = kc * 64 + ((lane & 7) ^ ((r >> 1) & 7)) * 8;
-    load_lds<16>(wres, smem + i * 1024, k < d.Kp ? (uint32_t)((n0 + r) * d.Kp + k) * 2 : OOB);   // (rows past Co lie past the buffer's end)
+    load_lds<16>(wres, smem + i * 1024, k < d.Kp ? (uint32_t)(r * d.Kp + k) * 2 : OOB);   // (rows past Co lie past the buffer's end)
   }
-  for (int i = tid; i < BN; i += SW * 64) bias_s[i] = n0 + i < d.Cop ? reinterpret_cast<const float*>(a.wbase + d.b_off)[n0 + i] : 0.0f;
+  for (int i = tid; i < BN; i += SW * 64) bias_s[i] = i < d.Cop ? reinterpret_cast<const float*>(a.wbase + d.b_off)[i] : 0.0f;
   if constexpr (PRE == 1)
     for (int i = tid; i < KP; i += SW * 64) {
       scale_s[i] = i < d.Cp ? bf2f(reinterpret_cast<const bf16_t*>(a.wbase + d.pw_off)[i]) : 0.0f;
@@ -273,22 +275,23 @@ __global__ void __launch_bounds__(SW * 64, 2) conv_stream_kernel(KArgs a) {
       request(c, live);   // the same piece of the next block
       __builtin_amdgcn_sched_barrier(0);
     }
-    finish_rows<WIDE, NB>(d, acc, t * 32, n0, lane, bias_s + fresh, patch, act, rres, has_res, yres, stream_out);
+    finish_rows<WIDE, NB>(d, acc, t * 32, 0, lane, bias_s + fresh, patch, act, rres, has_res, yres, stream_out);
   }
 }
 
 // The same, for rows of any length behind an affine stage with ReLU (DenseNet's layers beyond 384 channels, or of too few rows to pay for resident
 // weights): four waves, a block of 32 rows each, the weights of 64 channels at a time through a ring of three stages in LDS (one barrier per
-// 64 channels), the rows four pieces ahead in registers, scale and shift as tables in LDS, read before the barrier.  Bound: what a compute unit takes
-// from L2 (32 KB per piece in 0.9 us).  DenseNet-121, four members at batch 32, 14 x 14, 288 / 480 / 672 / 960 -> 128 channels: 17.2 / 22.0 / 26.0 / 32.0 us on the
-// 128x64 tile, 15.2 / 18.2 / 21.3 / 25.0 here.
+// 64 channels), the rows four pieces ahead in registers (three for the first of every four: a row may end after
+// any piece, so the compiler's wait there counts as if the piece before had been the last), scale and shift as tables in LDS, read before the barrier.  A piece
+// takes 0.9 us, that wait included, for 32 KB from L2.  DenseNet-121, four members at batch 32, 14 x 14, 288 / 480 / 672 / 960 -> 128 channels: 19.1 / 23.8 / 27.2 / 33.3 us on the
+// 128x64 tile, 16.0 / 19.2 / 20.8 / 25.4 here.
 constexpr int LW = LONG_WAVES, LK = LONG_K;   // (the tables of the longest row leave room for two workgroups per compute unit)
 
 __global__ void __launch_bounds__(LW * 64, 2) conv_long_kernel(KArgs a) {
   constexpr int NB = 4, BN = 128, NS = 3, STAGE = BN * 128, D = 4;   // columns; stages of the weights' ring; pieces of a row in registers
   constexpr int AT_PATCH = NS * STAGE, AT_BIAS = AT_PATCH + LW * 4096, AT_SHIFT = AT_BIAS + BN * 4, AT_SCALE = AT_SHIFT + LK * 4;
   __shared__ __attribute__((aligned(1024))) uint8_t smem[AT_SCALE + LK * 4];   // (one array: operand reads must not wait for the direct loads)
-  static_assert(sizeof(smem) <= 80 * 1024, "two workgroups per compute unit");   // (one array: operand reads must not wait for the direct loads)
+  static_assert(sizeof(smem) <= 80 * 1024, "two workgroups per compute unit");
   float* const bias_s = reinterpret_cast<float*>(smem + AT_BIAS);
   float* const shift_s = reinterpret_cast<float*>(smem + AT_SHIFT);
   float* const scale_s = reinterpret_cast<float*>(smem + AT_SCALE);
@@ -422,8 +425,9 @@ int launch_stream(const Launch& L, const KArgs& args, int nb, int nch, void* str
   }
   share_workgroups(rows, most, L.n, 256, groups);
   for (int i = 0; i < L.n; ++i) {
+    if (a.d[i].Cop > nb * 32) return (int)hipErrorInvalidValue;   // (a workgroup holds the weights of all columns)
     a.first_block[i] = (int32_t)blocks;
-    blocks += groups[i] * ((a.d[i].Cop + nb * 32 - 1) / (nb * 32));
+    blocks += groups[i];
   }
   for (int i = L.n; i <= FI_MAX_GROUP; ++i) a.first_block[i] = (int32_t)blocks;
   const int n = (int)blocks;
