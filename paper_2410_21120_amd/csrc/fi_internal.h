@@ -61,7 +61,8 @@ FI_HD inline int tile_bn(int t) { return (t == T_128x128 || t == T_256x128 || t 
 // Tiles of the K_CONV_KWAVE kernels: side of the square tile x waves that share its reduction (the bits depend on the waves, not
 // on the side; fp32 takes the first two, bf16 the last two).  KW_SCALAR is added for
 // fp32 tensors whose channel stride four does not divide, KW_RGB for those of them with one to three channels whose weights and
-// input patch fit LDS: a kernel of its own, which has no tile choice (the rule looks at the node's own shape: the sums are ordered differently).
+// input patch fit LDS: a kernel of its own, which has no tile choice.  Its sums are ordered differently, so the rule looks at the
+// node's own shape and the handle's max_batch only: a member's bits depend on neither its co-members nor the batch of a pass, but may differ between handles of another max_batch.
 enum KwaveTile : int32_t { KW_64x4 = 0, KW_32x8 = 1, KW_64x8 = 2, KW_NTILES, KW_SCALAR = 8, KW_RGB = 16 };
 constexpr int64_t KW_RGB_LDS = 64 << 10;
 inline int64_t rgb_lds(int64_t k, int64_t kw, int64_t stride, int64_t C) {   // bytes: 32 outputs' weights, the patch under 16 x 16 pixels

@@ -1390,8 +1390,8 @@ __global__ void __launch_bounds__(256) dwconv_strip_kernel(KArgs a) {
 }
 
 // 3x3 stride 1, fp32 rows, two rows of four outputs per thread: the four input rows are loaded once (three pixels per output instead of four and a
-// half).  Bound: the vector cache's loads.  Two members at batch 32, strip kernel -> this one: 112 x 112 x 16 39.5 -> 35.0 us, 56 x 56 x 72 40.5 ->
-// 37.8, 14 x 14 x 672 29.2 -> 25.9.  Every output adds its taps in the strip kernel's order: the same bits.
+// half).  Bound: the vector cache's loads.  Two members at batch 32, strip kernel -> this one: 112 x 112 x 16 40.7 -> 35.8 us, 56 x 56 x 72 38.4 ->
+// 33.8, 14 x 14 x 672 29.3 -> 24.4.  Every output adds its taps in the strip kernel's order: the same bits.
 __global__ void __launch_bounds__(256) dwconv_block_kernel(KArgs a) {
   constexpr int S = 4, NPIX = S + 2;
   int p, bid;

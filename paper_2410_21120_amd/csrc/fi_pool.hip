@@ -1,11 +1,11 @@
 // 3x3 stride-1 convolution of 64 to 64 channels on wide images, with the 2x2 stride-2 max-pool that alone reads it.
 //
 // VGG-16's second layer, 224 x 224: wider than a patch of consecutive pixels can be, so the tile kernel fetched every pixel nine
-// times (354 us at batch 64), wrote 411 MB and the pooling launch read them back (86 us).  Here a workgroup of eight waves walks blocks of 16 x 16
+// times (388 us at batch 64), wrote 411 MB and the pooling launch read them back (87 us).  Here a workgroup of eight waves walks blocks of 16 x 16
 // pixels: the patch under the next block comes into LDS by direct loads (pixels outside the image as zeros, so no tap is masked) while this
 // one is multiplied, a wave holds the weights of 32 output channels as operands for life (six taps in registers, three in LDS), and the pool
-// is taken between the lanes of the accumulators' layout, so that a quarter of the output leaves.  214 to 225 us for both launches, 1.1 PFLOP/s.  Bound: a block takes
-// 4.4 us, of which the matrix instructions need 1.9: the phases (addresses, multiply, pool) do not overlap, as the waves meet at every block.
+// is taken between the lanes of the accumulators' layout, so that a quarter of the output leaves.  217 to 240 us for both launches (233 alone, 1.02 PFLOP/s).  Bound: a block takes
+// 4.4 to 4.9 us, of which the matrix instructions need 1.9: the phases (addresses, multiply, pool) do not overlap, as the waves meet at every block.
 // Tried: pooling the rounded values with shuffles 270 us; masks from divisions per load 222.
 //
 // The order of the sums is the tile kernel's (tap after tap, 16 channels per instruction), so are the bits.
