@@ -521,7 +521,7 @@ static void take_stem_launches(fi_dag* g) {
 // patch kernel holds (below: its 256-row patches), whose ONLY reader is a 2x2 stride-2 max-pool: one launch, carried by the pool node; the convolution's
 // output is stored nowhere.  Same bits as the separate launches.  The kernel fills every compute unit's registers for its whole life, so it is
 // taken where no other lane needs them: VGG-16 at batch 64 2513 -> 2434 us; a three-model DAG at batch 8 on three lanes 1074 -> 1093 with it, 1062 without.
-// The batch does not matter: 33 x 97 to 512 x 512, one to three members of 1 to 32 images, 118 launches are ahead of the two, from 1 us of 30 (33 x 97, one image) to
+// The batch does not matter: 33 x 97 to 512 x 512, one to three members of 1 to 32 images, 134 launches are ahead of the two, from 1 us of 30 (33 x 97, one image) to
 // a third (224 x 224, one image 39.8 -> 31.4 with the layers around it, 8 109 -> 81, 32 334 -> 225).
 static void take_pool_launches(fi_dag* g) {
   if (g->opts.separate_stem || g->wdtype != FI_BF16 || g->n_lanes > 1) return;
