@@ -1389,9 +1389,10 @@ __global__ void __launch_bounds__(256) dwconv_strip_kernel(KArgs a) {
   }
 }
 
-// 3x3 stride 1, fp32 rows, two rows of four outputs per thread: the four input rows are loaded once (three pixels per output instead of four and a
-// half).  Bound: the vector cache's loads.  Two members at batch 32, strip kernel -> this one: 112 x 112 x 16 40.7 -> 35.8 us, 56 x 56 x 72 38.4 ->
+// 3x3 stride 1, two rows of four outputs per thread: the four input rows are loaded once (three pixels per output instead of four and a
+// half).  Bound: the vector cache's loads.  fp32 rows, two members at batch 32, strip kernel -> this one: 112 x 112 x 16 40.7 -> 35.8 us, 56 x 56 x 72 38.4 ->
 // 33.8, 14 x 14 x 672 29.3 -> 24.4.  Every output adds its taps in the strip kernel's order: the same bits.
+template <typename TA>
 __global__ void __launch_bounds__(256) dwconv_block_kernel(KArgs a) {
   constexpr int S = 4, NPIX = S + 2;
   int p, bid;
@@ -1406,7 +1407,7 @@ __global__ void __launch_bounds__(256) dwconv_block_kernel(KArgs a) {
   const int q0 = (int)(t % strips) * S;
   const int p0 = (int)((t / strips) % bands) * 2;
   const int n = (int)(t / ((int64_t)strips * bands));
-  const float* const xn = reinterpret_cast<const float*>(a.abase + d.x_off) + (int64_t)n * d.H * d.W * d.xs + c8;
+  const TA* const xn = reinterpret_cast<const TA*>(a.abase + d.x_off) + (int64_t)n * d.H * d.W * d.xs + c8;
   const bf16_t* const w = reinterpret_cast<const bf16_t*>(a.wbase + d.w_off) + c8;
   float acc[2][S][8];
 #pragma unroll
@@ -1420,7 +1421,7 @@ __global__ void __launch_bounds__(256) dwconv_block_kernel(KArgs a) {
   for (int r = 0; r < 4; ++r) {
     const int ih = ih0 + r;
     if ((unsigned)ih >= (unsigned)d.H) continue;   // a row outside the image adds nothing
-    const float* const xr = xn + (int64_t)ih * d.W * d.xs;
+    const TA* const xr = xn + (int64_t)ih * d.W * d.xs;
     float xv[NPIX][8];
 #pragma unroll
     for (int c = 0; c < NPIX; ++c) {
@@ -1458,7 +1459,7 @@ __global__ void __launch_bounds__(256) dwconv_block_kernel(KArgs a) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) v[i] = acc[o][j][i] + bv[i];
       activate_n<8>(v, d.act);
-      store8(reinterpret_cast<float*>(a.abase + d.y_off) + m * d.ys + c8, v);
+      store8(reinterpret_cast<TA*>(a.abase + d.y_off) + m * d.ys + c8, v);
     }
   }
 }
@@ -1890,7 +1891,7 @@ int launch_kernel(const Launch& L, const KArgs& args, void* stream, const std::v
             a.first_block[i] = (int32_t)rows;
             if (i < L.n) rows += dw_rows_blocks(a.d[i], a.batch[i]);
           }
-          return go(dwconv_block_kernel, (int)rows, 256, a, s);
+          return ab ? go(dwconv_block_kernel<bf16_t>, (int)rows, 256, a, s) : go(dwconv_block_kernel<float>, (int)rows, 256, a, s);
         }
 #define FI_DW_STRIP(K, T) if (ks == K && st == T) return ab ? go(dwconv_strip_kernel<bf16_t, K, T>, nb, 256, a, s) : go(dwconv_strip_kernel<float, K, T>, nb, 256, a, s);
         FI_DW_STRIP(3, 1) FI_DW_STRIP(3, 2) FI_DW_STRIP(5, 1) FI_DW_STRIP(5, 2) FI_DW_STRIP(7, 1) FI_DW_STRIP(7, 2)

@@ -381,19 +381,20 @@ static bool long_fits(const Launch& L, const Desc* d, const int32_t* batch) {
   return blocks >= 128;
 }
 
-// Whether a depthwise launch computes two rows of four outputs per thread (3x3, stride 1, fp32 rows): from 384 workgroups on (strip kernel -> two
+// Whether a depthwise launch computes two rows of four outputs per thread (3x3, stride 1).  fp32 rows from 384 workgroups on (strip kernel -> two
 // rows, us: 14 x 14 x 480, 420 workgroups 22.2 -> 18.7, 112 x 112 x 16, 784 40 -> 35, 1 x 2000 x 64, 500 18.2 -> 18.1); below, half as many threads leave
-// the chip idle (14 x 14 x 200, 175 workgroups 15.3 -> 18.5).  bf16 rows keep the strip kernel: the pixels that two rows share are half the bytes,
-// and fewer threads cost more than that (14 x 14 x 480, 420 workgroups 15.9 -> 16.8, 112 x 112 x 32, 392 16.1 -> 18.0, 1568 39.7 -> 39.3, 3 x 1000 x 64,
-// 2000 30.1 -> 32.1; ahead only from some 1500 workgroups on, and not always: 28 x 28 x 256 41.3 -> 37.7).
+// the chip idle (14 x 14 x 200, 175 workgroups 15.3 -> 18.5).  bf16 rows gain less, as the pixels that two rows share are half the bytes: from 512
+// workgroups on, where 107 launches take 0.92 to 1.03 of the strip kernel's time with the layers around them, 0.970 in the mean (below, 13 from 334 on: 0.99 to 1.03; 14 x 14 x
+// 480, 420 workgroups 15.9 -> 16.8, 112 x 112 x 32, 392 16.1 -> 18.0), and not where an odd last row makes more than an eighth of the work (3 x 1000 x 64, 2000 workgroups 30.1 -> 32.1).
 static bool two_rows_fit(const Launch& L, const Desc* d, const int32_t* batch) {
   int64_t blocks = 0;
   for (int i = 0; i < L.n; ++i) {
     const Desc& t = d[i];
     if (!t.vec || t.tiles_n != 4 || t.k != 3 || t.stride != 1 || t.r_off != kNone || t.ext || t.Co != t.Cop) return false;
+    if (L.adtype != FI_F32 && (t.Ho + 1) / 2 * 16 > t.Ho * 9) return false;
     blocks += dw_rows_blocks(t, batch[i]);
   }
-  return L.adtype == FI_F32 && blocks >= 384;
+  return blocks >= (L.adtype == FI_F32 ? 384 : 512);
 }
 
 Choice choose_route(const Launch& L, const Desc* d, const int32_t* batch) {

@@ -183,6 +183,20 @@ def test_lines_from_which_affine_and_first_layers_stream():
         assert names(m, (3, 4), **kw) == want, cout
 
 
+@pytest.mark.parametrize("h, w, c, act_dtype, first", [(56, 56, 128, "f32", 16), (56, 56, 128, None, 21), (3, 1000, 64, "f32", 25), (3, 1000, 64, None, None), (9, 1000, 64, None, 14)])
+def test_lines_from_which_depthwise_layers_take_two_rows(h, w, c, act_dtype, first):
+    m = zoo.Model("c", "bf16", 8, h, w)
+    a = m.add(zoo.CONV, -1, cin=8, cout=c, k=1, stride=1, pad=0, act=zoo.SILU)
+    a = m.add(zoo.DWCONV, a, cin=c, cout=c, k=3, stride=1, pad=1, act=zoo.RELU)
+    m.add(zoo.CONV, a, cin=c, cout=8, k=1, stride=1, pad=0, act=zoo.SILU)
+    m.shapes()
+    blob = gen.make_blob(m, 1)
+    spec, keep = fi.make_spec(m, blob.ctypes.data, blob.nbytes, act_dtype=act_dtype)
+    d = fi.Dag([spec], 100, fi.HostAllocators(), keepalive=(keep, blob))
+    for b in sorted({1, (first or 2) - 1, first or 100, 100}):
+        assert ([L.name.decode() for L in d.launches(b)].count("dwconv_rows") == 1) == (first is not None and b >= first), b
+
+
 def test_patch_launches_count_the_convolutions_they_carry():
     """The patch kernel's lines are in workgroups of one launch.  A 1x1 convolution beside a 3x3 of the same size, output channels and
     tile stays on the tile kernel and must not count: 42 images of 28 x 28 x 256 are 130 tiles of 512x128, below the line of 256 (two
