@@ -325,7 +325,7 @@ static bool streams(const Desc& t, int batch, bool wide, int past) {
 //   fp32, 33 to 64           16 -> 64, 512 8.7 -> 9.1, 1024 11.1 -> 9.6; 64 -> 64, 1312 12.0 -> 12.0, 2048 14.2 -> 13.4; 120 -> 40, 1568 13.0 -> 13.9, 32768 142 -> 151 (never)
 //   fp32, 65 to 128          32 -> 128, 512 10.8 -> 11.8, 1024 14.6 -> 13.3; 128 -> 128, 1024 15.9 -> 18.4, 1312 19.1 -> 18.9; 184 -> 128, 1568 22.9 -> 21.8
 //   a residual               bf16 24 -> 24, 1024 8.8 -> 7.4; 40 -> 40, 1024 8.9 -> 8.3; 64 -> 64, 1024 9.0 -> 10.1, 65536 145 -> 149 (never); fp32 64 -> 32, 1024 9.6 -> 10.3,
-//                            4096 18.6 -> 16.9, 65536 193 -> 201; 40 -> 40, 16384 44 -> 50 (never)
+//                            4096 18.6 -> 16.9, 65536 193 -> 201; 40 -> 40, 16384 44 -> 50 (never); bf16 rows of six pieces, 14 layers 0.98 to 1.025 (never)
 //   an affine stage          (against the R_LONG kernel) 64 channels, 1024 10.4 -> 11.3, 2048 13.2 -> 12.8; 256, 2048 19.8 -> 19.9, 3008 27.4 -> 23.6; 384, 2048 23.1 -> 25.0,
 //                            3008 33.8 -> 31.8
 //   the four-channel input   8 columns, 512 9.0 -> 8.0; 128, fp32, 512 13.0 -> 11.9
@@ -333,7 +333,7 @@ static int64_t stream_line(int form, bool wide, bool residual, int cop, int piec
   if (cop > 128 || pieces > 6) return -1;
   if (form == 1) return std::max(2048, 512 * pieces);
   if (form == 2) return residual ? -1 : 512;
-  if (residual) return cop <= (wide ? 32 : 40) ? 1024 * pieces : -1;
+  if (residual) return cop <= (wide ? 32 : 40) && (wide || pieces <= 5) ? 1024 * pieces : -1;
   if (cop <= 32) return 512 * pieces;
   if (!wide) return pieces <= (cop <= 64 ? 3 : 4) ? 1024 * pieces : -1;
   if (cop <= 64) return pieces <= 2 ? 1024 * pieces : -1;
@@ -344,7 +344,7 @@ static int64_t stream_line(int form, bool wide, bool residual, int cop, int piec
 static bool stream_fits(const Launch& L, const Desc* d, const int32_t* batch, Choice* c) {
   const bool wide = L.adtype != FI_BF16;
   const int ce = wide ? 32 : 64;   // elements of a 128-byte piece
-  int64_t tiles = 0;
+  int64_t tiles = 0, pieced = 0;   // pieced: bytes of output rows that are not whole lines
   int cop = 0, pieces = 0;
   bool residual = false;
   auto form = [](const Desc& t) { return t.Cp == 4 ? 2 : t.pre_kind; };   // (the kernel's PRE)
@@ -356,10 +356,15 @@ static bool stream_fits(const Launch& L, const Desc* d, const int32_t* batch, Ch
     cop = std::max(cop, t.Cop);
     pieces = std::max(pieces, ((t.Cp == 4 ? 36 : t.Cp) + ce - 1) / ce);
     residual = residual || t.r_off != kNone;
+    if ((((int64_t)t.Cop | t.ys) * (wide ? 4 : 2)) & 127) pieced += m * t.Cop * (wide ? 4 : 2);
   }
   const int64_t line = stream_line(form(d[0]), wide, residual, cop, pieces);
   if (line < 0 || tiles < line) return false;
   if (wide && cop <= 32 && pieces + residual > 2 && tiles > 16384) return false;   // (long fp32 rows, narrow outputs: 96 -> 24 above)
+  // fp32 rows that are not whole lines, of more than the memory-side cache's 256 MB (somewhat less: the input is there, too): through the cache they cost
+  // more than on the tile (layers around them included; 16 -> 120, 269 MB 324 -> 358 us, 64 -> 120, 459 MB 519 -> 561, 48 -> 56, 474 MB 781 -> 840, 48 -> 80, 241 MB 410 ->
+  // 425; 64 -> 120, 162 MB 228 -> 180, 40 -> 80, 109 MB 182 -> 163; the four-channel input -> 88, 609 MB 831 -> 857, -> 112, 172 MB 126 -> 106), and past it still more.
+  if (wide && pieced > (224ll << 20)) return false;
   c->nb = form(d[0]) == 1 || cop > 64 ? 4 : cop > 32 ? 2 : 1;
   c->nch = pieces <= 4 ? pieces : 6;
 #define FI_BUILT(WIDE, PRE, NB, NCH) if (wide == (WIDE) && form(d[0]) == (PRE) && c->nb == (NB) && c->nch == (NCH)) return true;

@@ -141,8 +141,8 @@ def test_few_channel_launches_hold_one_channel_count():
     # images of 64 x 64 are 128 blocks of 32 rows; from the first batch of `lines` on the layer streams, from the second on no more
     (64, 32, None, False, (4, None)), (64, 128, None, False, (8, None)), (128, 64, None, False, (16, None)), (192, 64, None, False, (24, None)), (256, 64, None, False, None),
     (256, 128, None, False, (32, None)), (320, 96, None, False, None), (328, 24, None, False, (24, None)), (136, 136, None, False, None),
-    (16, 64, "f32", False, (8, None)), (64, 64, "f32", False, (16, None)), (120, 40, "f32", False, None), (128, 128, "f32", False, (10, None)), (96, 24, "f32", False, (12, 129)),
-    (24, 24, None, True, (8, None)), (40, 40, None, True, (8, None)), (200, 40, None, True, None), (64, 64, None, True, None), (40, 40, "f32", True, None), (64, 32, "f32", True, (16, 129)),
+    (16, 64, "f32", False, (8, None)), (64, 64, "f32", False, (16, None)), (120, 40, "f32", False, None), (128, 128, "f32", False, (10, None)), (16, 120, "f32", False, (7, 120)), (16, 96, "f32", False, (7, None)), (8, 16, "f32", False, (4, None)), (96, 24, "f32", False, (12, 129)),
+    (24, 24, None, True, (8, None)), (40, 40, None, True, (8, None)), (320, 24, None, True, (40, None)), (384, 24, None, True, None), (200, 40, None, True, None), (64, 64, None, True, None), (40, 40, "f32", True, None), (64, 32, "f32", True, (16, 129)),
     (32, 16, "f32", True, (8, None))])
 def test_lines_from_which_pointwise_rows_stream(cin, cout, act_dtype, residual, lines):
     """Which 1x1 layers a pass issues to the streaming kernel, by its images: one image below and at every line."""
@@ -176,6 +176,10 @@ def test_lines_from_which_affine_and_first_layers_stream():
         a = m.add(zoo.CONV, a, cin=cin, cout=128, k=1, stride=1, pad=0, act=zoo.RELU)
         m.add(zoo.CONV, a, cin=128, cout=8, k=1, stride=1, pad=0, act=zoo.SILU)
         assert names(m, (3, 4, 15, 16, 24)) == want, (cin, act)
+    m = zoo.Model("c", "bf16", 3, 128, 128)
+    a = m.add(zoo.CONV, -1, cin=3, cout=120, k=3, stride=2, pad=1, act=zoo.RELU)
+    m.add(zoo.CONV, a, cin=120, cout=8, k=1, stride=1, pad=0, act=zoo.SILU)
+    assert names(m, (4, 119, 120), act_dtype="f32") == [["conv_stream"], ["conv_stream"], []]
     for cout, kw, want in ((16, {}, [[], ["conv_stream"]]), (128, {"act_dtype": "f32"}, [[], ["conv_stream"]]), (136, {}, [[], []])):
         m = zoo.Model("c", "bf16", 3, 128, 128)
         a = m.add(zoo.CONV, -1, cin=3, cout=cout, k=3, stride=2, pad=1, act=zoo.HARDSWISH)
