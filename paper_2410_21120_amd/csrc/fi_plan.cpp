@@ -374,13 +374,14 @@ static bool stream_fits(const Launch& L, const Desc* d, const int32_t* batch, Ch
 }
 
 // Whether a launch is one of affine stages and rows of any length.  From 128
-// workgroups on: fewer leave the chip idle (7 x 7, 640 channels, four members, 52 workgroups 17.0 us on the tile, 19.7 here).
+// workgroups on: fewer leave the chip idle (7 x 7, 640 channels, four members, 52 workgroups 17.0 us on the tile, 19.7 here).  Not for 64 columns or fewer, which
+// leave half of the kernel's 128 empty (12 layers with those around them 0.97 to 1.05 of the tile's time; 96 columns, 16 layers, 0.75 to 0.99).
 static bool long_fits(const Launch& L, const Desc* d, const int32_t* batch) {
   constexpr int rows = LONG_WAVES * 32;
   int64_t blocks = 0;
   for (int i = 0; i < L.n; ++i) {
     const Desc& t = d[i];
-    if (!streams(t, batch[i], L.adtype != FI_BF16, rows) || t.pre_kind != 1 || t.Cp > LONG_K) return false;
+    if (!streams(t, batch[i], L.adtype != FI_BF16, rows) || t.pre_kind != 1 || t.Cp > LONG_K || t.Cop <= 64) return false;
     blocks += ((int64_t)batch[i] * t.Ho * t.Wo + rows - 1) / rows * ((t.Cop + 127) / 128);
   }
   return blocks >= 128;

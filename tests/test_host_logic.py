@@ -180,6 +180,13 @@ def test_lines_from_which_affine_and_first_layers_stream():
     a = m.add(zoo.CONV, -1, cin=3, cout=120, k=3, stride=2, pad=1, act=zoo.RELU)
     m.add(zoo.CONV, a, cin=120, cout=8, k=1, stride=1, pad=0, act=zoo.SILU)
     assert names(m, (4, 119, 120), act_dtype="f32") == [["conv_stream"], ["conv_stream"], []]
+    for cout, want in ((64, []), (72, ["conv_long"])):   # (the long-row kernel has 128 columns)
+        m = zoo.Model("c", "bf16", 8, 64, 64)
+        a = m.add(zoo.CONV, -1, cin=8, cout=384, k=1, stride=1, pad=0, act=zoo.SILU)
+        a = m.add(zoo.DWCONV, a, cin=384, cout=384, k=1, stride=1, pad=0, act=zoo.RELU)
+        a = m.add(zoo.CONV, a, cin=384, cout=cout, k=1, stride=1, pad=0, act=zoo.RELU)
+        m.add(zoo.CONV, a, cin=cout, cout=8, k=1, stride=1, pad=0, act=zoo.SILU)
+        assert names(m, (4, 15)) == [want, want], cout
     for cout, kw, want in ((16, {}, [[], ["conv_stream"]]), (128, {"act_dtype": "f32"}, [[], ["conv_stream"]]), (136, {}, [[], []])):
         m = zoo.Model("c", "bf16", 3, 128, 128)
         a = m.add(zoo.CONV, -1, cin=3, cout=cout, k=3, stride=2, pad=1, act=zoo.HARDSWISH)
