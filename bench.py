@@ -332,15 +332,15 @@ def main():
 # 1 GiB device-to-device copy).  The figures belong to one exact set of sources: when any of them
 # has changed since the counters were taken the entry no longer applies and traffic is null.
 COUNTERS = {
-    "sources_sha256": "c080af15fe3f39172d4bd6357f7acec9a3568cb586cff4c3cdeecedcb6464be4",
+    "sources_sha256": "3c4acb8845afe606c529080a2f5ac716e242dc4e1c05bebbe82ff29cc1f45edb",
     "workload": "cfg4",
     "fetch_scale": 2.0, "write_scale": 1.0,
     "kernels": {   # kernel name -> launches and KiB per step
-        "conv_chain": {"launches_per_step": 20, "fetch_kib_per_step": 1405160.7, "write_kib_per_step": 2579475.3},
-        "conv_mfma_128x128": {"launches_per_step": 34, "fetch_kib_per_step": 1000095.0, "write_kib_per_step": 1593139.7},
-        "conv_stream": {"launches_per_step": 4, "fetch_kib_per_step": 50573.1, "write_kib_per_step": 100352.0},
-        "conv_mfma_256x128": {"launches_per_step": 14, "fetch_kib_per_step": 471289.2, "write_kib_per_step": 250880.0},
-        "conv_patch": {"launches_per_step": 14, "fetch_kib_per_step": 201434.4, "write_kib_per_step": 150528.0},
+        "conv_chain": {"launches_per_step": 20, "fetch_kib_per_step": 1404900.5, "write_kib_per_step": 2579457.1},
+        "conv_mfma_128x128": {"launches_per_step": 34, "fetch_kib_per_step": 1000819.6, "write_kib_per_step": 1593125.7},
+        "conv_stream": {"launches_per_step": 4, "fetch_kib_per_step": 50573.3, "write_kib_per_step": 100352.0},
+        "conv_mfma_256x128": {"launches_per_step": 14, "fetch_kib_per_step": 471034.8, "write_kib_per_step": 250880.0},
+        "conv_patch": {"launches_per_step": 14, "fetch_kib_per_step": 201435.2, "write_kib_per_step": 150528.0},
     },
 }
 
